@@ -49,18 +49,56 @@ __device__ __forceinline__ uint32_t hash_slot(int32_t j, int lg) {
 }
 
 // ------------------------------------------------------------- analysis --
-__global__ void row_products_kernel(const int64_t *__restrict__ rpA, const int32_t *__restrict__ cA,
-                                    const int64_t *__restrict__ rpB, int64_t m, int64_t *__restrict__ w) {
-  const int64_t wid = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
-  const int64_t nw = ((int64_t)gridDim.x * blockDim.x) / WAVE;
-  for (int64_t i = wid; i < m; i += nw) {
+// w[i] = products of row i.  Sixteen lanes take a row's first 256 entries,
+// four loads each in flight, so a wave covers four rows of an ordinary graph
+// at once; a row with more entries is then summed by its whole block (one
+// wave per row left 48 of 64 lanes idle on rows of 16 entries, and the hubs
+// of a skewed graph ran 64 entries at a time to the end: R-MAT 18 157 us).
+constexpr int RP_BS = 256, RP_G = 16, RP_U = 4, RP_LONG = 256;
+__global__ void __launch_bounds__(RP_BS) row_products_kernel(const int64_t *__restrict__ rpA,
+                                                             const int32_t *__restrict__ cA,
+                                                             const int64_t *__restrict__ rpB, int64_t m,
+                                                             int64_t *__restrict__ w) {
+  constexpr int ROWS = RP_BS / RP_G;
+  __shared__ int64_t more[ROWS];
+  __shared__ int64_t tmp[RP_BS / WAVE + 1];
+  const int t = threadIdx.x, g = t / RP_G, l = t % RP_G;
+  // sum of the lengths of the B rows of entries p, p + stride, ... below e
+  auto take = [&](int64_t p, int64_t e, int64_t stride) {
     int64_t acc = 0;
-    for (int64_t p = rpA[i] + lane_id(); p < rpA[i + 1]; p += WAVE) {
-      const int32_t k = cA[p];
-      acc += rpB[k + 1] - rpB[k];
+    for (; p < e; p += stride * RP_U) {
+      int32_t k[RP_U];
+#pragma unroll
+      for (int u = 0; u < RP_U; u++) k[u] = p + u * stride < e ? cA[p + u * stride] : -1;
+#pragma unroll
+      for (int u = 0; u < RP_U; u++)
+        if (k[u] >= 0) acc += rpB[k[u] + 1] - rpB[k[u]];
     }
-    acc = wave_sum(acc);
-    if (lane_id() == 0) w[i] = acc;
+    return acc;
+  };
+  for (int64_t i0 = (int64_t)blockIdx.x * ROWS; i0 < m; i0 += (int64_t)gridDim.x * ROWS) {
+    const int64_t i = i0 + g;
+    int64_t a = 0, e = 0;
+    if (i < m) {
+      a = rpA[i];
+      e = rpA[i + 1];
+    }
+    int64_t acc = take(a + l, min(e, a + RP_LONG), RP_G);
+#pragma unroll
+    for (int d = RP_G / 2; d >= 1; d >>= 1) acc += __shfl_xor(acc, d, WAVE);
+    if (l == 0) {
+      more[g] = e - a > RP_LONG ? e - a : 0;
+      if (i < m) w[i] = acc;
+    }
+    __syncthreads();
+    for (int q = 0; q < ROWS; q++) {
+      if (more[q] == 0) continue;  // the same on every thread
+      const int64_t b = rpA[i0 + q] + RP_LONG, n = more[q] - RP_LONG;
+      int64_t tot;
+      block_excl_scan<RP_BS>(take(b + t, b + n, RP_BS), tmp, &tot);
+      if (t == 0) w[i0 + q] += tot;  // written by lane 0 of group q before the barrier
+    }
+    __syncthreads();  // more is rewritten by the next rows
   }
 }
 
@@ -69,12 +107,13 @@ struct Thresholds {
   int64_t t[NBIN - 1];  // bin b (1..) takes v with t[b-2] < v <= t[b-1]; last bin above
 };
 
-// info layout: [0..NBIN) counts, [NBIN..2NBIN) starts, [2NBIN..3NBIN) cursors,
-// [3NBIN..4NBIN) work counters, [4NBIN] sum of values, [SUMV..SUMV+NBIN)
-// per-bin sums of values, [SUMA..SUMA+NBIN) per-bin sums of A row lengths
-constexpr int SUMV = 4 * NBIN + 1;
-constexpr int SUMA = 5 * NBIN + 1;
-constexpr int INFO = 6 * NBIN + 2;
+// info layout: [0..NBIN) counts, [NBIN..2NBIN) starts, [SUM] sum of values,
+// [SUMV..SUMV+NBIN) per-bin sums of values, [SUMA..SUMA+NBIN) per-bin sums
+// of A row lengths (bin 0's sums stay 0)
+constexpr int SUM = 2 * NBIN;
+constexpr int SUMV = 2 * NBIN + 1;
+constexpr int SUMA = 3 * NBIN + 1;
+constexpr int INFO = 4 * NBIN + 2;
 
 __device__ __forceinline__ int bin_of(int64_t v, const Thresholds &th) {
   if (v <= 0) return 0;
@@ -84,69 +123,170 @@ __device__ __forceinline__ int bin_of(int64_t v, const Thresholds &th) {
   return NBIN - 1;
 }
 
-__global__ void bin_count(const int64_t *v, int64_t m, Thresholds th, int64_t *info, const int64_t *rpA,
-                          const int32_t *row_map) {
-  __shared__ int32_t cnt[NBIN];
-  __shared__ unsigned long long sv[NBIN], sa[NBIN];
-  __shared__ unsigned long long sum;
-  if (threadIdx.x < NBIN) { cnt[threadIdx.x] = 0; sv[threadIdx.x] = 0; sa[threadIdx.x] = 0; }
-  if (threadIdx.x == 0) sum = 0;
-  __syncthreads();
-  unsigned long long local = 0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m;
-       i += (int64_t)gridDim.x * blockDim.x) {
+// Binning without global atomics: every block takes one contiguous run of
+// rows, counts its rows per bin (bin_count), one block scans those counts
+// (bin_offsets), and the rows go to their bin's list at the block's offset
+// and their rank in the run (bin_scatter), so lists keep row order.  With an
+// atomic per wave and bin on the bins' cursors, which share a cache line,
+// the scatter was bound by those atomics (R-MAT 18: 211 us per pass for
+// 262,144 rows).  Up to BIN_SMALL rows one block does all three in a launch.
+constexpr int BIN_BS = 256;
+constexpr int BIN_MAXB = 1024;
+constexpr int BIN_SMALL = 4096;
+constexpr int BIN_Q = 3 * (NBIN - 1);  // per block: counts, value sums, A length sums of bins 1..
+
+// Counts, value sums and A length sums of rows i0, i0 + stride, ... below i1,
+// reduced over each wave into acc[.][wave].
+template <int BS>
+__device__ __forceinline__ void bin_tally(const int64_t *__restrict__ v, int64_t i0, int64_t i1, int64_t stride,
+                                          const Thresholds &th, const int64_t *__restrict__ rpA,
+                                          const int32_t *__restrict__ row_map, int64_t (*acc)[BS / WAVE]) {
+  int64_t q[BIN_Q];
+#pragma unroll
+  for (int b = 0; b < BIN_Q; b++) q[b] = 0;
+  for (int64_t i = i0; i < i1; i += stride) {
     const int64_t x = v[i];
     const int b = bin_of(x, th);
     const int64_t r = row_map ? row_map[i] : i;
-    atomicAdd(&cnt[b], 1);
-    atomicAdd(&sv[b], (unsigned long long)x);
-    atomicAdd(&sa[b], (unsigned long long)(rpA[r + 1] - rpA[r]));
-    local += (unsigned long long)x;
-  }
-  local = wave_sum(local);
-  if (lane_id() == 0) atomicAdd(&sum, local);
-  __syncthreads();
-  if (threadIdx.x < NBIN) {
-    atomicAdd((unsigned long long *)&info[threadIdx.x], (unsigned long long)cnt[threadIdx.x]);
-    atomicAdd((unsigned long long *)&info[SUMV + threadIdx.x], sv[threadIdx.x]);
-    atomicAdd((unsigned long long *)&info[SUMA + threadIdx.x], sa[threadIdx.x]);
-  }
-  if (threadIdx.x == 0) atomicAdd((unsigned long long *)&info[4 * NBIN], sum);
-}
-
-__global__ void bin_offsets(int64_t *info) {
-  if (threadIdx.x == 0) {
-    int64_t run = 0;
-    for (int b = 0; b < NBIN; b++) {
-      info[NBIN + b] = run;
-      info[2 * NBIN + b] = 0;
-      info[3 * NBIN + b] = 0;
-      run += info[b];
+    const int64_t len = rpA[r + 1] - rpA[r];
+#pragma unroll
+    for (int bb = 1; bb < NBIN; bb++) {
+      q[bb - 1] += b == bb ? 1 : 0;
+      q[NBIN - 2 + bb] += b == bb ? x : 0;
+      q[2 * (NBIN - 1) + bb - 1] += b == bb ? len : 0;
     }
   }
+#pragma unroll
+  for (int b = 0; b < BIN_Q; b++) {
+    const int64_t x = wave_sum(q[b]);
+    if (lane_id() == 0) acc[b][threadIdx.x / WAVE] = x;
+  }
 }
 
-// Rows go to their bin's list; each wave takes one slot range per bin with a
-// single atomic and places its rows by ballot rank.
-__global__ void bin_scatter(const int64_t *v, int64_t m, Thresholds th, int64_t *info, int32_t *lists,
-                            const int32_t *row_map) {
+// Places rows i0 .. i1-1 (a block's run) in their lists: base[b] = first
+// free place of bin b.  cnt: LDS, one row per wave.
+template <int BS>
+__device__ __forceinline__ void bin_place(const int64_t *__restrict__ v, int64_t i0, int64_t i1, const Thresholds &th,
+                                          const int32_t *__restrict__ row_map, int64_t *base, int32_t (*cnt)[NBIN],
+                                          int32_t *__restrict__ lists) {
+  constexpr int NW = BS / WAVE;
   const uint64_t lt = lanemask_lt();
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i0 = (int64_t)blockIdx.x * blockDim.x; i0 < m; i0 += stride) {
-    const int64_t i = i0 + threadIdx.x;
-    const int b = i < m ? bin_of(v[i], th) : 0;
+  const int w = threadIdx.x / WAVE;
+  for (int64_t t0 = i0; t0 < i1; t0 += BS) {
+    const int64_t i = t0 + threadIdx.x;
+    const int b = i < i1 ? bin_of(v[i], th) : 0;
+    int rank = 0;
 #pragma unroll
     for (int bb = 1; bb < NBIN; bb++) {
       const uint64_t mk = __ballot(b == bb);
-      if (mk == 0) continue;
-      const int leader = __ffsll((unsigned long long)mk) - 1;
-      long long p = 0;
-      if (lane_id() == leader)
-        p = (long long)atomicAdd((unsigned long long *)&info[2 * NBIN + bb], (unsigned long long)__popcll(mk));
-      p = __shfl(p, leader, WAVE);
-      if (b == bb) lists[info[NBIN + bb] + p + __popcll(mk & lt)] = row_map ? row_map[i] : (int32_t)i;
+      if (b == bb) rank = __popcll(mk & lt);
+      if (lane_id() == 0) cnt[w][bb] = __popcll(mk);
+    }
+    __syncthreads();
+    if (b > 0) {
+      int64_t p = base[b] + rank;
+      for (int q = 0; q < w; q++) p += cnt[q][b];
+      lists[p] = row_map ? row_map[i] : (int32_t)i;
+    }
+    __syncthreads();
+    if (threadIdx.x > 0 && threadIdx.x < NBIN) {
+      int64_t p = base[threadIdx.x];
+      for (int q = 0; q < NW; q++) p += cnt[q][threadIdx.x];
+      base[threadIdx.x] = p;
+    }
+    __syncthreads();
+  }
+}
+
+__global__ void __launch_bounds__(BIN_BS) bin_count(const int64_t *__restrict__ v, int64_t m, int64_t chunk,
+                                                    Thresholds th, int64_t *__restrict__ part,
+                                                    const int64_t *__restrict__ rpA,
+                                                    const int32_t *__restrict__ row_map) {
+  __shared__ int64_t acc[BIN_Q][BIN_BS / WAVE];
+  const int64_t i0 = (int64_t)blockIdx.x * chunk;
+  bin_tally<BIN_BS>(v, i0 + threadIdx.x, min(m, i0 + chunk), BIN_BS, th, rpA, row_map, acc);
+  __syncthreads();
+  if (threadIdx.x < BIN_Q) {
+    int64_t x = 0;
+    for (int q = 0; q < BIN_BS / WAVE; q++) x += acc[threadIdx.x][q];
+    part[(int64_t)threadIdx.x * BIN_MAXB + blockIdx.x] = x;
+  }
+}
+
+// info's counts, starts and sums from the totals of the BIN_Q quantities.
+__device__ __forceinline__ void bin_info(const int64_t *tot, int64_t *info) {
+  int64_t run = 0, sum = 0;
+  info[0] = info[NBIN] = info[SUMV] = info[SUMA] = 0;
+  for (int b = 1; b < NBIN; b++) {
+    info[b] = tot[b - 1];
+    info[NBIN + b] = run;
+    run += tot[b - 1];
+    sum += tot[NBIN - 2 + b];
+    info[SUMV + b] = tot[NBIN - 2 + b];
+    info[SUMA + b] = tot[2 * (NBIN - 1) + b - 1];
+  }
+  info[SUM] = sum;
+}
+
+// One wave per quantity: the counts become exclusive prefixes over the
+// blocks, the sums are added up.
+__global__ void __launch_bounds__(1024) bin_offsets(int64_t *__restrict__ part, int nblk, int64_t *__restrict__ info) {
+  __shared__ int64_t tot[BIN_Q];
+  const int q = threadIdx.x / WAVE, l = lane_id();
+  if (q < BIN_Q) {
+    int64_t run = 0;
+    for (int b0 = 0; b0 < nblk; b0 += WAVE) {
+      const int b = b0 + l;
+      const int64_t x = b < nblk ? part[(int64_t)q * BIN_MAXB + b] : 0;
+      const int64_t inc = wave_incl_scan(x);
+      if (q < NBIN - 1 && b < nblk) part[(int64_t)q * BIN_MAXB + b] = run + inc - x;
+      run += lane63(inc);
+    }
+    if (l == 0) tot[q] = run;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) bin_info(tot, info);
+}
+static_assert(BIN_Q <= 16, "one wave of bin_offsets per quantity");
+
+__global__ void __launch_bounds__(BIN_BS) bin_scatter(const int64_t *__restrict__ v, int64_t m, int64_t chunk,
+                                                      Thresholds th, const int64_t *__restrict__ part,
+                                                      const int64_t *__restrict__ info, int32_t *__restrict__ lists,
+                                                      const int32_t *__restrict__ row_map) {
+  __shared__ int64_t base[NBIN];
+  __shared__ int32_t cnt[BIN_BS / WAVE][NBIN];
+  if (threadIdx.x > 0 && threadIdx.x < NBIN)
+    base[threadIdx.x] = info[NBIN + threadIdx.x] + part[(int64_t)(threadIdx.x - 1) * BIN_MAXB + blockIdx.x];
+  __syncthreads();
+  const int64_t i0 = (int64_t)blockIdx.x * chunk;
+  bin_place<BIN_BS>(v, i0, min(m, i0 + chunk), th, row_map, base, cnt, lists);
+}
+
+__global__ void __launch_bounds__(1024) bin_small(const int64_t *__restrict__ v, int64_t m, Thresholds th,
+                                                  const int64_t *__restrict__ rpA, const int32_t *__restrict__ row_map,
+                                                  int64_t *__restrict__ info, int32_t *__restrict__ lists) {
+  __shared__ int64_t acc[BIN_Q][1024 / WAVE];
+  __shared__ int64_t tot[BIN_Q];
+  __shared__ int64_t base[NBIN];
+  __shared__ int32_t cnt[1024 / WAVE][NBIN];
+  bin_tally<1024>(v, threadIdx.x, m, 1024, th, rpA, row_map, acc);
+  __syncthreads();
+  if (threadIdx.x < BIN_Q) {
+    int64_t x = 0;
+    for (int q = 0; q < 1024 / WAVE; q++) x += acc[threadIdx.x][q];
+    tot[threadIdx.x] = x;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    bin_info(tot, info);
+    int64_t run = 0;
+    for (int b = 1; b < NBIN; b++) {
+      base[b] = run;
+      run += tot[b - 1];
     }
   }
+  __syncthreads();
+  bin_place<1024>(v, 0, m, th, row_map, base, cnt, lists);
 }
 
 // Sort key putting heavy rows first: descending in a 16-bit code of the
@@ -379,30 +519,56 @@ __device__ __forceinline__ void for_products(const int64_t *__restrict__ rpA, co
   }
 }
 
-// Rows of a bin are handed out from a global counter, `step` consecutive
-// rows per fetch: thread 0 claims them and the block reads the first index
-// back through LDS.  (One row per fetch left bins of millions of small rows
-// bound by the throughput of atomics on that one counter.)  Callers fetch
-// before their loop and again at the end of its body, and walk the claimed
-// rows in an inner counted loop, so every loop test is on a block-uniform
-// value and no thread-dependent branch leads into a loop header.  (With the
-// fetch at the top of an endless loop, the compiler was free to route
-// threads other than 0 from the end of the body straight past the fetch; the
-// generated code then kept those lanes in an inner loop over the same row
-// that they never left.)
-__device__ __forceinline__ int64_t next_row(int64_t *ctr, int step = 1) {
+// Rows of a bin are handed out dynamically, `step` consecutive rows per
+// fetch: thread 0 claims them and the block reads their number back through
+// LDS.  The counter is cut into `nsh` shards, each in a cache line of its
+// own: chunk q of shard s covers rows (q nsh + s) step onwards, and a block
+// draws from shard blockIdx mod nsh only.  Device-scope atomics of all XCDs
+// on one address take turns at the memory side, about 12 ns each, so one
+// counter per bin put a floor of 12 ns per row under every bin (ER n =
+// 50,021, d = 16: sym_hash and num_hash at 314 to 414 us for 25,000 rows
+// each, whatever their work).  Sixteen lines lift that to 0.8 ns; rows of a
+// bin sorted heaviest first stay evenly spread, since shards interleave.
+// Callers fetch before their loop and again at the end of its body, and walk
+// the claimed rows in an inner counted loop, so every loop test is on a
+// block-uniform value and no thread-dependent branch leads into a loop
+// header.  (With the fetch at the top of an endless loop, the compiler was
+// free to route threads other than 0 from the end of the body straight past
+// the fetch; the generated code then kept those lanes in an inner loop over
+// the same row that they never left.)
+constexpr int NSH = 16;        // shards of a bin's counter (a power of two)
+constexpr int SH_STRIDE = 16;  // int64 per shard: one 128-byte line
+constexpr int BIN_CTRS = NSH * SH_STRIDE;
+struct RowFeed {
+  int64_t *ctr;  // the bin's shards, zeroed
+  int step;      // rows per fetch
+  int nsh;       // shards in use (a power of two, at most the grid)
+};
+__device__ __forceinline__ int64_t next_rows(const RowFeed &f) {
   __shared__ int64_t r;
-  if (threadIdx.x == 0) r = (int64_t)atomicAdd((unsigned long long *)ctr, (unsigned long long)step);
+  const int sh = (int)blockIdx.x & (f.nsh - 1);
+  if (threadIdx.x == 0) r = (int64_t)atomicAdd((unsigned long long *)(f.ctr + sh * SH_STRIDE), 1ull);
   __syncthreads();
   const int64_t v = r;
   __syncthreads();
-  return v;
+  return (v * f.nsh + sh) * f.step;
 }
 
-// Rows per fetch for a bin of `rows` rows on `grid` blocks: about 16
-// fetches per block, 1 to 32 rows each.
-inline int fetch_step(int64_t rows, int64_t grid) {
-  return (int)std::max<int64_t>(1, std::min<int64_t>(32, rows / std::max<int64_t>(1, grid * 16)));
+// The feed of a bin of `rows` rows on `grid` blocks: about 16 fetches per
+// block, 1 to 32 rows each.  Below 4,096 rows one counter is not what bounds
+// the bin (50 us in all, spread over the launch) and balances better.
+inline RowFeed row_feed(int64_t *ctr, int64_t rows, int64_t grid) {
+  RowFeed f;
+  f.ctr = ctr;
+  f.step = (int)std::max<int64_t>(1, std::min<int64_t>(32, rows / std::max<int64_t>(1, grid * 16)));
+  f.nsh = rows >= 4096 && grid >= 4 * NSH ? NSH : 1;
+  return f;
+}
+// The same for rows that are long and sorted heaviest first: one at a time.
+inline RowFeed heavy_feed(int64_t *ctr, int64_t rows, int64_t grid) {
+  RowFeed f = row_feed(ctr, rows, grid);
+  f.step = 1;
+  return f;
 }
 
 template <int BS, class T> __device__ __forceinline__ T block_sum(T v, T *tmp) {
@@ -417,15 +583,15 @@ __global__ void __launch_bounds__(BS) sym_hash(const int32_t *__restrict__ list,
                                                int bin, const int64_t *__restrict__ rpA,
                                                const int32_t *__restrict__ cA, const int64_t *__restrict__ rpB,
                                                const int32_t *__restrict__ cB, int64_t *__restrict__ nnz_row,
-                                               int64_t *ctr, int step, int64_t *err) {
+                                               RowFeed feed, int64_t *err) {
   constexpr int LG = __builtin_ctz(TBL);
   __shared__ int32_t keys[TBL];
   __shared__ Chunk<BS, uint8_t> L;
   __shared__ int64_t red[BS / WAVE + 1];
   const int64_t count = info[bin];
   const int32_t *rows = list + info[NBIN + bin];
-  for (int64_t r0 = next_row(ctr, step); r0 < count; r0 = next_row(ctr, step)) {
-   const int64_t r1 = min(r0 + (int64_t)step, count);
+  for (int64_t r0 = next_rows(feed); r0 < count; r0 = next_rows(feed)) {
+   const int64_t r1 = min(r0 + (int64_t)feed.step, count);
    for (int64_t r = r0; r < r1; r++) {
     const int64_t i = rows[r];
     for (int s = threadIdx.x; s < TBL; s += BS) keys[s] = EMPTY;
@@ -462,15 +628,15 @@ __global__ void __launch_bounds__(BS) sym_bitmap(const int32_t *__restrict__ lis
                                                  const int32_t *__restrict__ cA, const int64_t *__restrict__ rpB,
                                                  const int32_t *__restrict__ cB, int64_t ncols, int32_t wwords,
                                                  const int32_t *__restrict__ woff, int nwin,
-                                                 int64_t *__restrict__ nnz_row, int64_t *ctr, int step) {
+                                                 int64_t *__restrict__ nnz_row, RowFeed feed) {
   extern __shared__ uint32_t bits[];
   __shared__ Chunk<BS, uint8_t> L;
   __shared__ int64_t red[BS / WAVE + 1];
   const int64_t count = info[bin];
   const int32_t *rows = list + info[NBIN + bin];
   const int64_t wcols = (int64_t)wwords * 32;
-  for (int64_t r0 = next_row(ctr, step); r0 < count; r0 = next_row(ctr, step)) {
-   const int64_t r1 = min(r0 + (int64_t)step, count);
+  for (int64_t r0 = next_rows(feed); r0 < count; r0 = next_rows(feed)) {
+   const int64_t r1 = min(r0 + (int64_t)feed.step, count);
    for (int64_t r = r0; r < r1; r++) {
     const int64_t i = rows[r];
     int64_t mine = 0;
@@ -512,7 +678,7 @@ __global__ void __launch_bounds__(BS) num_hash(const int32_t *__restrict__ list,
                                                int32_t wwords, OutRows orows,
                                                int32_t *__restrict__ cC, typename SR::val_t *__restrict__ vC,
                                                typename SR::acc_t id, int64_t *__restrict__ row_kept,
-                                               int32_t *any_short, int64_t *ctr, int step) {
+                                               int32_t *any_short, RowFeed feed) {
   using V = typename SR::val_t;
   using A = typename SR::acc_t;
   constexpr int LG = __builtin_ctz(TBL);
@@ -523,8 +689,8 @@ __global__ void __launch_bounds__(BS) num_hash(const int32_t *__restrict__ list,
   __shared__ int64_t red[BS / WAVE + 1];
   const int64_t count = info[bin];
   const int32_t *rows = list + info[NBIN + bin];
-  for (int64_t r0 = next_row(ctr, step); r0 < count; r0 = next_row(ctr, step)) {
-   const int64_t r1 = min(r0 + (int64_t)step, count);
+  for (int64_t r0 = next_rows(feed); r0 < count; r0 = next_rows(feed)) {
+   const int64_t r1 = min(r0 + (int64_t)feed.step, count);
    for (int64_t r = r0; r < r1; r++) {
     const int64_t i = rows[r];
     for (int s = threadIdx.x; s < TBL; s += BS) {
@@ -911,7 +1077,7 @@ __global__ void __launch_bounds__(BS, 4) num_dense(const int32_t *__restrict__ l
                                                 OutRows orows, int32_t *__restrict__ cC,
                                                 typename SR::val_t *__restrict__ vC, typename SR::acc_t id,
                                                 int64_t *__restrict__ row_kept, int32_t *any_short,
-                                                int64_t *ctr, int step, const uint2 *__restrict__ rB) {
+                                                RowFeed feed, const uint2 *__restrict__ rB) {
   using V = typename SR::val_t;
   using A = typename SR::acc_t;
   using R = RankWin<SR, BS, W>;
@@ -940,8 +1106,8 @@ __global__ void __launch_bounds__(BS, 4) num_dense(const int32_t *__restrict__ l
   const bool can_rank = R::OK && woff != nullptr && nwin > 1 && nwin <= NWPW;
   const int64_t count = info[bin];
   const int32_t *rows = list + info[NBIN + bin];
-  for (int64_t r0 = next_row(ctr, step); r0 < count; r0 = next_row(ctr, step)) {
-   const int64_t r1 = min(r0 + (int64_t)step, count);
+  for (int64_t r0 = next_rows(feed); r0 < count; r0 = next_rows(feed)) {
+   const int64_t r1 = min(r0 + (int64_t)feed.step, count);
    for (int64_t r = r0; r < r1; r++) {
     const int64_t i = rows[r];
     const int64_t base = orows.start[i];
@@ -1185,7 +1351,7 @@ __global__ void __launch_bounds__(BS) masked_rows(const int64_t *__restrict__ rp
                                                   const int32_t *__restrict__ ichunk,
                                                   const int32_t *__restrict__ order, int64_t items,
                                                   int32_t *__restrict__ cC, typename SR::val_t *__restrict__ vC,
-                                                  typename SR::acc_t id, int64_t *__restrict__ kept, int64_t *ctr) {
+                                                  typename SR::acc_t id, int64_t *__restrict__ kept, RowFeed feed) {
   using V = typename SR::val_t;
   using A = typename SR::acc_t;
   __shared__ int32_t keys[LM];
@@ -1193,7 +1359,9 @@ __global__ void __launch_bounds__(BS) masked_rows(const int64_t *__restrict__ rp
   __shared__ Chunk<BS, V> L;
   __shared__ int64_t red[BS / WAVE + 1];
   const int t = threadIdx.x;
-  for (int64_t r = next_row(ctr); r < items; r = next_row(ctr)) {
+  for (int64_t r0 = next_rows(feed); r0 < items; r0 = next_rows(feed)) {
+   const int64_t r1 = min(r0 + (int64_t)feed.step, items);
+   for (int64_t r = r0; r < r1; r++) {
     const int32_t x = order[r];
     const int64_t i = irow[x];
     const int64_t s0 = rpM[i] + (int64_t)ichunk[x] * LM;
@@ -1217,6 +1385,7 @@ __global__ void __launch_bounds__(BS) masked_rows(const int64_t *__restrict__ rp
     });
     const int64_t written = write_kept<SR, BS>(vals, keys, n, id, s0, cC, vC, red);
     if (t == 0) kept[x] = written;
+   }
   }
 }
 
@@ -1357,6 +1526,28 @@ inline unsigned gridn(int64_t n, int bs = 256, int64_t cap = 65536) {
   return (unsigned)std::max<int64_t>(1, std::min<int64_t>(g, cap));
 }
 
+// Binning of the nsel values v (row ids in row_map, or 0..nsel-1): info (INFO
+// entries) and the rows listed by bin.
+void bin_rows(Ctx *c, const int64_t *v, int64_t nsel, const Thresholds &th, const int64_t *rpA,
+              const int32_t *row_map, int64_t *info, int32_t *list, hipStream_t s) {
+  if (nsel <= BIN_SMALL) {
+    bin_small<<<1, 1024, 0, s>>>(v, nsel, th, rpA, row_map, info, list);
+    SRTC_LAUNCH_CHECK("bin_small");
+    return;
+  }
+  // whole tiles per block, at most BIN_MAXB blocks
+  const int64_t tiles = (nsel + BIN_BS - 1) / BIN_BS;
+  const int64_t chunk = (tiles + BIN_MAXB - 1) / BIN_MAXB * BIN_BS;
+  const int nblk = (int)((nsel + chunk - 1) / chunk);
+  Buf part(c, sizeof(int64_t) * (size_t)(BIN_Q * BIN_MAXB));
+  bin_count<<<nblk, BIN_BS, 0, s>>>(v, nsel, chunk, th, part.as<int64_t>(), rpA, row_map);
+  SRTC_LAUNCH_CHECK("bin_count");
+  bin_offsets<<<1, 1024, 0, s>>>(part.as<int64_t>(), nblk, info);
+  SRTC_LAUNCH_CHECK("bin_offsets");
+  bin_scatter<<<nblk, BIN_BS, 0, s>>>(v, nsel, chunk, th, part.as<int64_t>(), info, list, row_map);
+  SRTC_LAUNCH_CHECK("bin_scatter");
+}
+
 // Order the rows of one bin heaviest first (by their product counts), so the
 // longest rows of a persistent launch start early instead of forming its tail.
 void heavy_first(Ctx *c, int32_t *seg, int64_t nb, const int64_t *w, hipStream_t s) {
@@ -1424,8 +1615,8 @@ void launch_sym_hash(const Launch &L, int64_t rows, const int32_t *list, const i
   if (rows == 0) return;
   const int lds = TBL * 4 + sizeof(Chunk<BS, uint8_t>) + 64;
   const unsigned grid = L.grid(rows, lds, BS);
-  sym_hash<BS, TBL><<<grid, BS, 0, L.s>>>(list, info, bin, A.rowptr, A.col, B.rowptr, B.col, nnz_row, ctr,
-                                          fetch_step(rows, grid), err);
+  sym_hash<BS, TBL><<<grid, BS, 0, L.s>>>(list, info, bin, A.rowptr, A.col, B.rowptr, B.col, nnz_row,
+                                          row_feed(ctr, rows, grid), err);
   SRTC_LAUNCH_CHECK("sym_hash");
 }
 
@@ -1441,10 +1632,11 @@ int32_t bitmap_words(int64_t ncols, int bs, int64_t budget_bytes) {
 
 // Symbolic pass over `nsel` rows (row ids in row_map, or 0..nsel-1) whose
 // product counts are w (indexed by row id): nnz_row[row] for each.  Returns
-// the product total.  Synchronizes once (bin sizes).
+// the product total.  Synchronizes once (bin sizes).  ctrs: the bins' row
+// counters (NBIN * BIN_CTRS, zeroed by the caller).
 int64_t run_symbolic(const Launch &L, const Schedule &S, const CsrView &Am, const CsrView &Bm, const int64_t *w,
                      const int32_t *row_map, int64_t nsel, int64_t *info1, int32_t *list, int64_t *nnz_row,
-                     int64_t *err) {
+                     int64_t *err, int64_t *ctrs) {
   hipStream_t s = L.s;
   Ctx *c = L.c;
   const int64_t n = Bm.n;
@@ -1469,15 +1661,11 @@ int64_t run_symbolic(const Launch &L, const Schedule &S, const CsrView &Am, cons
       prev = th1.t[b];
     }
   }
-  bin_count<<<gridn(nsel, 256, 2048), 256, 0, s>>>(wsel, nsel, th1, info1, Am.rowptr, row_map);
-  SRTC_LAUNCH_CHECK("bin_count");
-  bin_offsets<<<1, 64, 0, s>>>(info1);
-  bin_scatter<<<gridn(nsel, 256, 4096), 256, 0, s>>>(wsel, nsel, th1, info1, list, row_map);
-  SRTC_LAUNCH_CHECK("bin_scatter");
+  bin_rows(c, wsel, nsel, th1, Am.rowptr, row_map, info1, list, s);
   int64_t hinfo[INFO];
   read_to_host(c, hinfo, info1, sizeof(hinfo), s);
   heavy_first(c, list + hinfo[NBIN + 5], hinfo[5], w, s);
-  int64_t *ctr1 = info1 + 3 * NBIN;
+  auto ctr1 = [&](int b) { return ctrs + b * BIN_CTRS; };
   // algorithmic bytes of a symbolic bin: its A rows (pointers + columns),
   // B's columns once, one count per row
   auto sym_bytes = [&](int b) {
@@ -1489,10 +1677,10 @@ int64_t run_symbolic(const Launch &L, const Schedule &S, const CsrView &Am, cons
   for (int b = 1; b < NBIN - 1; b++) {
     if (hinfo[b] == 0) continue;
     ProfScope ps(c, kSymName[b], sym_bytes(b), s);
-    if (b == 1) launch_sym_hash<64, 64>(L, hinfo[1], list, info1, 1, Am, Bm, nnz_row, ctr1 + 1, err);
-    if (b == 2) launch_sym_hash<64, 512>(L, hinfo[2], list, info1, 2, Am, Bm, nnz_row, ctr1 + 2, err);
-    if (b == 3) launch_sym_hash<256, 4096>(L, hinfo[3], list, info1, 3, Am, Bm, nnz_row, ctr1 + 3, err);
-    if (b == 4) launch_sym_hash<512, 16384>(L, hinfo[4], list, info1, 4, Am, Bm, nnz_row, ctr1 + 4, err);
+    if (b == 1) launch_sym_hash<64, 64>(L, hinfo[1], list, info1, 1, Am, Bm, nnz_row, ctr1(1), err);
+    if (b == 2) launch_sym_hash<64, 512>(L, hinfo[2], list, info1, 2, Am, Bm, nnz_row, ctr1(2), err);
+    if (b == 3) launch_sym_hash<256, 4096>(L, hinfo[3], list, info1, 3, Am, Bm, nnz_row, ctr1(3), err);
+    if (b == 4) launch_sym_hash<512, 16384>(L, hinfo[4], list, info1, 4, Am, Bm, nnz_row, ctr1(4), err);
   }
   if (hinfo[5] > 0) {
     ProfScope ps(c, kSymName[5], sym_bytes(5), s);
@@ -1517,12 +1705,12 @@ int64_t run_symbolic(const Launch &L, const Schedule &S, const CsrView &Am, cons
     auto kern = sym_bitmap<BS>;
     if (ww * 4 > 64 * 1024)
       SRTC_HIP(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, ww * 4));
-    kern<<<L.grid(hinfo[5], stat + ww * 4, BS), BS, (size_t)ww * 4, s>>>(list, info1, 5, Am.rowptr, Am.col,
-                                                                      Bm.rowptr, Bm.col, n, ww, wo,
-                                                                      nwin, nnz_row, ctr1 + 5, 1);
+    const unsigned grid = L.grid(hinfo[5], stat + ww * 4, BS);
+    kern<<<grid, BS, (size_t)ww * 4, s>>>(list, info1, 5, Am.rowptr, Am.col, Bm.rowptr, Bm.col, n, ww, wo, nwin,
+                                          nnz_row, heavy_feed(ctr1(5), hinfo[5], grid));
     SRTC_LAUNCH_CHECK("sym_bitmap");
   }
-  return hinfo[4 * NBIN];
+  return hinfo[SUM];
 }
 
 template <class SR> struct NumLaunch {
@@ -1538,7 +1726,7 @@ template <class SR> struct NumLaunch {
     const unsigned grid = L.grid(rows, stat, BS);
     num_hash<SR, BS, TBL, EX><<<grid, BS, 0, L.s>>>(
         list, info, bin, Am.rowptr, Am.col, (const V *)Am.val, Bm.rowptr, Bm.col, (const V *)Bm.val, Bm.n, 0,
-        orows, cC, vC, id, kept, any_short, ctr, fetch_step(rows, grid));
+        orows, cC, vC, id, kept, any_short, row_feed(ctr, rows, grid));
     SRTC_LAUNCH_CHECK("num_hash");
   }
   template <int BS, int W>
@@ -1548,9 +1736,10 @@ template <class SR> struct NumLaunch {
     if (rows == 0) return;
     constexpr int NV = SR::HAS_VALS ? W : 1;
     const int stat = NV * (int)sizeof(A) + W / 8 + (int)sizeof(Chunk<BS, V>) + (RankWin<SR, BS, W>::OK ? NWPW * 8 : 8) + 64;
-    num_dense<SR, BS, W><<<L.grid(rows, stat, BS), BS, 0, L.s>>>(
+    const unsigned grid = L.grid(rows, stat, BS);
+    num_dense<SR, BS, W><<<grid, BS, 0, L.s>>>(
         list, info, bin, Am.rowptr, Am.col, (const V *)Am.val, Bm.rowptr, Bm.col, (const V *)Bm.val, Bm.n, woff,
-        nwin, orows, cC, vC, id, kept, any_short, ctr, 1, rB);
+        nwin, orows, cC, vC, id, kept, any_short, heavy_feed(ctr, rows, grid), rB);
     SRTC_LAUNCH_CHECK("num_dense");
   }
 };
@@ -1610,8 +1799,7 @@ template <class SR> Schedule budgeted(const Ctx *c, int id) {
 
 // Numeric binning of one group of rows (row ids in g.row_map, or every row
 // when it is null) under schedule g.sched: rows go to bins by their exact
-// output counts (info2: INFO entries, zeroed by the caller; list: the
-// group's rows by bin).  Nothing is read back here.
+// output counts (info2: INFO entries; list: the group's rows by bin).  Nothing is read back here.
 template <class SR>
 void numeric_bin(Ctx *c, const CsrView &Am, const int64_t *nnz_row, const RowGroup &g, int64_t *info2, int32_t *list,
                  Buf *vbuf, hipStream_t s) {
@@ -1631,33 +1819,30 @@ void numeric_bin(Ctx *c, const CsrView &Am, const int64_t *nnz_row, const RowGro
   th2.t[1] = std::max(S.t_small, th2.t[0]);
   th2.t[2] = std::max(S.t_mid, th2.t[1]);
   th2.t[3] = std::max(S.t_big, th2.t[2]);
-  bin_count<<<gridn(nsel, 256, 2048), 256, 0, s>>>(vsel, nsel, th2, info2, Am.rowptr, g.row_map);
-  SRTC_LAUNCH_CHECK("bin_count");
-  bin_offsets<<<1, 64, 0, s>>>(info2);
-  bin_scatter<<<gridn(nsel, 256, 4096), 256, 0, s>>>(vsel, nsel, th2, info2, list, g.row_map);
-  SRTC_LAUNCH_CHECK("bin_scatter");
+  bin_rows(c, vsel, nsel, th2, Am.rowptr, g.row_map, info2, list, s);
 }
 
 // Numeric kernels of one binned group (hinfo2: the host copy of its bin
 // table), writing at rpC.  kp[row] = entries written; fl[0] is raised when a
 // row came out short (identity results dropped) or holds an entry with
 // column -1 (an identity result written in place), fl[1] on a broken hash
-// invariant.
+// invariant.  ctrs: the bins' row counters (NBIN * BIN_CTRS, zeroed by the
+// caller).
 template <class SR>
 void numeric_launch(Ctx *c, typename SR::acc_t id, const CsrView &Am, const CsrView &Bm, const int64_t *w,
                     const RowGroup &g, const int64_t *hinfo2, int64_t *info2, int32_t *lst, int sorted,
                     OutRows rpC, int32_t *cC, typename SR::val_t *vC, int64_t *kp, int32_t *fl,
-                    SpgemmStats *st, hipStream_t s) {
+                    int64_t *ctrs, SpgemmStats *st, hipStream_t s) {
   using V = typename SR::val_t;
   const Schedule S = budgeted<SR>(c, g.sched);
   const int64_t n = Bm.n;
   Launch L{c, s};
   heavy_first(c, lst + hinfo2[NBIN + 5], hinfo2[5], w, s);
   c->tracef("spgemm: schedule %d, nnz %lld; numeric bins %lld %lld %lld %lld %lld", g.sched,
-            (long long)hinfo2[4 * NBIN], (long long)hinfo2[1], (long long)hinfo2[2], (long long)hinfo2[3],
+            (long long)hinfo2[SUM], (long long)hinfo2[1], (long long)hinfo2[2], (long long)hinfo2[3],
             (long long)hinfo2[4], (long long)hinfo2[5]);
   if (st) st->dense_rows += hinfo2[5];
-  int64_t *ctr2 = info2 + 3 * NBIN;
+  auto ctr2 = [&](int b) { return ctrs + b * BIN_CTRS; };
   using NL = NumLaunch<SR>;
   // algorithmic bytes of a numeric bin: its C entries written, its A rows
   // read, B read once
@@ -1677,18 +1862,18 @@ void numeric_launch(Ctx *c, typename SR::acc_t id, const CsrView &Am, const CsrV
     if (hinfo2[b] == 0) continue;
     ProfScope ps(c, pname(b).c_str(), num_bytes(b), s);
     if (b == 1) {
-      if (sorted) NL::template hash<64, 64, 0>(L, hinfo2[1], lst, info2, 1, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2 + 1);
-      else NL::template hash<64, 64, 2>(L, hinfo2[1], lst, info2, 1, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2 + 1);
+      if (sorted) NL::template hash<64, 64, 0>(L, hinfo2[1], lst, info2, 1, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(1));
+      else NL::template hash<64, 64, 2>(L, hinfo2[1], lst, info2, 1, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(1));
     } else if (b == 2) {
-      if (!sorted) NL::template hash<128, 512, 2>(L, hinfo2[2], lst, info2, 2, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2 + 2);
-      else if (S.small_wave) NL::template hash<64, 512, 0>(L, hinfo2[2], lst, info2, 2, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2 + 2);
-      else NL::template hash<128, 512, 0>(L, hinfo2[2], lst, info2, 2, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2 + 2);
+      if (!sorted) NL::template hash<128, 512, 2>(L, hinfo2[2], lst, info2, 2, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(2));
+      else if (S.small_wave) NL::template hash<64, 512, 0>(L, hinfo2[2], lst, info2, 2, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(2));
+      else NL::template hash<128, 512, 0>(L, hinfo2[2], lst, info2, 2, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(2));
     } else if (b == 3) {
-      if (sorted) NL::template hash<256, 4096, 0>(L, hinfo2[3], lst, info2, 3, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2 + 3);
-      else NL::template hash<256, 4096, 2>(L, hinfo2[3], lst, info2, 3, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2 + 3);
+      if (sorted) NL::template hash<256, 4096, 0>(L, hinfo2[3], lst, info2, 3, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(3));
+      else NL::template hash<256, 4096, 2>(L, hinfo2[3], lst, info2, 3, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(3));
     } else {
-      if (sorted) NL::template hash<512, 8192, 0>(L, hinfo2[4], lst, info2, 4, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2 + 4);
-      else NL::template hash<512, 8192, 2>(L, hinfo2[4], lst, info2, 4, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2 + 4);
+      if (sorted) NL::template hash<512, 8192, 0>(L, hinfo2[4], lst, info2, 4, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(4));
+      else NL::template hash<512, 8192, 2>(L, hinfo2[4], lst, info2, 4, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(4));
     }
   }
   if (hinfo2[5] > 0) {
@@ -1717,12 +1902,12 @@ void numeric_launch(Ctx *c, typename SR::acc_t id, const CsrView &Am, const CsrV
     if (S.dense_wide == 1) {
       // the widest window fills the LDS (one block per CU): 1024 threads keep
       // 16 waves per CU in flight instead of 8
-      NL::template dense<1024, W1>(L, hinfo2[5], lst, info2, 5, Am, Bm, wo, nwin, rb, rpC, cC, vC, id, kp, fl, ctr2 + 5);
+      NL::template dense<1024, W1>(L, hinfo2[5], lst, info2, 5, Am, Bm, wo, nwin, rb, rpC, cC, vC, id, kp, fl, ctr2(5));
     } else if (S.dense_wide == 2) {
-      NL::template dense<512, W2>(L, hinfo2[5], lst, info2, 5, Am, Bm, wo, nwin, rb, rpC, cC, vC, id, kp, fl, ctr2 + 5);
+      NL::template dense<512, W2>(L, hinfo2[5], lst, info2, 5, Am, Bm, wo, nwin, rb, rpC, cC, vC, id, kp, fl, ctr2(5));
     } else {
-      if (S.dense_bs == 512) NL::template dense<512, W0>(L, hinfo2[5], lst, info2, 5, Am, Bm, wo, nwin, rb, rpC, cC, vC, id, kp, fl, ctr2 + 5);
-      else NL::template dense<256, W0>(L, hinfo2[5], lst, info2, 5, Am, Bm, wo, nwin, rb, rpC, cC, vC, id, kp, fl, ctr2 + 5);
+      if (S.dense_bs == 512) NL::template dense<512, W0>(L, hinfo2[5], lst, info2, 5, Am, Bm, wo, nwin, rb, rpC, cC, vC, id, kp, fl, ctr2(5));
+      else NL::template dense<256, W0>(L, hinfo2[5], lst, info2, 5, Am, Bm, wo, nwin, rb, rpC, cC, vC, id, kp, fl, ctr2(5));
     }
   }
 }
@@ -1777,9 +1962,12 @@ void spgemm_groups(Ctx *c, IdVal idv, const CsrView &Am, const CsrView &Bm, cons
             G ? groups[0].sched : -1);
   // per group: a bin table (symbolic, then reused for the numeric pass) and
   // a row list; slot 0 of `tables` receives the output size
-  Buf tables(c, sizeof(int64_t) * (size_t)(1 + G * INFO));
+  // the row counters of both passes follow the tables
+  Buf tables(c, sizeof(int64_t) * (size_t)(1 + G * (INFO + 2 * NBIN * BIN_CTRS)));
   int64_t *tab = tables.as<int64_t>();
-  fill_i64(tab, 1 + (int64_t)G * INFO, 0, s);
+  int64_t *ctrs = tab + 1 + (int64_t)G * INFO;
+  fill_i64(tab, 1 + (int64_t)G * (INFO + 2 * NBIN * BIN_CTRS), 0, s);
+  auto pass_ctrs = [&](int q, int pass) { return ctrs + (int64_t)(2 * q + pass) * NBIN * BIN_CTRS; };
   std::vector<Buf> lists(G);
   int64_t products = 0;
   for (int q = 0; q < G; q++) {
@@ -1789,8 +1977,7 @@ void spgemm_groups(Ctx *c, IdVal idv, const CsrView &Am, const CsrView &Bm, cons
     if (nsel == 0) continue;
     int64_t *info1 = tab + 1 + (int64_t)q * INFO;
     products += run_symbolic(L, budgeted<SR>(c, g.sched), Am, Bm, w.as<int64_t>(), g.row_map, nsel, info1,
-                             lists[q].as<int32_t>(), nnz_row.as<int64_t>(), sym_err);
-    fill_i64(info1, INFO, 0, s);  // the table serves the numeric binning next
+                             lists[q].as<int32_t>(), nnz_row.as<int64_t>(), sym_err, pass_ctrs(q, 0));
   }
   c->tracef("spgemm: symbolic launched, %lld products", (long long)products);
   if (st) st->products = products;
@@ -1819,7 +2006,7 @@ void spgemm_groups(Ctx *c, IdVal idv, const CsrView &Am, const CsrView &Bm, cons
     for (int q = 0; q < G; q++)
       numeric_launch<SR>(c, id, Am, Bm, w.as<int64_t>(), groups[q], htab.data() + 1 + (size_t)q * INFO,
                          tab + 1 + (int64_t)q * INFO, lists[q].as<int32_t>(), sorted,
-                         OutRows{rpC, nnz_row.as<int64_t>(), 0}, cC, vC, kp, fl, st, s);
+                         OutRows{rpC, nnz_row.as<int64_t>(), 0}, cC, vC, kp, fl, pass_ctrs(q, 1), st, s);
   // 6. compaction when identity results were dropped
   int32_t flags_h[4] = {0, 0, 0, 0};
   read_to_host(c, flags_h, fl, sizeof(flags_h), s);
@@ -2041,9 +2228,12 @@ void spgemm_blocked(Ctx *c, IdVal idv, const CsrView &Am, const CsrView &Bm, int
   fill_i32(flag.as<int32_t>(), 4, 0, s);
   int32_t *fl = flag.as<int32_t>();
   int64_t *sym_err = reinterpret_cast<int64_t *>(flag.as<char>() + 8);
-  Buf tables(c, sizeof(int64_t) * (size_t)(1 + G * INFO));
+  // the row counters of both passes follow the tables
+  Buf tables(c, sizeof(int64_t) * (size_t)(1 + G * (INFO + 2 * NBIN * BIN_CTRS)));
   int64_t *tab = tables.as<int64_t>();
-  fill_i64(tab, 1 + (int64_t)G * INFO, 0, s);
+  int64_t *ctrs = tab + 1 + (int64_t)G * INFO;
+  fill_i64(tab, 1 + (int64_t)G * (INFO + 2 * NBIN * BIN_CTRS), 0, s);
+  auto pass_ctrs = [&](int q, int pass) { return ctrs + (int64_t)(2 * q + pass) * NBIN * BIN_CTRS; };
   std::vector<Buf> blists(G);
   int64_t products = 0;
   for (int q = 0; q < G; q++) {
@@ -2053,7 +2243,7 @@ void spgemm_blocked(Ctx *c, IdVal idv, const CsrView &Am, const CsrView &Bm, int
     int64_t *info1 = tab + 1 + (int64_t)q * INFO;
     if (q == 0) {
       products += run_symbolic(L, budgeted<SR>(c, sched), Am, Bm, w, light, nlight, info1, blists[q].as<int32_t>(),
-                               nnz_row.as<int64_t>(), sym_err);
+                               nnz_row.as<int64_t>(), sym_err, pass_ctrs(q, 0));
     } else {
       const CsrView bq = block_view(q - 1);
       int64_t *wq_b = wq.as<int64_t>() + (int64_t)(q - 1) * m;
@@ -2061,9 +2251,9 @@ void spgemm_blocked(Ctx *c, IdVal idv, const CsrView &Am, const CsrView &Bm, int
                                                                          wq_b);
       SRTC_LAUNCH_CHECK("row_products_rows");
       products += run_symbolic(L, budgeted<SR>(c, sched), Am, bq, wq_b, heavy, nheavy, info1,
-                               blists[q].as<int32_t>(), nnzq.as<int64_t>() + (int64_t)(q - 1) * m, sym_err);
+                               blists[q].as<int32_t>(), nnzq.as<int64_t>() + (int64_t)(q - 1) * m, sym_err,
+                               pass_ctrs(q, 0));
     }
-    fill_i64(info1, INFO, 0, s);
   }
   if (st) st->products = products;
   // rowptr: heavy rows' totals over blocks, then the scan; block starts
@@ -2103,13 +2293,14 @@ void spgemm_blocked(Ctx *c, IdVal idv, const CsrView &Am, const CsrView &Bm, int
       if (grp[q].nsel == 0) continue;
       if (q == 0) {
         numeric_launch<SR>(c, id, Am, Bm, w, grp[0], htab.data() + 1, tab + 1, blists[0].as<int32_t>(), sorted,
-                           OutRows{rpC, nnz_row.as<int64_t>(), 0}, cC, vC, kept.as<int64_t>(), fl, st, s);
+                           OutRows{rpC, nnz_row.as<int64_t>(), 0}, cC, vC, kept.as<int64_t>(), fl, pass_ctrs(q, 1), st,
+                           s);
       } else {
         const int64_t off = (int64_t)(q - 1) * m;
         numeric_launch<SR>(c, id, Am, block_view(q - 1), wq.as<int64_t>() + off, grp[q],
                            htab.data() + 1 + (size_t)q * INFO, tab + 1 + (int64_t)q * INFO, blists[q].as<int32_t>(),
                            sorted, OutRows{startq.as<int64_t>() + off, nnzq.as<int64_t>() + off, (q - 1) * bc}, cC, vC,
-                           keptq.as<int64_t>() + off, fl, st, s);
+                           keptq.as<int64_t>() + off, fl, pass_ctrs(q, 1), st, s);
       }
     }
   }
@@ -2246,7 +2437,7 @@ const Schedule &schedule(int id) {
 
 void row_products(const CsrView &A, const CsrView &B, int64_t *w, hipStream_t s) {
   if (A.m == 0) return;
-  row_products_kernel<<<gridn(A.m * WAVE, 256, 16384), 256, 0, s>>>(A.rowptr, A.col, B.rowptr, A.m, w);
+  row_products_kernel<<<gridn(A.m * RP_G, RP_BS, 16384), RP_BS, 0, s>>>(A.rowptr, A.col, B.rowptr, A.m, w);
   SRTC_LAUNCH_CHECK("row_products");
 }
 
@@ -2287,7 +2478,7 @@ void masked_typed(Ctx *c, IdVal idv, const CsrView &Am, const CsrView &Bm, const
   if (items >= 0x7fffffff) fail(SRTC_ERR_UNSUPPORTED, "masked spgemm: more than 2^31-2 work items");
   Buf irow(c, 4 * (size_t)items), ichunk(c, 4 * (size_t)items), order(c, 4 * (size_t)items);
   Buf witem(c, 8 * (size_t)items), src(c, 8 * (size_t)items), kept(c, 8 * (size_t)items);
-  Buf koff(c, 8 * (size_t)(items + 1)), ctr(c, 64);
+  Buf koff(c, 8 * (size_t)(items + 1)), ctr(c, sizeof(int64_t) * BIN_CTRS);
   {
     Buf w(c, sizeof(int64_t) * (size_t)m);
     row_products(Am, Bm, w.as<int64_t>(), s);
@@ -2297,16 +2488,17 @@ void masked_typed(Ctx *c, IdVal idv, const CsrView &Am, const CsrView &Bm, const
     SRTC_LAUNCH_CHECK("masked_fill_items");
     heavy_first(c, order.as<int32_t>(), items, witem.as<int64_t>(), s);
   }
-  fill_i64(ctr.as<int64_t>(), 1, 0, s);
+  fill_i64(ctr.as<int64_t>(), BIN_CTRS, 0, s);
   Buf colM(c, sizeof(int32_t) * (size_t)Mm.nnz), valM(c, es * (size_t)Mm.nnz);
   {
     ProfScope ps(c, "spgemm.masked", 16.0 * (m + 1) + 12.0 * Am.nnz + (4.0 + es) * Bm.nnz + 4.0 * Mm.nnz +
                  (4.0 + es) * Mm.nnz, s);
     const int stat = LM * (4 + (int)sizeof(A)) + (int)sizeof(Chunk<BS, V>) + 64;
-    masked_rows<SR, BS, LM><<<L.grid(items, stat, BS), BS, 0, s>>>(
+    const unsigned grid = L.grid(items, stat, BS);
+    masked_rows<SR, BS, LM><<<grid, BS, 0, s>>>(
         Am.rowptr, Am.col, (const V *)Am.val, Bm.rowptr, Bm.col, (const V *)Bm.val, Mm.rowptr, Mm.col,
         irow.as<int32_t>(), ichunk.as<int32_t>(), order.as<int32_t>(), items, colM.as<int32_t>(), valM.as<V>(), id,
-        kept.as<int64_t>(), ctr.as<int64_t>());
+        kept.as<int64_t>(), heavy_feed(ctr.as<int64_t>(), items, grid));
     SRTC_LAUNCH_CHECK("masked_rows");
   }
   excl_scan_i64(c, kept.as<int64_t>(), koff.as<int64_t>(), items, s);
@@ -2393,13 +2585,15 @@ void spgemm_features(Ctx *c, int sr, int dt, const CsrView &A, const CsrView &B,
     memcpy(pin, hrows.data(), sizeof(int32_t) * (size_t)ns);
     SRTC_HIP(hipMemcpyAsync(rows.p, pin, sizeof(int32_t) * (size_t)ns, hipMemcpyHostToDevice, s));
     gather_i64<<<gridn(ns), 256, 0, s>>>(w.as<int64_t>(), rows.as<int32_t>(), ns, wsel.as<int64_t>());
-    Buf info(c, sizeof(int64_t) * INFO);
-    fill_i64(info.as<int64_t>(), INFO, 0, s);
+    // bin table, row counters, and the hash kernels' error count (not read)
+    Buf info(c, sizeof(int64_t) * (INFO + NBIN * BIN_CTRS + 1));
+    fill_i64(info.as<int64_t>(), INFO + NBIN * BIN_CTRS + 1, 0, s);
     Buf list(c, sizeof(int32_t) * (size_t)ns);
     Buf nnz_row(c, sizeof(int64_t) * (size_t)m);
     fill_i64(nnz_row.as<int64_t>(), m, 0, s);
     run_symbolic(L, schedule(0), A, B, w.as<int64_t>(), rows.as<int32_t>(), ns, info.as<int64_t>(),
-                 list.as<int32_t>(), nnz_row.as<int64_t>(), info.as<int64_t>() + INFO - 1);
+                 list.as<int32_t>(), nnz_row.as<int64_t>(), info.as<int64_t>() + INFO + NBIN * BIN_CTRS,
+                 info.as<int64_t>() + INFO);
     gather_i64<<<gridn(ns), 256, 0, s>>>(nnz_row.as<int64_t>(), rows.as<int32_t>(), ns, nsel.as<int64_t>());
     std::vector<int64_t> hw(ns), hn(ns);
     read_to_host(c, hw.data(), wsel.p, sizeof(int64_t) * (size_t)ns, s);
