@@ -102,7 +102,8 @@ __global__ void __launch_bounds__(RP_BS) row_products_kernel(const int64_t *__re
   }
 }
 
-constexpr int NBIN = 6;  // bin 0 = empty rows (skipped)
+constexpr int NBIN = 8;  // bin 0 = empty rows (skipped)
+constexpr int HEAVY = NBIN - 1;  // the bin of bitmap (symbolic) and dense-window (numeric) rows
 struct Thresholds {
   int64_t t[NBIN - 1];  // bin b (1..) takes v with t[b-2] < v <= t[b-1]; last bin above
 };
@@ -232,8 +233,8 @@ __device__ __forceinline__ void bin_info(const int64_t *tot, int64_t *info) {
 // blocks, the sums are added up.
 __global__ void __launch_bounds__(1024) bin_offsets(int64_t *__restrict__ part, int nblk, int64_t *__restrict__ info) {
   __shared__ int64_t tot[BIN_Q];
-  const int q = threadIdx.x / WAVE, l = lane_id();
-  if (q < BIN_Q) {
+  const int l = lane_id();
+  for (int q = threadIdx.x / WAVE; q < BIN_Q; q += 1024 / WAVE) {
     int64_t run = 0;
     for (int b0 = 0; b0 < nblk; b0 += WAVE) {
       const int b = b0 + l;
@@ -247,7 +248,6 @@ __global__ void __launch_bounds__(1024) bin_offsets(int64_t *__restrict__ part, 
   __syncthreads();
   if (threadIdx.x == 0) bin_info(tot, info);
 }
-static_assert(BIN_Q <= 16, "one wave of bin_offsets per quantity");
 
 __global__ void __launch_bounds__(BIN_BS) bin_scatter(const int64_t *__restrict__ v, int64_t m, int64_t chunk,
                                                       Thresholds th, const int64_t *__restrict__ part,
@@ -521,9 +521,10 @@ __device__ __forceinline__ void for_products(const int64_t *__restrict__ rpA, co
 
 // Rows of a bin are handed out dynamically, `step` consecutive rows per
 // fetch: thread 0 claims them and the block reads their number back through
-// LDS.  The counter is cut into `nsh` shards, each in a cache line of its
-// own: chunk q of shard s covers rows (q nsh + s) step onwards, and a block
-// draws from shard blockIdx mod nsh only.  Device-scope atomics of all XCDs
+// LDS (a grid that covers every row needs no fetch: block b takes chunk b).
+// The counter is cut into `nsh` shards, each in a cache line of its own:
+// claim q of shard s is chunk q nsh + s, and a block draws from shard
+// blockIdx mod nsh only.  Device-scope atomics of all XCDs
 // on one address take turns at the memory side, about 12 ns each, so one
 // counter per bin put a floor of 12 ns per row under every bin (ER n =
 // 50,021, d = 16: sym_hash and num_hash at 314 to 414 us for 25,000 rows
@@ -544,8 +545,9 @@ struct RowFeed {
   int step;      // rows per fetch
   int nsh;       // shards in use (a power of two, at most the grid)
 };
-__device__ __forceinline__ int64_t next_rows(const RowFeed &f) {
+__device__ __forceinline__ int64_t next_rows(const RowFeed &f, int64_t count, bool first = false) {
   __shared__ int64_t r;
+  if ((int64_t)gridDim.x * f.step >= count) return first ? (int64_t)blockIdx.x * f.step : count;
   const int sh = (int)blockIdx.x & (f.nsh - 1);
   if (threadIdx.x == 0) r = (int64_t)atomicAdd((unsigned long long *)(f.ctr + sh * SH_STRIDE), 1ull);
   __syncthreads();
@@ -554,20 +556,22 @@ __device__ __forceinline__ int64_t next_rows(const RowFeed &f) {
   return (v * f.nsh + sh) * f.step;
 }
 
-// The feed of a bin of `rows` rows on `grid` blocks: about 16 fetches per
-// block, 1 to 32 rows each.  Below 4,096 rows one counter is not what bounds
-// the bin (50 us in all, spread over the launch) and balances better.
+// The feed of a hash bin of `rows` rows on `grid` blocks: about 16 fetches
+// per block, 1 to 32 rows each.
 inline RowFeed row_feed(int64_t *ctr, int64_t rows, int64_t grid) {
   RowFeed f;
   f.ctr = ctr;
   f.step = (int)std::max<int64_t>(1, std::min<int64_t>(32, rows / std::max<int64_t>(1, grid * 16)));
-  f.nsh = rows >= 4096 && grid >= 4 * NSH ? NSH : 1;
+  f.nsh = grid >= 4 * NSH ? NSH : 1;
   return f;
 }
-// The same for rows that are long and sorted heaviest first: one at a time.
+// The same for rows that are long and sorted heaviest first: one at a time,
+// from one counter below 4,096 of them (at most 50 us of fetches, spread
+// over a launch of long rows, and the better balance).
 inline RowFeed heavy_feed(int64_t *ctr, int64_t rows, int64_t grid) {
   RowFeed f = row_feed(ctr, rows, grid);
   f.step = 1;
+  if (rows < 4096) f.nsh = 1;
   return f;
 }
 
@@ -590,7 +594,7 @@ __global__ void __launch_bounds__(BS) sym_hash(const int32_t *__restrict__ list,
   __shared__ int64_t red[BS / WAVE + 1];
   const int64_t count = info[bin];
   const int32_t *rows = list + info[NBIN + bin];
-  for (int64_t r0 = next_rows(feed); r0 < count; r0 = next_rows(feed)) {
+  for (int64_t r0 = next_rows(feed, count, true); r0 < count; r0 = next_rows(feed, count)) {
    const int64_t r1 = min(r0 + (int64_t)feed.step, count);
    for (int64_t r = r0; r < r1; r++) {
     const int64_t i = rows[r];
@@ -635,7 +639,7 @@ __global__ void __launch_bounds__(BS) sym_bitmap(const int32_t *__restrict__ lis
   const int64_t count = info[bin];
   const int32_t *rows = list + info[NBIN + bin];
   const int64_t wcols = (int64_t)wwords * 32;
-  for (int64_t r0 = next_rows(feed); r0 < count; r0 = next_rows(feed)) {
+  for (int64_t r0 = next_rows(feed, count, true); r0 < count; r0 = next_rows(feed, count)) {
    const int64_t r1 = min(r0 + (int64_t)feed.step, count);
    for (int64_t r = r0; r < r1; r++) {
     const int64_t i = rows[r];
@@ -667,7 +671,11 @@ __global__ void __launch_bounds__(BS) sym_bitmap(const int32_t *__restrict__ lis
 // column -1 (ranked groups of the dense windows), so that a compaction
 // follows.
 
-// EXTRACT: 0 = sorted (kept entries compacted, then bitonic-sorted by column), 2 = table order
+// most entries of one rank bucket (num_hash): each entry reads its bucket
+constexpr int BK_MAX = 64;
+
+// EXTRACT: 0 = sorted by column, 2 = table order.  bshift: a column's rank
+// bucket is column >> bshift (TBL / 2 buckets cover B's columns).
 template <class SR, int BS, int TBL, int EXTRACT>
 __global__ void __launch_bounds__(BS) num_hash(const int32_t *__restrict__ list, const int64_t *__restrict__ info,
                                                int bin, const int64_t *__restrict__ rpA,
@@ -675,7 +683,7 @@ __global__ void __launch_bounds__(BS) num_hash(const int32_t *__restrict__ list,
                                                const typename SR::val_t *__restrict__ vA,
                                                const int64_t *__restrict__ rpB, const int32_t *__restrict__ cB,
                                                const typename SR::val_t *__restrict__ vB, int64_t ncols,
-                                               int32_t wwords, OutRows orows,
+                                               int32_t bshift, OutRows orows,
                                                int32_t *__restrict__ cC, typename SR::val_t *__restrict__ vC,
                                                typename SR::acc_t id, int64_t *__restrict__ row_kept,
                                                int32_t *any_short, RowFeed feed) {
@@ -689,7 +697,7 @@ __global__ void __launch_bounds__(BS) num_hash(const int32_t *__restrict__ list,
   __shared__ int64_t red[BS / WAVE + 1];
   const int64_t count = info[bin];
   const int32_t *rows = list + info[NBIN + bin];
-  for (int64_t r0 = next_rows(feed); r0 < count; r0 = next_rows(feed)) {
+  for (int64_t r0 = next_rows(feed, count, true); r0 < count; r0 = next_rows(feed, count)) {
    const int64_t r1 = min(r0 + (int64_t)feed.step, count);
    for (int64_t r = r0; r < r1; r++) {
     const int64_t i = rows[r];
@@ -735,63 +743,81 @@ __global__ void __launch_bounds__(BS) num_hash(const int32_t *__restrict__ list,
         written += tot;
       }
     } else {
-      // sorted output: gather the kept entries (results equal to the
-      // identity are dropped) to the front of the table, bitonic-sort the
-      // next power of two of them by column, write them out in order
+      // sorted output: the kept entries (results equal to the identity are
+      // dropped) go to their rank by column, or, in a crowded row, are
+      // gathered to the front of the table, bitonic-sorted (the next power
+      // of two of them) and written out in order
       constexpr int PER = TBL / BS;
       int32_t kk[PER];
       A vv[PER];
-      int32_t mine = 0;
+      int32_t cnt;
 #pragma unroll
       for (int q = 0; q < PER; q++) {
         const int s = q * BS + threadIdx.x;
         kk[q] = keys[s];
         vv[q] = SR::HAS_VALS ? vals[s] : (A)1;
         if (kk[q] != EMPTY && SR::acc_absent(vv[q], id)) kk[q] = EMPTY;
-        mine += kk[q] != EMPTY ? 1 : 0;
       }
-      int32_t cnt;
-      int32_t pos = block_excl_scan<BS, int32_t>(mine, L.tmp, &cnt);  // ends with a barrier: table reads done
-      // When B's columns fit a bitmap in the table's own LDS (with a word
-      // prefix array beside it), the kept entries are placed by rank: mark
-      // their columns, scan the popcounts once, and every entry's position
-      // is the number of marked columns before it -- column order without
-      // a sort (the table was read into registers above).
-      const int nbw = (int)((ncols + 31) >> 5);
-      const bool by_rank = SR::HAS_VALS ? (nbw <= TBL && nbw * 4 <= NV * (int)sizeof(A)) : (2 * nbw <= TBL);
-      if (by_rank) {
-        uint32_t *bm = reinterpret_cast<uint32_t *>(keys);
-        uint32_t *pre = SR::HAS_VALS ? reinterpret_cast<uint32_t *>(vals) : bm + nbw;
-        for (int u = threadIdx.x; u < nbw; u += BS) bm[u] = 0u;
+      __syncthreads();  // table reads done
+      // Ranks by bucket: the columns' leading bits give NBK buckets (at
+      // least as many as kept entries), a block scan of their counts places
+      // each bucket, and an entry's rank is its bucket's start plus the
+      // number of smaller columns in it.  With columns spread over B's range
+      // a bucket holds about one entry, and each costs a few LDS accesses
+      // where the bitonic sort takes (log2 n)^2 / 2 compare steps: ER n =
+      // 50,021 d = 16 squared (fp32), rows of 65 to 256 outputs 187 -> 107 us,
+      // of 257 to 512 349 -> 134 us (with a table of 1024 slots, not 4096).  A
+      // row with more than BK_MAX entries in one bucket is sorted instead.
+      constexpr int NBK = TBL / 2, BPT = NBK > BS ? NBK / BS : 1;
+      int32_t *const bcnt = keys, *const bcol = keys + NBK;
+      for (int u = threadIdx.x; u < NBK; u += BS) bcnt[u] = 0;
+      __syncthreads();
+      int32_t in_b[PER];
+#pragma unroll
+      for (int q = 0; q < PER; q++) {
+        // a column outside B (a malformed operand) is dropped
+        if (kk[q] != EMPTY && (uint32_t)kk[q] >= (uint32_t)ncols) kk[q] = EMPTY;
+        if (kk[q] != EMPTY) in_b[q] = atomicAdd(&bcnt[kk[q] >> bshift], 1);
+      }
+      __syncthreads();
+      int32_t bs[BPT], bsum = 0, bmax = 0;
+#pragma unroll
+      for (int u = 0; u < BPT; u++) {
+        const int x = (int)threadIdx.x * BPT + u;
+        bs[u] = x < NBK ? bcnt[x] : 0;
+        bsum += bs[u];
+        bmax = max(bmax, bs[u]);
+      }
+      const bool crowded = __syncthreads_or(bmax > BK_MAX);
+      if (!crowded) {
+        int32_t bpos = block_excl_scan<BS, int32_t>(bsum, L.tmp, &cnt);
+#pragma unroll
+        for (int u = 0; u < BPT; u++) {
+          const int x = (int)threadIdx.x * BPT + u;
+          if (x < NBK) bcnt[x] = bpos;
+          bpos += bs[u];
+        }
         __syncthreads();
 #pragma unroll
-        for (int q = 0; q < PER; q++) {
-          // a column outside B (a malformed operand) is dropped, never marked
-          if (kk[q] != EMPTY && (uint32_t)kk[q] >= (uint32_t)ncols) kk[q] = EMPTY;
-          if (kk[q] != EMPTY) atomicOr(&bm[kk[q] >> 5], 1u << (kk[q] & 31));
-        }
-        __syncthreads();
-        const int per = (nbw + BS - 1) / BS;
-        const int u0 = min((int)threadIdx.x * per, nbw), u1 = min(u0 + per, nbw);
-        int32_t c = 0;
-        for (int u = u0; u < u1; u++) c += __popc(bm[u]);
-        int32_t tot;
-        int32_t rk = block_excl_scan<BS, int32_t>(c, L.tmp, &tot);
-        for (int u = u0; u < u1; u++) {
-          pre[u] = (uint32_t)rk;
-          rk += __popc(bm[u]);
-        }
+        for (int q = 0; q < PER; q++)
+          if (kk[q] != EMPTY) bcol[bcnt[kk[q] >> bshift] + in_b[q]] = kk[q];
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < PER; q++) {
           if (kk[q] == EMPTY) continue;
-          const int32_t j = kk[q];
-          const int64_t o = base + (int64_t)pre[j >> 5] + __popc(bm[j >> 5] & ((1u << (j & 31)) - 1u));
-          cC[o] = j + coff;
-          vC[o] = SR::out(vv[q]);
+          const int bk = kk[q] >> bshift;
+          const int s0 = bcnt[bk], s1 = bk + 1 < NBK ? bcnt[bk + 1] : cnt;
+          int rk = s0;
+          for (int x = s0; x < s1; x++) rk += bcol[x] < kk[q] ? 1 : 0;
+          cC[base + rk] = kk[q] + coff;
+          vC[base + rk] = SR::out(vv[q]);
         }
         written = cnt;
       } else {
+      int32_t mine = 0;
+#pragma unroll
+      for (int q = 0; q < PER; q++) mine += kk[q] != EMPTY ? 1 : 0;
+      int32_t pos = block_excl_scan<BS, int32_t>(mine, L.tmp, &cnt);
 #pragma unroll
       for (int q = 0; q < PER; q++) {
         if (kk[q] != EMPTY) {
@@ -1106,7 +1132,7 @@ __global__ void __launch_bounds__(BS, 4) num_dense(const int32_t *__restrict__ l
   const bool can_rank = R::OK && woff != nullptr && nwin > 1 && nwin <= NWPW;
   const int64_t count = info[bin];
   const int32_t *rows = list + info[NBIN + bin];
-  for (int64_t r0 = next_rows(feed); r0 < count; r0 = next_rows(feed)) {
+  for (int64_t r0 = next_rows(feed, count, true); r0 < count; r0 = next_rows(feed, count)) {
    const int64_t r1 = min(r0 + (int64_t)feed.step, count);
    for (int64_t r = r0; r < r1; r++) {
     const int64_t i = rows[r];
@@ -1359,7 +1385,7 @@ __global__ void __launch_bounds__(BS) masked_rows(const int64_t *__restrict__ rp
   __shared__ Chunk<BS, V> L;
   __shared__ int64_t red[BS / WAVE + 1];
   const int t = threadIdx.x;
-  for (int64_t r0 = next_rows(feed); r0 < items; r0 = next_rows(feed)) {
+  for (int64_t r0 = next_rows(feed, items, true); r0 < items; r0 = next_rows(feed, items)) {
    const int64_t r1 = min(r0 + (int64_t)feed.step, items);
    for (int64_t r = r0; r < r1; r++) {
     const int32_t x = order[r];
@@ -1651,12 +1677,13 @@ int64_t run_symbolic(const Launch &L, const Schedule &S, const CsrView &Am, cons
   }
   Thresholds th1{};
   {
-    // bins: 1: <=32 (64-slot hash), 2: <=256 (512), 3: <=2048 (4096),
-    // 4: <=8192 (16384), 5: bitmap.  Edges above sym_hash_max collapse so
-    // those rows fall through to the bitmap.
-    const int64_t edges[4] = {32, 256, 2048, 8192};
+    // bins: 1: <=32 products (64-slot hash), 2: <=256 (512), 3: <=512 (1024),
+    // 4: <=1024 (2048), 5: <=2048 (4096), 6: <=8192 (16384), 7: bitmap.
+    // Edges above sym_hash_max collapse so those rows fall through to the
+    // bitmap.
+    const int64_t edges[NBIN - 2] = {32, 256, 512, 1024, 2048, 8192};
     int64_t prev = 0;
-    for (int b = 0; b < 4; b++) {
+    for (int b = 0; b < NBIN - 2; b++) {
       th1.t[b] = edges[b] <= S.sym_hash_max ? edges[b] : prev;
       prev = th1.t[b];
     }
@@ -1664,7 +1691,7 @@ int64_t run_symbolic(const Launch &L, const Schedule &S, const CsrView &Am, cons
   bin_rows(c, wsel, nsel, th1, Am.rowptr, row_map, info1, list, s);
   int64_t hinfo[INFO];
   read_to_host(c, hinfo, info1, sizeof(hinfo), s);
-  heavy_first(c, list + hinfo[NBIN + 5], hinfo[5], w, s);
+  heavy_first(c, list + hinfo[NBIN + HEAVY], hinfo[HEAVY], w, s);
   auto ctr1 = [&](int b) { return ctrs + b * BIN_CTRS; };
   // algorithmic bytes of a symbolic bin: its A rows (pointers + columns),
   // B's columns once, one count per row
@@ -1672,6 +1699,7 @@ int64_t run_symbolic(const Launch &L, const Schedule &S, const CsrView &Am, cons
     return 16.0 * hinfo[b] + 4.0 * hinfo[SUMA + b] + 4.0 * Bm.nnz + 8.0 * (Bm.m + 1) + 8.0 * hinfo[b];
   };
   static const char *kSymName[NBIN] = {"", "spgemm.symbolic.hash64", "spgemm.symbolic.hash512",
+                                       "spgemm.symbolic.hash1024", "spgemm.symbolic.hash2048",
                                        "spgemm.symbolic.hash4096", "spgemm.symbolic.hash16384",
                                        "spgemm.symbolic.bitmap"};
   for (int b = 1; b < NBIN - 1; b++) {
@@ -1679,11 +1707,13 @@ int64_t run_symbolic(const Launch &L, const Schedule &S, const CsrView &Am, cons
     ProfScope ps(c, kSymName[b], sym_bytes(b), s);
     if (b == 1) launch_sym_hash<64, 64>(L, hinfo[1], list, info1, 1, Am, Bm, nnz_row, ctr1(1), err);
     if (b == 2) launch_sym_hash<64, 512>(L, hinfo[2], list, info1, 2, Am, Bm, nnz_row, ctr1(2), err);
-    if (b == 3) launch_sym_hash<256, 4096>(L, hinfo[3], list, info1, 3, Am, Bm, nnz_row, ctr1(3), err);
-    if (b == 4) launch_sym_hash<512, 16384>(L, hinfo[4], list, info1, 4, Am, Bm, nnz_row, ctr1(4), err);
+    if (b == 3) launch_sym_hash<128, 1024>(L, hinfo[3], list, info1, 3, Am, Bm, nnz_row, ctr1(3), err);
+    if (b == 4) launch_sym_hash<128, 2048>(L, hinfo[4], list, info1, 4, Am, Bm, nnz_row, ctr1(4), err);
+    if (b == 5) launch_sym_hash<256, 4096>(L, hinfo[5], list, info1, 5, Am, Bm, nnz_row, ctr1(5), err);
+    if (b == 6) launch_sym_hash<512, 16384>(L, hinfo[6], list, info1, 6, Am, Bm, nnz_row, ctr1(6), err);
   }
-  if (hinfo[5] > 0) {
-    ProfScope ps(c, kSymName[5], sym_bytes(5), s);
+  if (hinfo[HEAVY] > 0) {
+    ProfScope ps(c, kSymName[HEAVY], sym_bytes(HEAVY), s);
     // 512 threads: the bitmap bounds blocks per CU, so larger blocks keep
     // more gathers in flight (R-MAT 18 squared: 7.8 -> 6.1 ms)
     constexpr int BS = 512;
@@ -1705,12 +1735,19 @@ int64_t run_symbolic(const Launch &L, const Schedule &S, const CsrView &Am, cons
     auto kern = sym_bitmap<BS>;
     if (ww * 4 > 64 * 1024)
       SRTC_HIP(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, ww * 4));
-    const unsigned grid = L.grid(hinfo[5], stat + ww * 4, BS);
-    kern<<<grid, BS, (size_t)ww * 4, s>>>(list, info1, 5, Am.rowptr, Am.col, Bm.rowptr, Bm.col, n, ww, wo, nwin,
-                                          nnz_row, heavy_feed(ctr1(5), hinfo[5], grid));
+    const unsigned grid = L.grid(hinfo[HEAVY], stat + ww * 4, BS);
+    kern<<<grid, BS, (size_t)ww * 4, s>>>(list, info1, HEAVY, Am.rowptr, Am.col, Bm.rowptr, Bm.col, n, ww, wo, nwin,
+                                          nnz_row, heavy_feed(ctr1(HEAVY), hinfo[HEAVY], grid));
     SRTC_LAUNCH_CHECK("sym_bitmap");
   }
   return hinfo[SUM];
+}
+
+// Smallest shift that maps columns 0 .. n-1 to fewer than nbk buckets + 1.
+int32_t bucket_shift(int64_t n, int nbk) {
+  int32_t sh = 0;
+  while (((n - 1) >> sh) >= nbk) sh++;
+  return sh;
 }
 
 template <class SR> struct NumLaunch {
@@ -1725,8 +1762,8 @@ template <class SR> struct NumLaunch {
     const int stat = TBL * 4 + NV * (int)sizeof(A) + (int)sizeof(Chunk<BS, V>) + 64;
     const unsigned grid = L.grid(rows, stat, BS);
     num_hash<SR, BS, TBL, EX><<<grid, BS, 0, L.s>>>(
-        list, info, bin, Am.rowptr, Am.col, (const V *)Am.val, Bm.rowptr, Bm.col, (const V *)Bm.val, Bm.n, 0,
-        orows, cC, vC, id, kept, any_short, row_feed(ctr, rows, grid));
+        list, info, bin, Am.rowptr, Am.col, (const V *)Am.val, Bm.rowptr, Bm.col, (const V *)Bm.val, Bm.n,
+        bucket_shift(Bm.n, TBL / 2), orows, cC, vC, id, kept, any_short, row_feed(ctr, rows, grid));
     SRTC_LAUNCH_CHECK("num_hash");
   }
   template <int BS, int W>
@@ -1778,7 +1815,7 @@ template <class SR> Schedule budgeted(const Ctx *c, int id) {
   if (sym_hash_lds<64>(64) > B) S.sym_hash_max = 0;
   // numeric bins, largest first: a dropped bin's rows fall through to the
   // dense windows (thresholds are applied as running maxima)
-  if (num_hash_lds<SR, 512>(8192) > B) S.t_big = S.t_mid;
+  if (num_hash_lds<SR, 1024>(8192) > B) S.t_big = S.t_mid;
   if (num_hash_lds<SR, 256>(4096) > B) S.t_mid = S.t_big = S.t_small;
   if (num_hash_lds<SR, 128>(512) > B) S.t_small = S.t_mid = S.t_big = S.t_tiny;
   if (num_hash_lds<SR, 64>(64) > B) S.t_tiny = S.t_small = S.t_mid = S.t_big = 0;
@@ -1817,8 +1854,10 @@ void numeric_bin(Ctx *c, const CsrView &Am, const int64_t *nnz_row, const RowGro
   Thresholds th2{};
   th2.t[0] = S.t_tiny;
   th2.t[1] = std::max(S.t_small, th2.t[0]);
-  th2.t[2] = std::max(S.t_mid, th2.t[1]);
-  th2.t[3] = std::max(S.t_big, th2.t[2]);
+  th2.t[2] = std::max(std::min<int64_t>(512, S.t_mid), th2.t[1]);
+  th2.t[3] = std::max(std::min<int64_t>(1024, S.t_mid), th2.t[2]);
+  th2.t[4] = std::max(S.t_mid, th2.t[3]);
+  th2.t[5] = std::max(S.t_big, th2.t[4]);
   bin_rows(c, vsel, nsel, th2, Am.rowptr, g.row_map, info2, list, s);
 }
 
@@ -1837,11 +1876,11 @@ void numeric_launch(Ctx *c, typename SR::acc_t id, const CsrView &Am, const CsrV
   const Schedule S = budgeted<SR>(c, g.sched);
   const int64_t n = Bm.n;
   Launch L{c, s};
-  heavy_first(c, lst + hinfo2[NBIN + 5], hinfo2[5], w, s);
-  c->tracef("spgemm: schedule %d, nnz %lld; numeric bins %lld %lld %lld %lld %lld", g.sched,
+  heavy_first(c, lst + hinfo2[NBIN + HEAVY], hinfo2[HEAVY], w, s);
+  c->tracef("spgemm: schedule %d, nnz %lld; numeric bins %lld %lld %lld %lld %lld %lld %lld", g.sched,
             (long long)hinfo2[SUM], (long long)hinfo2[1], (long long)hinfo2[2], (long long)hinfo2[3],
-            (long long)hinfo2[4], (long long)hinfo2[5]);
-  if (st) st->dense_rows += hinfo2[5];
+            (long long)hinfo2[4], (long long)hinfo2[5], (long long)hinfo2[6], (long long)hinfo2[7]);
+  if (st) st->dense_rows += hinfo2[HEAVY];
   auto ctr2 = [&](int b) { return ctrs + b * BIN_CTRS; };
   using NL = NumLaunch<SR>;
   // algorithmic bytes of a numeric bin: its C entries written, its A rows
@@ -1852,6 +1891,7 @@ void numeric_launch(Ctx *c, typename SR::acc_t id, const CsrView &Am, const CsrV
            (4.0 + vb) * Bm.nnz + 8.0 * (Bm.m + 1);
   };
   static const char *kNumName[NBIN] = {"", "spgemm.numeric.hash64", "spgemm.numeric.hash512",
+                                       "spgemm.numeric.hash1024", "spgemm.numeric.hash2048",
                                        "spgemm.numeric.hash4096", "spgemm.numeric.hash8192",
                                        "spgemm.numeric.dense"};
   // profile names carry the value type, so each names one kernel instance
@@ -1868,15 +1908,27 @@ void numeric_launch(Ctx *c, typename SR::acc_t id, const CsrView &Am, const CsrV
       if (!sorted) NL::template hash<128, 512, 2>(L, hinfo2[2], lst, info2, 2, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(2));
       else if (S.small_wave) NL::template hash<64, 512, 0>(L, hinfo2[2], lst, info2, 2, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(2));
       else NL::template hash<128, 512, 0>(L, hinfo2[2], lst, info2, 2, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(2));
+    // rows of up to 512 and 1024 outputs have tables of their own: these
+    // kernels wait on dependent LDS and memory accesses, and three to four
+    // times as many of their rows fit a CU as of the 4096-slot table's (20
+    // ER instances batched: 3,866 -> 1,762 us; R-MAT 18 fp64: 2,406 -> 728
+    // us in all); the 8192-slot table fills the LDS with one block, so it
+    // takes 1024 threads (R-MAT 18 fp64: 512 threads 2,010, 1,024 1,535 us)
     } else if (b == 3) {
-      if (sorted) NL::template hash<256, 4096, 0>(L, hinfo2[3], lst, info2, 3, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(3));
-      else NL::template hash<256, 4096, 2>(L, hinfo2[3], lst, info2, 3, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(3));
-    } else {
-      if (sorted) NL::template hash<512, 8192, 0>(L, hinfo2[4], lst, info2, 4, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(4));
-      else NL::template hash<512, 8192, 2>(L, hinfo2[4], lst, info2, 4, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(4));
+      if (sorted) NL::template hash<128, 1024, 0>(L, hinfo2[3], lst, info2, 3, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(3));
+      else NL::template hash<128, 1024, 2>(L, hinfo2[3], lst, info2, 3, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(3));
+    } else if (b == 4) {
+      if (sorted) NL::template hash<256, 2048, 0>(L, hinfo2[4], lst, info2, 4, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(4));
+      else NL::template hash<256, 2048, 2>(L, hinfo2[4], lst, info2, 4, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(4));
+    } else if (b == 5) {
+      if (sorted) NL::template hash<256, 4096, 0>(L, hinfo2[5], lst, info2, 5, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(5));
+      else NL::template hash<256, 4096, 2>(L, hinfo2[5], lst, info2, 5, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(5));
+    } else if (b == 6) {
+      if (sorted) NL::template hash<1024, 8192, 0>(L, hinfo2[6], lst, info2, 6, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(6));
+      else NL::template hash<1024, 8192, 2>(L, hinfo2[6], lst, info2, 6, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(6));
     }
   }
-  if (hinfo2[5] > 0) {
+  if (hinfo2[HEAVY] > 0) {
     const int64_t W = dense_width<SR>(S.dense_wide);
     const int nwin = (int)((n + W - 1) / W);
     Buf woff;
@@ -1897,17 +1949,17 @@ void numeric_launch(Ctx *c, typename SR::acc_t id, const CsrView &Am, const CsrV
       });
     // the window-table lookups (8 B per A entry and window) are overhead of
     // the method, not bytes the product must move: they stay out of the count
-    ProfScope ps(c, pname(5).c_str(), num_bytes(5), s);
+    ProfScope ps(c, pname(HEAVY).c_str(), num_bytes(HEAVY), s);
     constexpr int W0 = (int)dense_width<SR>(0), W1 = (int)dense_width<SR>(1), W2 = (int)dense_width<SR>(2);
     if (S.dense_wide == 1) {
       // the widest window fills the LDS (one block per CU): 1024 threads keep
       // 16 waves per CU in flight instead of 8
-      NL::template dense<1024, W1>(L, hinfo2[5], lst, info2, 5, Am, Bm, wo, nwin, rb, rpC, cC, vC, id, kp, fl, ctr2(5));
+      NL::template dense<1024, W1>(L, hinfo2[HEAVY], lst, info2, HEAVY, Am, Bm, wo, nwin, rb, rpC, cC, vC, id, kp, fl, ctr2(HEAVY));
     } else if (S.dense_wide == 2) {
-      NL::template dense<512, W2>(L, hinfo2[5], lst, info2, 5, Am, Bm, wo, nwin, rb, rpC, cC, vC, id, kp, fl, ctr2(5));
+      NL::template dense<512, W2>(L, hinfo2[HEAVY], lst, info2, HEAVY, Am, Bm, wo, nwin, rb, rpC, cC, vC, id, kp, fl, ctr2(HEAVY));
     } else {
-      if (S.dense_bs == 512) NL::template dense<512, W0>(L, hinfo2[5], lst, info2, 5, Am, Bm, wo, nwin, rb, rpC, cC, vC, id, kp, fl, ctr2(5));
-      else NL::template dense<256, W0>(L, hinfo2[5], lst, info2, 5, Am, Bm, wo, nwin, rb, rpC, cC, vC, id, kp, fl, ctr2(5));
+      if (S.dense_bs == 512) NL::template dense<512, W0>(L, hinfo2[HEAVY], lst, info2, HEAVY, Am, Bm, wo, nwin, rb, rpC, cC, vC, id, kp, fl, ctr2(HEAVY));
+      else NL::template dense<256, W0>(L, hinfo2[HEAVY], lst, info2, HEAVY, Am, Bm, wo, nwin, rb, rpC, cC, vC, id, kp, fl, ctr2(HEAVY));
     }
   }
 }
