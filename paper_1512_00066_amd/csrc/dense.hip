@@ -6,13 +6,12 @@
 // (+,x) semiring maps onto MFMA; tropical, boolean and (max,x) products have
 // no matrix-core form.
 //
-// Tile: 64x64 outputs per 256-thread block, each wave a 32x32 quadrant made
-// of 2x2 MFMA 16x16 tiles; K is staged through LDS 16 at a time.
 //   fp64: V_MFMA_F64_16X16X4_F64, fp64 accumulation.
 //   fp32: V_MFMA_F32_16X16X4_F32, with the fp32 accumulators added into fp64
-//         registers every 128 K-steps, so a dot product of any length keeps
+//         registers every 128 k-terms, so a dot product of any length keeps
 //         the relative error of an fp32 sum of at most 128 terms.
 #include <algorithm>
+#include <type_traits>
 
 #include "internal.hpp"
 
@@ -23,225 +22,330 @@ namespace {
 typedef double v4d __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-constexpr int TM = 64, TN = 64, TK = 16;
-
+// One tile of C per block: WM x WN waves, each forming NTM x NTN MFMA 16x16
+// tiles, k taken 128 bytes of A's row (16 fp64 or 32 fp32 terms) at a time
+// through two LDS buffers, one barrier per k-tile.  Bound by the matrix
+// cores: fp64 8192^3 47 -> 73 TFLOP/s of 78.6, fp32 4096^3 67 -> 125 of 157
+// (single-entry loads and LDS accesses, one tile of 128 x 128 per block and
+// accumulators spilled before).  The 16-byte global loads run two k-tiles
+// ahead in registers: with one tile of distance the matrix cores waited for
+// them (67 and 117 TFLOP/s; a lone block per CU 48 and 86).
+// Which k a lane group multiplies in a step, and which column a lane of a
+// 16x16 tile stands for, are free as long as both operands (and the stores)
+// agree: lane group g takes k = g VEC .. g VEC + VEC - 1 of a 4 VEC deep step,
+// so a fragment of A is one 16-byte LDS read, and a lane's tiles are adjacent
+// columns, so fragments of B and C's stores are 16 bytes too.  A's LDS rows
+// are 144 bytes apart (8 lanes of a read touch 64 different banks).
+// Global loads need only their element's alignment, whatever the row length.
+// The main loop has no branch (the compiler copied every accumulator at each
+// join): rows past M and vectors past N are clamped into the matrix (their
+// results are not stored; a vector that crosses N, possible when N is no
+// multiple of VEC, is shifted into place), loads past the last whole k-tile
+// repeat it, and the k remainder follows the loop, entry by entry.
 // Batch z of a strided batch (grid z, grid-stride over batches) multiplies
-// A + z M K by B + z K N into C + z M N.
-template <class T>
-__global__ void __launch_bounds__(256) gemm_mfma(const T *__restrict__ A0, const T *__restrict__ B0, T *__restrict__ C0,
-                                                 int64_t M, int64_t N, int64_t K, int accumulate, int64_t batch) {
-  __shared__ T As[TM][TK + 1];
-  __shared__ T Bs[TK][TN + 1];
+// A + z M K by B + z K N into C + z M N.  With W given, block row y handles
+// the k range [y kchunk, (y + 1) kchunk) and stores its fp64 partial sums to
+// W + (z gridDim.y + y) M N; gemm_combine adds them in order.
+template <class T> struct GemmVec {
+  static constexpr int N = 16 / (int)sizeof(T);
+  typedef T lds __attribute__((ext_vector_type(16 / sizeof(T))));
+  typedef T glb __attribute__((ext_vector_type(16 / sizeof(T)), aligned(sizeof(T))));
+};
+template <class T, int NTM, int NTN, int WM, int WN> struct GemmTile {
+  static constexpr int VEC = GemmVec<T>::N;
+  static constexpr int BK = 128 / (int)sizeof(T);
+  static constexpr int TM = NTM * 16 * WM, TN = NTN * 16 * WN;
+  static constexpr int THREADS = WAVE * WM * WN;
+  static constexpr int SA = BK + VEC, SB = TN + VEC;
+};
+
+// Off: 32-bit byte offsets into a row tile where they suffice (one register
+// per address, the row and k advance in scalar registers), else 64-bit.
+// SHIFT: N is no multiple of VEC.  N is at least VEC.
+template <class T, int NTM, int NTN, int WM, int WN, class Off, bool SHIFT>
+__global__ void __launch_bounds__(WAVE *WM *WN, 2) gemm_mfma(const T *__restrict__ A0, const T *__restrict__ B0,
+                                                    T *__restrict__ C0, double *__restrict__ W, int64_t M, int64_t N,
+                                                    int64_t K, int64_t kchunk, int accumulate, int64_t batch) {
+  using G = GemmTile<T, NTM, NTN, WM, WN>;
+  constexpr int THREADS = G::THREADS;
+  constexpr int VEC = G::VEC, BK = G::BK, TM = G::TM, TN = G::TN, SA = G::SA, SB = G::SB;
+  constexpr int CV = NTN < VEC ? NTN : VEC;        // adjacent columns of a lane
+  constexpr int RA = THREADS / 8, LA = TM / RA;    // A rows per round of loads, rounds
+  constexpr int VB = TN / VEC, RB = THREADS / VB, LB = BK / RB;  // the same for B (VB vectors per row)
+  static_assert(TM % RA == 0 && THREADS % VB == 0 && BK % RB == 0, "whole rounds of loads");
+  using VL = typename GemmVec<T>::lds;
+  using VG = typename GemmVec<T>::glb;
+  typedef T VC __attribute__((ext_vector_type(CV)));
+  typedef T VCG __attribute__((ext_vector_type(CV), aligned(sizeof(T))));
+  using Acc = std::conditional_t<sizeof(T) == 8, v4d, v4f>;
+  __shared__ __align__(16) T As[2][TM * SA];
+  __shared__ __align__(16) T Bs[2][BK * SB];
+  const int t = threadIdx.x, w = t / WAVE, l = lane_id();
+  const int wm = (w / WN) * NTM * 16, wn = (w % WN) * NTN * 16;
+  const int lr = l % 16, lg = l / 16;
+  const int64_t tm = (M + TM - 1) / TM;
+  const int64_t m0 = blockIdx.x % tm * TM, n0 = blockIdx.x / tm * TN;
+  const int64_t kb = (int64_t)blockIdx.y * kchunk, ke = min(K, kb + kchunk);
   for (int64_t z = blockIdx.z; z < batch; z += gridDim.z) {
     const T *__restrict__ A = A0 + z * M * K;
     const T *__restrict__ B = B0 + z * K * N;
-    T *__restrict__ C = C0 + z * M * N;
-    const int t = threadIdx.x;
-    const int w = t / WAVE, l = lane_id();
-    const int64_t m0 = (int64_t)blockIdx.y * TM, n0 = (int64_t)blockIdx.x * TN;
-    const int wm = (w / 2) * 32, wn = (w % 2) * 32;  // wave quadrant
-    double acc64[2][2][4];
+    // a thread's bytes from the tile's first row of A, and from B's row k0
+    const T *__restrict__ Am = A + m0 * K;
+    Off oa[LA];
 #pragma unroll
-    for (int a = 0; a < 2; a++)
+    for (int i = 0; i < LA; i++)
+      oa[i] = (Off)(((Off)min((int64_t)(t / 8 + RA * i), M - 1 - m0) * (Off)K + (t % 8) * VEC) * sizeof(T));
+    const int64_t bn = n0 + (t % VB) * VEC, bc = min(bn, N - VEC);
+    const int sh = (int)min(bn - bc, (int64_t)VEC);  // VEC: past the matrix, never stored
+    const Off ob = (Off)(((Off)(t / VB) * (Off)N + (Off)bc) * sizeof(T));
+    auto at_a = [&](int i, int64_t k0) { return (const T *)((const char *)(Am + k0) + oa[i]); };
+    auto at_b = [&](int64_t k) { return (const T *)((const char *)(B + k * N) + ob); };
+    struct Regs {
+      VL a[LA], b[LB];
+    };
+    const int64_t nt = (ke - kb) / BK;  // whole k-tiles
+    auto fetch = [&](Regs &r, int64_t tile) {
+      const int64_t k0 = kb + min(tile, nt - 1) * BK;
 #pragma unroll
-      for (int b = 0; b < 2; b++)
+      for (int i = 0; i < LA; i++) r.a[i] = *(const VG *)at_a(i, k0);
 #pragma unroll
-        for (int q = 0; q < 4; q++) acc64[a][b][q] = 0.0;
-    v4f acc32[2][2];
+      for (int i = 0; i < LB; i++) r.b[i] = *(const VG *)at_b(k0 + i * RB);
+    };
+    // the terms from k0 on, fewer than a tile; zero beyond
+    auto fetch_rest = [&](Regs &r, int64_t k0) {
 #pragma unroll
-    for (int a = 0; a < 2; a++)
+      for (int i = 0; i < LA; i++)
 #pragma unroll
-      for (int b = 0; b < 2; b++) acc32[a][b] = v4f{0.f, 0.f, 0.f, 0.f};
-    v4d accd[2][2];
+        for (int e = 0; e < VEC; e++) r.a[i][e] = k0 + (t % 8) * VEC + e < ke ? at_a(i, k0)[e] : (T)0;
 #pragma unroll
-    for (int a = 0; a < 2; a++)
+      for (int i = 0; i < LB; i++)
 #pragma unroll
-      for (int b = 0; b < 2; b++) accd[a][b] = v4d{0.0, 0.0, 0.0, 0.0};
-    int since_flush = 0;
-    for (int64_t k0 = 0; k0 < K; k0 += TK) {
-      // stage A (64x16) and B (16x64): 1024 elements each, 4 per thread
+        for (int e = 0; e < VEC; e++) r.b[i][e] = k0 + t / VB + i * RB < ke ? at_b(k0 + i * RB)[e] : (T)0;
+    };
+    auto stage = [&](const Regs &r, int buf) {
 #pragma unroll
-      for (int r = 0; r < 4; r++) {
-        const int e = t + r * 256;
-        const int am = e / TK, ak = e % TK;
-        const int64_t gm = m0 + am, gk = k0 + ak;
-        As[am][ak] = (gm < M && gk < K) ? A[gm * K + gk] : (T)0;
-        const int bk = e / TN, bn = e % TN;
-        const int64_t gk2 = k0 + bk, gn = n0 + bn;
-        Bs[bk][bn] = (gk2 < K && gn < N) ? B[gk2 * N + gn] : (T)0;
+      for (int i = 0; i < LA; i++) *(VL *)&As[buf][(t / 8 + RA * i) * SA + (t % 8) * VEC] = r.a[i];
+#pragma unroll
+      for (int i = 0; i < LB; i++) {
+        VL v = r.b[i];
+        if constexpr (SHIFT) {
+#pragma unroll
+          for (int e = 0; e < VEC; e++)
+#pragma unroll
+            for (int d = 1; e + d < VEC; d++) v[e] = sh == d ? r.b[i][e + d] : v[e];
+        }
+        *(VL *)&Bs[buf][(t / VB + i * RB) * SB + (t % VB) * VEC] = v;
       }
-      __syncthreads();
+    };
+    Acc acc[NTM][NTN];
+    double acc64[sizeof(T) == 4 ? NTM : 1][NTN][4];
 #pragma unroll
-      for (int kk = 0; kk < TK; kk += 4) {
-        T av[2], bv[2];
+    for (int a = 0; a < NTM; a++)
 #pragma unroll
-        for (int a = 0; a < 2; a++) av[a] = As[wm + a * 16 + (l % 16)][kk + l / 16];
+      for (int b = 0; b < NTN; b++)
 #pragma unroll
-        for (int b = 0; b < 2; b++) bv[b] = Bs[kk + l / 16][wn + b * 16 + (l % 16)];
+        for (int q = 0; q < 4; q++) {
+          acc[a][b][q] = 0;
+          if constexpr (sizeof(T) == 4) acc64[a][b][q] = 0.0;
+        }
+    auto multiply = [&](int buf) {
 #pragma unroll
-        for (int a = 0; a < 2; a++)
+      for (int s = 0; s < BK / (4 * VEC); s++) {
+        VL av[NTM];
 #pragma unroll
-          for (int b = 0; b < 2; b++) {
-            if constexpr (sizeof(T) == 8)
-              accd[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], accd[a][b], 0, 0, 0);
-            else
-              acc32[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[a], bv[b], acc32[a][b], 0, 0, 0);
-          }
-      }
-      __syncthreads();
-      if constexpr (sizeof(T) == 4) {
-        since_flush += TK;
-        if (since_flush >= 128) {
+        for (int a = 0; a < NTM; a++)
+          av[a] = *(const VL *)&As[buf][(wm + a * 16 + lr) * SA + s * 4 * VEC + lg * VEC];
 #pragma unroll
-          for (int a = 0; a < 2; a++)
+        for (int e = 0; e < VEC; e++) {
+          VC bv[NTN / CV];
 #pragma unroll
-            for (int b = 0; b < 2; b++) {
+          for (int h = 0; h < NTN / CV; h++)
+            bv[h] = *(const VC *)&Bs[buf][(s * 4 * VEC + lg * VEC + e) * SB + wn + h * 16 * CV + lr * CV];
 #pragma unroll
-              for (int q = 0; q < 4; q++) acc64[a][b][q] += (double)acc32[a][b][q];
-              acc32[a][b] = v4f{0.f, 0.f, 0.f, 0.f};
+          for (int a = 0; a < NTM; a++)
+#pragma unroll
+            for (int b = 0; b < NTN; b++) {
+              if constexpr (sizeof(T) == 8)
+                acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a][e], bv[b / CV][b % CV], acc[a][b], 0, 0, 0);
+              else
+                acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[a][e], bv[b / CV][b % CV], acc[a][b], 0, 0, 0);
             }
-          since_flush = 0;
+        }
+      }
+    };
+    auto flush = [&]() {
+      if constexpr (sizeof(T) == 4) {
+#pragma unroll
+        for (int a = 0; a < NTM; a++)
+#pragma unroll
+          for (int b = 0; b < NTN; b++)
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+              acc64[a][b][q] += (double)acc[a][b][q];
+              acc[a][b][q] = 0.f;
+            }
+      }
+    };
+    // UN tiles per round (128 k-terms for fp32, then the flush).  At its head
+    // tile i is in buffer 0, i + 1 in r1 and i + 2 in r0; a buffer is refilled
+    // one barrier after its last read.
+    constexpr int UN = sizeof(T) == 4 ? 128 / BK : 2;
+    Regs r0, r1;
+    if (nt > 0) {
+      fetch(r0, 0);
+      fetch(r1, 1);
+      stage(r0, 0);
+      fetch(r0, 2);
+    }
+    __syncthreads();
+    int64_t i = 0;
+    for (; i + UN <= nt; i += UN) {
+#pragma unroll
+      for (int u = 0; u < UN; u += 2) {
+        multiply(0);
+        stage(r1, 1);
+        fetch(r1, i + u + 3);
+        __syncthreads();
+        multiply(1);
+        stage(r0, 0);
+        fetch(r0, i + u + 4);
+        __syncthreads();
+      }
+      flush();
+    }
+    // up to UN - 1 more tiles and the rest: fewer than 128 terms in fp32
+    if (i < nt) {
+      multiply(0);
+      if (i + 1 < nt) {
+        stage(r1, 1);
+        __syncthreads();
+        multiply(1);
+        if (i + 2 < nt) {
+          stage(r0, 0);
+          __syncthreads();
+          multiply(0);
         }
       }
     }
-    // output layout of a 16x16 MFMA tile, lane l, column l%16, accumulator q:
+    if (kb + nt * BK < ke) {
+      fetch_rest(r0, kb + nt * BK);
+      __syncthreads();
+      stage(r0, 0);
+      __syncthreads();
+      multiply(0);
+    }
+    // output layout of a 16x16 MFMA tile, lane l, accumulator q:
     //   fp32 (16x16x4 f32): row 4*(l/16) + q
     //   fp64 (16x16x4 f64): row 4*q + l/16
+    // and tile h CV + e, lane column l % 16 holds column h 16 CV + (l % 16) CV + e
+    T *__restrict__ C = C0 + z * M * N;
+    double *__restrict__ P = W ? W + (z * gridDim.y + blockIdx.y) * M * N : nullptr;
 #pragma unroll
-    for (int a = 0; a < 2; a++)
+    for (int a = 0; a < NTM; a++)
 #pragma unroll
-      for (int b = 0; b < 2; b++)
+      for (int q = 0; q < 4; q++) {
+        const int64_t gm = m0 + wm + a * 16 + (sizeof(T) == 8 ? 4 * q + lg : 4 * lg + q);
+        if (gm >= M) continue;
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-          double v;
-          if constexpr (sizeof(T) == 8) v = accd[a][b][q];
-          else v = acc64[a][b][q] + (double)acc32[a][b][q];
-          const int64_t gm = m0 + wm + a * 16 + (sizeof(T) == 8 ? 4 * q + l / 16 : 4 * (l / 16) + q);
-          const int64_t gn = n0 + wn + b * 16 + (l % 16);
-          if (gm < M && gn < N) {
-            if (accumulate) v += (double)C[gm * N + gn];
-            C[gm * N + gn] = (T)v;
+        for (int h = 0; h < NTN / CV; h++) {
+          const int64_t gn = n0 + wn + h * 16 * CV + lr * CV;
+          double v[CV];
+#pragma unroll
+          for (int e = 0; e < CV; e++) {
+            v[e] = (double)acc[a][h * CV + e][q];
+            if constexpr (sizeof(T) == 4) v[e] += acc64[a][h * CV + e][q];
+          }
+          if (P) {
+#pragma unroll
+            for (int e = 0; e < CV; e++)
+              if (gn + e < N) P[gm * N + gn + e] = v[e];
+          } else if (!accumulate && gn + CV <= N) {
+            VCG o;
+#pragma unroll
+            for (int e = 0; e < CV; e++) o[e] = (T)v[e];
+            *(VCG *)(C + gm * N + gn) = o;
+          } else {
+#pragma unroll
+            for (int e = 0; e < CV; e++)
+              if (gn + e < N) C[gm * N + gn + e] = (T)(accumulate ? v[e] + (double)C[gm * N + gn + e] : v[e]);
           }
         }
+      }
     __syncthreads();  // the next batch restages As and Bs
   }
 }
 
-// Large tiles: 128x128 outputs per 256-thread block, each wave a 64x64
-// quadrant of 4x4 MFMA 16x16 tiles (16 MFMAs per 4-deep k step against 8
-// fragment reads), the next 32-deep k-tile prefetched into registers while
-// the current one is multiplied.  Used when both output sides reach 128.
-constexpr int BM = 128, BN = 128, BK = 32;
-
+// Products with fewer columns than a vector: one wave per row of C, exact
+// products summed in fp64.
 template <class T>
-__global__ void __launch_bounds__(256) gemm_mfma_128(const T *__restrict__ A0, const T *__restrict__ B0,
-                                                     T *__restrict__ C0, int64_t M, int64_t N, int64_t K,
-                                                     int accumulate, int64_t batch) {
-  __shared__ T As[BM][BK + 1];
-  __shared__ T Bs[BK][BN + 1];
-  constexpr int LA = BM * BK / 256, LB = BK * BN / 256;  // staged elements per thread
-  const int t = threadIdx.x;
-  const int w = t / WAVE, l = lane_id();
-  const int wm = (w / 2) * 64, wn = (w % 2) * 64;
-  for (int64_t z = blockIdx.z; z < batch; z += gridDim.z) {
-    const T *__restrict__ A = A0 + z * M * K;
-    const T *__restrict__ B = B0 + z * K * N;
-    T *__restrict__ C = C0 + z * M * N;
-    const int64_t m0 = (int64_t)blockIdx.y * BM, n0 = (int64_t)blockIdx.x * BN;
-    v4d accd[4][4];
-    v4f acc32[4][4];
-    double acc64[4][4][4];
+__global__ void __launch_bounds__(256) gemm_narrow(const T *__restrict__ A, const T *__restrict__ B,
+                                                   T *__restrict__ C, int64_t M, int N, int64_t K, int accumulate,
+                                                   int64_t batch) {
+  constexpr int MAXN = GemmVec<T>::N - 1;
+  const int64_t wid = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
+  const int64_t nw = ((int64_t)gridDim.x * blockDim.x) / WAVE;
+  for (int64_t r = wid; r < batch * M; r += nw) {
+    const T *a = A + r * K, *b = B + r / M * K * N;
+    double acc[MAXN] = {};
+    for (int64_t k = lane_id(); k < K; k += WAVE)
 #pragma unroll
-    for (int a = 0; a < 4; a++)
+      for (int n = 0; n < MAXN; n++)
+        if (n < N) acc[n] += (double)a[k] * (double)b[k * N + n];
 #pragma unroll
-      for (int b = 0; b < 4; b++) {
-        if constexpr (sizeof(T) == 8) {
-          accd[a][b] = v4d{0.0, 0.0, 0.0, 0.0};
-        } else {
-          acc32[a][b] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int q = 0; q < 4; q++) acc64[a][b][q] = 0.0;
-        }
-      }
-    T ra[LA], rb[LB];
-    auto fetch = [&](int64_t k0) {
-#pragma unroll
-      for (int r = 0; r < LA; r++) {
-        const int e = t + r * 256, am = e / BK, ak = e % BK;
-        const int64_t gm = m0 + am, gk = k0 + ak;
-        ra[r] = (gm < M && gk < K) ? A[gm * K + gk] : (T)0;
-      }
-#pragma unroll
-      for (int r = 0; r < LB; r++) {
-        const int e = t + r * 256, bk = e / BN, bn = e % BN;
-        const int64_t gk = k0 + bk, gn = n0 + bn;
-        rb[r] = (gk < K && gn < N) ? B[gk * N + gn] : (T)0;
-      }
-    };
-    fetch(0);
-    int since_flush = 0;
-    for (int64_t k0 = 0; k0 < K; k0 += BK) {
-#pragma unroll
-      for (int r = 0; r < LA; r++) {
-        const int e = t + r * 256;
-        As[e / BK][e % BK] = ra[r];
-      }
-#pragma unroll
-      for (int r = 0; r < LB; r++) {
-        const int e = t + r * 256;
-        Bs[e / BN][e % BN] = rb[r];
-      }
-      __syncthreads();
-      if (k0 + BK < K) fetch(k0 + BK);
-#pragma unroll
-      for (int kk = 0; kk < BK; kk += 4) {
-        T av[4], bv[4];
-#pragma unroll
-        for (int a = 0; a < 4; a++) av[a] = As[wm + a * 16 + (l % 16)][kk + l / 16];
-#pragma unroll
-        for (int b = 0; b < 4; b++) bv[b] = Bs[kk + l / 16][wn + b * 16 + (l % 16)];
-#pragma unroll
-        for (int a = 0; a < 4; a++)
-#pragma unroll
-          for (int b = 0; b < 4; b++) {
-            if constexpr (sizeof(T) == 8)
-              accd[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], accd[a][b], 0, 0, 0);
-            else
-              acc32[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[a], bv[b], acc32[a][b], 0, 0, 0);
-          }
-      }
-      __syncthreads();
-      if constexpr (sizeof(T) == 4) {
-        since_flush += BK;
-        if (since_flush >= 128) {
-#pragma unroll
-          for (int a = 0; a < 4; a++)
-#pragma unroll
-            for (int b = 0; b < 4; b++) {
-#pragma unroll
-              for (int q = 0; q < 4; q++) acc64[a][b][q] += (double)acc32[a][b][q];
-              acc32[a][b] = v4f{0.f, 0.f, 0.f, 0.f};
-            }
-          since_flush = 0;
-        }
-      }
+    for (int n = 0; n < MAXN; n++) {
+      const double v = wave_sum(acc[n]);
+      if (n < N && lane_id() == 0) C[r * N + n] = (T)(accumulate ? v + (double)C[r * N + n] : v);
     }
-#pragma unroll
-    for (int a = 0; a < 4; a++)
-#pragma unroll
-      for (int b = 0; b < 4; b++)
-#pragma unroll
-        for (int q = 0; q < 4; q++) {
-          double v;
-          if constexpr (sizeof(T) == 8) v = accd[a][b][q];
-          else v = acc64[a][b][q] + (double)acc32[a][b][q];
-          const int64_t gm = m0 + wm + a * 16 + (sizeof(T) == 8 ? 4 * q + l / 16 : 4 * (l / 16) + q);
-          const int64_t gn = n0 + wn + b * 16 + (l % 16);
-          if (gm < M && gn < N) {
-            if (accumulate) v += (double)C[gm * N + gn];
-            C[gm * N + gn] = (T)v;
-          }
-        }
+  }
+}
+
+// C (+)= the S partial products of each batch, added in order in fp64.
+template <class T>
+__global__ void gemm_combine(const double *__restrict__ W, T *__restrict__ C, int64_t mn, int S, int64_t total,
+                             int accumulate) {
+  for (int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; o < total; o += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t z = o / mn, e = o - z * mn;
+    const double *p = W + z * S * mn + e;
+    double v = 0.0;
+    for (int y = 0; y < S; y++) v += p[(int64_t)y * mn];
+    if (accumulate) v += (double)C[o];
+    C[o] = (T)v;
+  }
+}
+
+template <class T, int NTM, int NTN, int WM, int WN, class Off = uint32_t>
+void gemm_launch(Ctx *c, const T *A, const T *B, T *C, int64_t M, int64_t N, int64_t K, int accumulate,
+                 int64_t batch, int S, hipStream_t s) {
+  using G = GemmTile<T, NTM, NTN, WM, WN>;
+  const int64_t tiles = ((M + G::TM - 1) / G::TM) * ((N + G::TN - 1) / G::TN);
+  const int64_t kt = (K + G::BK - 1) / G::BK;
+  int64_t kchunk = std::max<int64_t>(K, 1);
+  Buf ws;
+  if (S > 1) {
+    kchunk = (kt + S - 1) / S * G::BK;
+    S = (int)((K + kchunk - 1) / kchunk);
+  }
+  if (S > 1) {
+    try {
+      ws = Buf(c, sizeof(double) * (size_t)(S * batch) * (size_t)(M * N));
+    } catch (const Error &) {  // no room for the partial sums: one pass over k
+      S = 1;
+      kchunk = K;
+    }
+  }
+  const dim3 grid((unsigned)tiles, (unsigned)std::max(S, 1), (unsigned)std::min<int64_t>(batch, 65535));
+  if (N % G::VEC == 0)
+    gemm_mfma<T, NTM, NTN, WM, WN, Off, false><<<grid, G::THREADS, 0, s>>>(A, B, C, ws.as<double>(), M, N, K, kchunk,
+                                                                          accumulate, batch);
+  else
+    gemm_mfma<T, NTM, NTN, WM, WN, Off, true><<<grid, G::THREADS, 0, s>>>(A, B, C, ws.as<double>(), M, N, K, kchunk,
+                                                                         accumulate, batch);
+  SRTC_LAUNCH_CHECK("gemm_mfma");
+  if (S > 1) {
+    const int64_t total = batch * M * N;
+    gemm_combine<T><<<(unsigned)std::min<int64_t>((total + 255) / 256, 65536), 256, 0, s>>>(ws.as<double>(), C, M * N,
+                                                                                         S, total, accumulate);
+    SRTC_LAUNCH_CHECK("gemm_combine");
   }
 }
 
@@ -375,35 +479,73 @@ void dense_permute_combine(int sr, int dt, IdVal id, const void *src, void *dst,
   SRTC_DISPATCH_SR(sr, dt, permute_combine_typed, q);
 }
 
-void dense_gemm_plus_times(Ctx *, int dt, const void *A, const void *B, void *C, int64_t M, int64_t N, int64_t K,
-                           int accumulate, hipStream_t s, int64_t batch) {
-  if (M == 0 || N == 0 || batch <= 0) return;
-  if (M >= BM && N >= BN) {
-    dim3 g((unsigned)((N + BN - 1) / BN), (unsigned)((M + BM - 1) / BM), (unsigned)std::min<int64_t>(batch, 65535));
-    if (g.y > 65535) fail(SRTC_ERR_UNSUPPORTED, "dense gemm: too many row tiles");
-    if (dt == SRTC_F64)
-      gemm_mfma_128<double><<<g, 256, 0, s>>>((const double *)A, (const double *)B, (double *)C, M, N, K, accumulate,
-                                               batch);
-    else if (dt == SRTC_F32)
-      gemm_mfma_128<float><<<g, 256, 0, s>>>((const float *)A, (const float *)B, (float *)C, M, N, K, accumulate,
-                                              batch);
-    else
-      fail(SRTC_ERR_DTYPE, "dense (+,x) needs F64 or F32");
-    SRTC_LAUNCH_CHECK("gemm_mfma_128");
+namespace {
+// Tile and split of a product.  64 x 64 tiles, four blocks per CU, are the
+// general shape: fp64 8192^3 15.1 ms (72.8 TFLOP/s) and 2560^3 0.53 ms,
+// against 15.3 and 0.62 ms with 128 x 128 tiles, whose last round of blocks
+// leaves more of the chip idle.  128 x 64 tiles read A's and B's entries less
+// often and gain 1 to 5% (fp64 4096^3 1.99 -> 1.92 ms, fp32 2048^3 0.149 ->
+// 0.142 ms) where their blocks fill the last round of two per CU to at
+// least nine tenths (2560^3, filled to 0.78: 0.53 -> 0.61 ms).
+// Otherwise k may be split over S blocks.  The time of S parts follows the
+// blocks per CU: one alone takes c1 ns per k-term (it waits on memory), b
+// together c2 b; a split adds a launch (6 us) and its fp64 partial sums
+// written and read at about 4 TB/s.  At c1, c2 as measured (64 x 64 x 5000:
+// 190 us fp64, 108 us fp32; 2000^3: 246 and 148 us) S = 1 stays for 1000^3
+// (46 against 48 us at S = 2), 500 x 500 x 3000 fp64 goes from 118 to 40 us
+// and 800 x 2500 x 6000 from 555 to 411 us.  Partial sums take at most 64 MB;
+// nothing is split while the stream is captured, where nothing is allocated.
+template <class T, int LM, int LN, int WM, int WN>
+void gemm_shape(Ctx *c, const T *A, const T *B, T *C, int64_t M, int64_t N, int64_t K, int accumulate,
+                int64_t batch, hipStream_t s) {
+  if (N < GemmVec<T>::N) {
+    gemm_narrow<T><<<(unsigned)std::min<int64_t>((M * batch + 3) / 4, 16384), 256, 0, s>>>(A, B, C, M, (int)N, K,
+                                                                                         accumulate, batch);
+    SRTC_LAUNCH_CHECK("gemm_narrow");
     return;
   }
-  dim3 grid((unsigned)((N + TN - 1) / TN), (unsigned)((M + TM - 1) / TM),
-            (unsigned)std::min<int64_t>(batch, 65535));
-  if (grid.y > 65535) fail(SRTC_ERR_UNSUPPORTED, "dense gemm: too many row tiles");
+  auto blocks = [&](int tm, int tn) { return ((M + tm - 1) / tm) * ((N + tn - 1) / tn) * batch; };
+  const int64_t cus = c->num_cus;
+  // byte offsets of a row tile past 32 bits: 64-bit ones
+  if (std::max(K, N) >= (int64_t(1) << 32) / (128 * (int64_t)sizeof(T))) {
+    gemm_launch<T, 2, 2, 2, 2, uint64_t>(c, A, B, C, M, N, K, accumulate, batch, 1, s);
+    return;
+  }
+  const int64_t big = blocks(LM * 16 * WM, LN * 16 * WN), small = blocks(64, 64);
+  const int64_t round = 2 * cus;
+  if (10 * big >= 9 * ((big + round - 1) / round * round)) {
+    gemm_launch<T, LM, LN, WM, WN>(c, A, B, C, M, N, K, accumulate, batch, 1, s);
+    return;
+  }
+  const double c1 = sizeof(T) == 8 ? 38e-3 : 21.6e-3, c2 = sizeof(T) == 8 ? 31e-3 : 18.5e-3;  // us
+  const double mn = (double)M * (double)N * (double)batch;
+  int best = 1;
+  double t_best = 0;
+  for (int S = 1; S <= 32 && (S == 1 || (K / S >= 64 && 8.0 * S * mn <= (double)(64 << 20))); S++) {
+    const double b = (double)((small * S + cus - 1) / cus);
+    const double t = (double)K / S * std::max(c1, c2 * b) + (S > 1 ? 6.0 + S * mn * 16.0 / 4e6 : 0.0);
+    if (S == 1 || t < t_best) {
+      best = S;
+      t_best = t;
+    }
+  }
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (best > 1 && (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone)) best = 1;
+  gemm_launch<T, 2, 2, 2, 2>(c, A, B, C, M, N, K, accumulate, batch, best, s);
+}
+}  // namespace
+
+void dense_gemm_plus_times(Ctx *c, int dt, const void *A, const void *B, void *C, int64_t M, int64_t N, int64_t K,
+                           int accumulate, hipStream_t s, int64_t batch) {
+  if (M == 0 || N == 0 || batch <= 0) return;
+  const int64_t side = M >= 128 && N >= 128 ? 128 : 64;
+  if ((M + side - 1) / side > 65535) fail(SRTC_ERR_UNSUPPORTED, "dense gemm: too many row tiles");
   if (dt == SRTC_F64)
-    gemm_mfma<double><<<grid, 256, 0, s>>>((const double *)A, (const double *)B, (double *)C, M, N, K, accumulate,
-                                            batch);
+    gemm_shape<double, 2, 2, 4, 2>(c, (const double *)A, (const double *)B, (double *)C, M, N, K, accumulate, batch, s);
   else if (dt == SRTC_F32)
-    gemm_mfma<float><<<grid, 256, 0, s>>>((const float *)A, (const float *)B, (float *)C, M, N, K, accumulate,
-                                           batch);
+    gemm_shape<float, 4, 2, 2, 2>(c, (const float *)A, (const float *)B, (float *)C, M, N, K, accumulate, batch, s);
   else
     fail(SRTC_ERR_DTYPE, "dense (+,x) needs F64 or F32");
-  SRTC_LAUNCH_CHECK("gemm_mfma");
 }
 
 void dense_permute(const void *src, void *dst, int esize, int order, const int64_t *dims, const int *perm,
