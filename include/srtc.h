@@ -420,13 +420,15 @@ srtc_status srtc_transform(srtc_ctx *ctx, srtc_transform_op op, double alpha, co
  * least one update, as the listing's do-while).  A: n x n CSR (split 1) or
  * COO, F64 or F32; b, x: dense length-n vectors of the same type (device);
  * x is overwritten with that x^l.  Each step is one fused kernel (row sum,
- * update and the residual of the incoming iterate) plus a fixed-order
- * reduction; steps are replayed as captured HIP graphs of
+ * update and the residual of the incoming iterate, summed in a fixed order
+ * at the head of the next step); steps are replayed as captured HIP graphs of
  * `steps_per_check` steps and the host reads that many residual norms per
  * replay.  *iters_out = l, *resid_out = |b - A x^l|_2 (host, may be NULL).
  * Errors: SRTC_ERR_ARG if a row has no nonzero diagonal entry,
  * SRTC_ERR_NOT_CONVERGED if no l <= max_iters (<= 0: 10,000) qualifies (x
- * then holds x^max_iters).  Needs 3n values of scratch. */
+ * then holds x^max_iters).  Needs 3n values of scratch; large systems
+ * with rows of much the same length also take a copy of A in another layout
+ * where there is room for it. */
 srtc_status srtc_jacobi(srtc_ctx *ctx, const srtc_tensor *A, const srtc_tensor *b, srtc_tensor *x, double tol,
                         int64_t max_iters, int32_t steps_per_check, int64_t *iters_out, double *resid_out,
                         void *stream);

@@ -1304,7 +1304,11 @@ srtc_status srtc_jacobi(srtc_ctx *ctx, const srtc_tensor *A, const srtc_tensor *
     JacobiState *st = reinterpret_cast<JacobiState *>(stb.p);
     void *bufs[2] = {x->vals, xb.p};
     const double tol2 = tol * tol;
-    auto step = [&](int t, hipStream_t q) { jacobi_step_call(pl, b->vals, bufs[t & 1], bufs[(t & 1) ^ 1], st, tol2, q); };
+    // step j of a run whose first step reads buffer `par`
+    auto step = [&](int par, int j, bool last, hipStream_t q) {
+      const int t = (par + j) & 1;
+      jacobi_step_call(pl, b->vals, bufs[t], bufs[t ^ 1], st, tol2, j, last, q);
+    };
     JacobiState hs{};
     if (n > 0) {
       // k steps per replay; after the stopping step the rest do nothing,
@@ -1324,7 +1328,7 @@ srtc_status srtc_jacobi(srtc_ctx *ctx, const srtc_tensor *A, const srtc_tensor *
         }
       } cleanup{&cap, &graph, &exec};
       SRTC_HIP(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
-      for (int t = 0; t < k; t++) step(t, cap);
+      for (int t = 0; t < k; t++) step(0, t, t == k - 1, cap);
       SRTC_HIP(hipStreamEndCapture(cap, &graph));
       SRTC_HIP(hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
       int64_t ran = 0;  // steps issued; the last one checks x^{ran-1}
@@ -1335,7 +1339,7 @@ srtc_status srtc_jacobi(srtc_ctx *ctx, const srtc_tensor *A, const srtc_tensor *
         } else {
           // the remaining steps one by one, parity continuing from `ran`
           const int64_t left = max_iters + 1 - ran;
-          for (int64_t t = 0; t < left; t++) step((int)((ran + t) & 1), s);
+          for (int64_t t = 0; t < left; t++) step((int)((ran + t) & 1), 0, true, s);
           ran += left;
         }
         read_to_host(c, &hs, st, sizeof(hs), s);

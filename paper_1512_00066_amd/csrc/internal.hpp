@@ -248,31 +248,39 @@ void transform_dense_call(int op, int dt, double alpha, const int64_t *cext, int
                           const int64_t *sa, const void *B, const int64_t *sb, void *C, hipStream_t s);
 
 // Jacobi iteration on an n x n CSR A: the inverse-free diagonal d, the
-// lanes per row and the fixed grid whose per-block residual partials are
-// summed in a fixed order.
+// lanes per row, for large systems with even rows a copy of A in slices of 64
+// rows (columns as 16-bit offsets from their row where all fit, else 32-bit),
+// and the fixed grid whose per-block residual partials are summed in a fixed
+// order (two sets, by step parity).
 struct JacobiPlan {
   Ctx *ctx = nullptr;
   int dt = SRTC_F64;
   CsrView A;
   int G = 32;
   int grid = 1;
-  Buf dbuf, part;
+  int64_t slices = 0;  // 0: the steps read the CSR
+  bool wide = false;   // 32-bit offsets
+  Buf dbuf, part, start, off, sval;
   // fails with SRTC_ERR_ARG when a row has no nonzero diagonal entry
   void build(Ctx *c, int dt, const CsrView &A, hipStream_t s);
 };
 // Device state of a Jacobi solve: iter = l of the current iterate x^l,
 // done = 1 once |b - A x^l|^2 <= tol^2 with l >= 1 (rsq = that value; while
-// running, the last residual formed).
+// running, the last residual formed at the end of a run of steps), base = l
+// at the start of the current run of steps.
 struct JacobiState {
   int64_t iter;
   int32_t done;
   int32_t pad;
   double rsq;
+  int64_t base;
 };
-// Unless st->done: x_out = (b - (A - diag) x_in) / diag, then the residual
-// of x_in decides whether to stop (x_in kept) or advance st->iter.
+// Step j of a run of steps, unless st->done: x_out = (b - (A - diag) x_in) /
+// diag.  The residual of a step's x_in decides whether to stop (x_in kept) at
+// the head of the next step, or, for the last step of the run, right after
+// it; st->base then advances by j + 1.
 void jacobi_step_call(const JacobiPlan &pl, const void *b, const void *x_in, void *x_out, JacobiState *st,
-                      double tol2, hipStream_t s);
+                      double tol2, int j, bool last, hipStream_t s);
 
 // ------------------------------------------------------------- features --
 void spgemm_features(Ctx *c, int sr, int dt, const CsrView &A, const CsrView &B, float *out,

@@ -73,33 +73,137 @@ void transform_typed(int op, const void *A, const void *B, void *C, const BcastA
 
 // ------------------------------------------------------------- Jacobi --
 
-// The diagonal of each row (0 where missing); bad[0] set if any is 0.
+// The diagonal of each row (0 where missing), eight lanes per row; flags[0]
+// set if any is 0, flags[1] if some entry lies 2^15 or more columns from its
+// row.
 template <class T>
-__global__ void jacobi_diag(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, const T *__restrict__ val,
-                            int64_t n, T *__restrict__ d, int32_t *bad) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+__global__ void __launch_bounds__(256) jacobi_diag(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
+                                                   const T *__restrict__ val, int64_t n, T *__restrict__ d,
+                                                   int64_t *flags) {
+  constexpr int G = 8;
+  const int sub = lane_id() % G;
+  const int64_t ngrp = (int64_t)gridDim.x * blockDim.x / G;
+  bool zero = false, far = false;
+  for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / G; i < n; i += ngrp) {
     T dii = 0;
-    for (int64_t p = rp[i]; p < rp[i + 1]; p++)
-      if (col[p] == i) dii += val[p];
-    d[i] = dii;
-    if (dii == (T)0) atomicOr(bad, 1);
+    for (int64_t p = rp[i] + sub; p < rp[i + 1]; p += G) {
+      const int64_t o = col[p] - i;
+      if (o == 0) dii += val[p];
+      far |= o < -32768 || o > 32767;
+    }
+#pragma unroll
+    for (int w = G / 2; w >= 1; w >>= 1) dii += __shfl_xor(dii, w, G);
+    if (sub == 0) d[i] = dii;
+    zero |= dii == (T)0;
+  }
+  if (__any(zero) && lane_id() == 0) atomicOr((unsigned long long *)&flags[0], 1ull);
+  if (__any(far) && lane_id() == 0) atomicOr((unsigned long long *)&flags[1], 1ull);
+}
+
+// Slices of 64 rows, one per lane of a wave, stored entry by entry: entry k of
+// the slice's rows at (start + k) 64 .. + 63, start = the scan of the slices'
+// longest rows.
+__global__ void __launch_bounds__(256) slice_widths(const int64_t *__restrict__ rp, int64_t n, int64_t slices,
+                                                    int64_t *__restrict__ width) {
+  const int64_t nw = (int64_t)gridDim.x * blockDim.x / WAVE;
+  for (int64_t q = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / WAVE; q < slices; q += nw) {
+    const int64_t i = q * WAVE + lane_id();
+    int64_t len = i < n ? rp[i + 1] - rp[i] : 0;
+#pragma unroll
+    for (int w = WAVE / 2; w >= 1; w >>= 1) len = max(len, (int64_t)__shfl_xor((long long)len, w, WAVE));
+    if (lane_id() == 0) width[q] = len;
   }
 }
 
-// One Jacobi step for G lanes per row: x_out = (b - R x_in) / d and the
-// block's partial sum of r_i^2 for r = b - A x_in (fp64), written to
-// part[blockIdx.x].  256 threads per block, a grid-stride loop over rows.
-// Does nothing once the iteration has stopped (st->done), so the steps
-// of a replayed graph after the stopping one leave both buffers alone.
+// Columns as offsets from the row in C; rows shorter than their slice are
+// filled up with value 0 at offset 0 (the diagonal, which steps skip).
+template <class T, class C>
+__global__ void __launch_bounds__(256) slice_fill(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
+                                                  const T *__restrict__ val, int64_t n, int64_t slices,
+                                                  const int64_t *__restrict__ start, C *__restrict__ off,
+                                                  T *__restrict__ sval) {
+  const int l = lane_id();
+  const int64_t nw = (int64_t)gridDim.x * blockDim.x / WAVE;
+  for (int64_t q = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / WAVE; q < slices; q += nw) {
+    const int64_t i = q * WAVE + l;
+    const int64_t a = i < n ? rp[i] : 0, len = i < n ? rp[i + 1] - a : 0;
+    const int64_t s0 = start[q], w = start[q + 1] - s0;
+    for (int64_t k = 0; k < w; k++) {
+      const bool in = k < len;
+      off[(s0 + k) * WAVE + l] = in ? (C)(col[a + k] - i) : (C)0;
+      sval[(s0 + k) * WAVE + l] = in ? val[a + k] : (T)0;
+    }
+  }
+}
+
+// Sum of part[0..nb) in a fixed order by a block of BS threads (every thread
+// gets it).
+template <int BS> __device__ __forceinline__ double sum_parts(const double *__restrict__ part, int64_t nb) {
+  __shared__ double red[BS / WAVE];
+  double t = 0.0;
+  for (int64_t q = threadIdx.x; q < nb; q += BS) t += part[q];
+  t = wave_sum(t);
+  if (lane_id() == 0) red[threadIdx.x / WAVE] = t;
+  __syncthreads();
+  double u = 0.0;
+#pragma unroll
+  for (int w = 0; w < BS / WAVE; w++) u += red[w];
+  return u;
+}
+
+// Whether step j of a run of steps stops before it starts: for j > 0 every
+// block adds up the partial sums of step j - 1 itself (8 KB from L2, the same
+// order everywhere) and stops if that iterate, l = st->base + j - 1, meets
+// the tolerance; block 0 records it.  (A kernel of its own for that sum took
+// one block 17 us and a launch per step.)  Later steps see st->done.  The
+// decision is the same in every block, also while block 0 sets st->done.
+template <int BS>
+__device__ __forceinline__ bool step_stops(const double *__restrict__ part_in, int j, JacobiState *st, double tol2) {
+  if (st->done) return true;
+  if (j == 0) return false;
+  const double u = sum_parts<BS>(part_in, gridDim.x);
+  const int64_t l = st->base + j - 1;
+  if (l < 1 || u > tol2 || u != u) return false;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st->rsq = u;
+    st->iter = l;
+    st->done = 1;
+  }
+  return true;
+}
+
+// The block's sum of rr to part_out[blockIdx.x].
+template <int BS> __device__ __forceinline__ void put_part(double rr, double *part_out) {
+  __shared__ double red[BS / WAVE];
+  rr = wave_sum(rr);
+  if (lane_id() == 0) red[threadIdx.x / WAVE] = rr;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double t = 0.0;
+    for (int w = 0; w < BS / WAVE; w++) t += red[w];
+    part_out[blockIdx.x] = t;
+  }
+}
+
+// Block id renumbered so that blocks of one XCD (id mod 8) are neighbours.
+__device__ __forceinline__ int xcd_block() {
+  const int nb = gridDim.x;
+  return nb % 8 == 0 ? (int)(blockIdx.x % 8) * (nb / 8) + (int)(blockIdx.x / 8) : (int)blockIdx.x;
+}
+
+// Step j of a run of steps (a replayed graph): x_out = (b - R x_in) / d and
+// the block's partial sum of r_i^2 for r = b - A x_in (fp64).  G lanes per
+// row on the CSR itself; for small systems and uneven rows.
+constexpr int JAC_BS = 512;
 template <class T, int G>
-__global__ void __launch_bounds__(256) jacobi_step(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
-                                                   const T *__restrict__ val, const T *__restrict__ d,
-                                                   const T *__restrict__ b, const T *__restrict__ x_in,
-                                                   T *__restrict__ x_out, int64_t n, double *__restrict__ part,
-                                                   const JacobiState *__restrict__ st) {
-  __shared__ double red[256 / WAVE];
-  if (st->done) return;  // uniform over the grid
-  const int lane = lane_id(), sub = lane % G;
+__global__ void __launch_bounds__(JAC_BS) jacobi_step(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
+                                                      const T *__restrict__ val, const T *__restrict__ d,
+                                                      const T *__restrict__ b, const T *__restrict__ x_in,
+                                                      T *__restrict__ x_out, int64_t n, double *__restrict__ part_out,
+                                                      const double *__restrict__ part_in, int j, JacobiState *st,
+                                                      double tol2) {
+  if (step_stops<JAC_BS>(part_in, j, st, tol2)) return;
+  const int sub = lane_id() % G;
   const int64_t grp = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / G;
   const int64_t ngrp = ((int64_t)gridDim.x * blockDim.x) / G;
   double rr = 0.0;
@@ -114,17 +218,17 @@ __global__ void __launch_bounds__(256) jacobi_step(const int64_t *__restrict__ r
     // four entries per lane per pass, all loads issued before the sums;
     // padding uses column i, which the diagonal test skips
     for (int64_t p = rp[i] + sub; p < p1; p += 4 * G) {
-      int32_t j[4];
+      int32_t c[4];
       T v[4];
 #pragma unroll
       for (int u = 0; u < 4; u++) {
         const bool ok = p + u * G < p1;
-        j[u] = ok ? col[p + u * G] : (int32_t)i;
+        c[u] = ok ? col[p + u * G] : (int32_t)i;
         v[u] = ok ? val[p + u * G] : (T)0;
       }
       double xv[4];
 #pragma unroll
-      for (int u = 0; u < 4; u++) xv[u] = j[u] != i ? (double)x_in[j[u]] : 0.0;
+      for (int u = 0; u < 4; u++) xv[u] = c[u] != i ? (double)x_in[c[u]] : 0.0;
 #pragma unroll
       for (int u = 0; u < 4; u++) s += (double)v[u] * xv[u];
     }
@@ -136,34 +240,83 @@ __global__ void __launch_bounds__(256) jacobi_step(const int64_t *__restrict__ r
       rr += r * r;
     }
   }
-  rr = wave_sum(rr);
-  if (lane == 0) red[threadIdx.x / WAVE] = rr;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double t = 0.0;
-    for (int w = 0; w < 256 / WAVE; w++) t += red[w];
-    part[blockIdx.x] = t;
-  }
+  put_part<JAC_BS>(rr, part_out);
 }
 
-// The residual of the step's incoming iterate x^l (l = st->iter): the sum
-// of part[0..nb) in a fixed order (one block of 256 threads).  Stops the
-// iteration when l >= 1 and |r|^2 <= tol2, else moves on to x^{l+1}.
-__global__ void __launch_bounds__(256) jacobi_reduce(const double *__restrict__ part, int64_t nb,
+// The same step on the slices: one row per lane, so every load of A is one
+// contiguous run per wave and the row sum needs no shuffles.  Bound by the
+// stream of A (10 bytes per fp64 entry with 16-bit offsets, 12 with 32-bit
+// ones); on the CSR, eight lanes per row, about 25 vector instructions per
+// entry bound it instead.  Blocks of one XCD take neighbouring slices, so its
+// L2 holds its part of x_in.  Stencil 100^3 (26.5 M nonzeros), per update:
+// fp64 103 us before (83 the step, 17 the separate sum), 65.6 now (100 on the
+// CSR); fp32 49.6 (69 on the CSR); stencil 50^3 fp64 14.8 (16.7).
+template <class T, class C>
+__global__ void __launch_bounds__(JAC_BS, 8) jacobi_slices(const int64_t *__restrict__ start, const C *__restrict__ off,
+                                                        const T *__restrict__ sval, const T *__restrict__ d,
+                                                        const T *__restrict__ b, const T *__restrict__ x_in,
+                                                        T *__restrict__ x_out, int64_t n, int64_t slices,
+                                                        double *__restrict__ part_out,
+                                                        const double *__restrict__ part_in, int j, JacobiState *st,
+                                                        double tol2) {
+  constexpr int U = 7;  // entries in flight per lane: 64 registers, eight waves per SIMD
+  if (step_stops<JAC_BS>(part_in, j, st, tol2)) return;
+  const int l = lane_id();
+  const int64_t nw = (int64_t)gridDim.x * (JAC_BS / WAVE);
+  const int64_t w0 = (int64_t)xcd_block() * (JAC_BS / WAVE) + threadIdx.x / WAVE;
+  double rr = 0.0;
+  for (int64_t q = w0; q < slices; q += nw) {
+    const int64_t i = q * WAVE + l;
+    const int64_t s0 = start[q];
+    const int w = (int)(start[q + 1] - s0);
+    const bool in = i < n;
+    const double bi = in ? (double)b[i] : 0.0, di = in ? (double)d[i] : 1.0, xi = in ? (double)x_in[i] : 0.0;
+    const C *po = off + s0 * WAVE + l;
+    const T *pv = sval + s0 * WAVE + l;
+    const T *px = x_in + i;
+    double s = 0.0;
+    for (int k = 0; k < w; k += U) {
+      C o[U];
+      T v[U];
+#pragma unroll
+      for (int u = 0; u < U; u++) {
+        o[u] = k + u < w ? po[u * WAVE] : (C)0;
+        v[u] = k + u < w ? pv[u * WAVE] : (T)0;
+      }
+      po += U * WAVE;
+      pv += U * WAVE;
+      double xv[U];
+#pragma unroll
+      for (int u = 0; u < U; u++) xv[u] = o[u] != 0 ? (double)px[o[u]] : 0.0;
+#pragma unroll
+      for (int u = 0; u < U; u++) s += (double)v[u] * xv[u];
+    }
+    if (in) {
+      x_out[i] = (T)((bi - s) / di);
+      const double r = bi - s - di * xi;
+      rr += r * r;
+    }
+  }
+  put_part<JAC_BS>(rr, part_out);
+}
+
+// The end of a run of k steps: the residual of the last step's incoming
+// iterate x^l, l = st->base + k - 1 (one block of 256 threads).  Stops the
+// iteration when l >= 1 and |r|^2 <= tol2, else moves on to x^{base + k}.
+__global__ void __launch_bounds__(256) jacobi_reduce(const double *__restrict__ part, int64_t nb, int k,
                                                      JacobiState *__restrict__ st, double tol2) {
-  __shared__ double red[256 / WAVE];
   if (st->done) return;  // uniform over the block
-  double t = 0.0;
-  for (int64_t q = threadIdx.x; q < nb; q += 256) t += part[q];
-  t = wave_sum(t);
-  if (lane_id() == 0) red[threadIdx.x / WAVE] = t;
-  __syncthreads();
+  const double u = sum_parts<256>(part, nb);
   if (threadIdx.x == 0) {
-    double u = 0.0;
-    for (int w = 0; w < 256 / WAVE; w++) u += red[w];
+    const int64_t l = st->base + k - 1;
     st->rsq = u;
-    if (st->iter >= 1 && u <= tol2) st->done = 1;
-    else st->iter += 1;
+    if (l >= 1 && u <= tol2) {
+      st->iter = l;
+      st->done = 1;
+    } else {
+      st->base += k;
+      st->iter = st->base;
+    }
   }
 }
 
@@ -186,6 +339,11 @@ void transform_dense_call(int op, int dt, double alpha, const int64_t *cext, int
   else fail(SRTC_ERR_DTYPE, "transforms are defined for F64 and F32");
 }
 
+// Fewest slices of 64 rows that the steps take one row per lane: fewer leave
+// CUs without a wave (stencil 25^3, 244 slices: 15.3 us per update against
+// 8.9 with eight lanes per row; 50^3, 1,954: 14.8 against 16.7).
+constexpr int64_t JAC_SLICES_MIN = 1024;
+
 void JacobiPlan::build(Ctx *c, int dt_, const CsrView &A_, hipStream_t s) {
   ctx = c;
   dt = dt_;
@@ -196,58 +354,126 @@ void JacobiPlan::build(Ctx *c, int dt_, const CsrView &A_, hipStream_t s) {
   // dependent loads of a row (row pointer, then columns, then x)
   G = 4;
   while (G < 64 && 4 * G < avg) G <<= 1;
-  grid = (int)std::max<int64_t>(1, std::min<int64_t>((n * G + 255) / 256, 16384));
   const size_t es = dtype_size(dt);
   dbuf = Buf(c, es * (size_t)std::max<int64_t>(n, 1));
-  part = Buf(c, sizeof(double) * (size_t)grid);
-  Buf bad(c, 64);
-  fill_i32(bad.as<int32_t>(), 1, 0, s);
-  const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 65536));
+  // flags, then the slices' widths and starts
+  const int64_t slices_ = (n + WAVE - 1) / WAVE;
+  Buf fw(c, sizeof(int64_t) * (size_t)(2 + slices_));
+  start = Buf(c, sizeof(int64_t) * (size_t)(slices_ + 1));
+  int64_t *flags = fw.as<int64_t>();
+  fill_i64(flags, 2, 0, s);
+  // slices for systems that fill the chip with one row per lane
+  const bool want = slices_ >= JAC_SLICES_MIN;
+  int64_t h[3] = {0, 0, 0};
   if (n > 0) {
+    const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>((n * 8 + 255) / 256, 8192));
     if (dt == SRTC_F64)
-      jacobi_diag<double><<<g, 256, 0, s>>>(A.rowptr, A.col, (const double *)A.val, n, dbuf.as<double>(),
-                                             bad.as<int32_t>());
+      jacobi_diag<double><<<g, 256, 0, s>>>(A.rowptr, A.col, (const double *)A.val, n, dbuf.as<double>(), flags);
     else
-      jacobi_diag<float><<<g, 256, 0, s>>>(A.rowptr, A.col, (const float *)A.val, n, dbuf.as<float>(),
-                                            bad.as<int32_t>());
+      jacobi_diag<float><<<g, 256, 0, s>>>(A.rowptr, A.col, (const float *)A.val, n, dbuf.as<float>(), flags);
     SRTC_LAUNCH_CHECK("jacobi_diag");
+    if (want) {
+      slice_widths<<<(unsigned)std::min<int64_t>((slices_ + 3) / 4, 8192), 256, 0, s>>>(A.rowptr, n, slices_, flags + 2);
+      SRTC_LAUNCH_CHECK("slice_widths");
+      excl_scan_i64(c, flags + 2, start.as<int64_t>(), slices_, s);
+      SRTC_HIP(hipMemcpyAsync(flags + 2, start.as<int64_t>() + slices_, sizeof(int64_t), hipMemcpyDeviceToDevice, s));
+    }
+    read_to_host(c, h, flags, sizeof(int64_t) * (want ? 3 : 2), s);
+    if (h[0]) fail(SRTC_ERR_ARG, "Jacobi needs a nonzero diagonal entry in every row");
   }
-  int32_t h = 0;
-  read_to_host(c, &h, bad.p, sizeof(h), s);
-  if (h) fail(SRTC_ERR_ARG, "Jacobi needs a nonzero diagonal entry in every row");
+  // rows of much the same length: at most a quarter of padding; and room for
+  // the copy
+  const int64_t cells = h[2] * WAVE;
+  if (want && 4 * cells <= 5 * A.nnz) {
+    wide = h[1] != 0;
+    try {
+      off = Buf(c, (wide ? sizeof(int32_t) : sizeof(int16_t)) * (size_t)cells);
+      sval = Buf(c, es * (size_t)cells);
+      slices = slices_;
+    } catch (const Error &) {
+      off = Buf();
+      sval = Buf();
+    }
+  }
+  if (slices > 0) {
+    const unsigned g = (unsigned)std::min<int64_t>((slices + 3) / 4, 16384);
+    if (dt == SRTC_F64 && wide)
+      slice_fill<double, int32_t><<<g, 256, 0, s>>>(A.rowptr, A.col, (const double *)A.val, n, slices,
+                                                    start.as<int64_t>(), off.as<int32_t>(), sval.as<double>());
+    else if (dt == SRTC_F64)
+      slice_fill<double, int16_t><<<g, 256, 0, s>>>(A.rowptr, A.col, (const double *)A.val, n, slices,
+                                                    start.as<int64_t>(), off.as<int16_t>(), sval.as<double>());
+    else if (wide)
+      slice_fill<float, int32_t><<<g, 256, 0, s>>>(A.rowptr, A.col, (const float *)A.val, n, slices,
+                                                   start.as<int64_t>(), off.as<int32_t>(), sval.as<float>());
+    else
+      slice_fill<float, int16_t><<<g, 256, 0, s>>>(A.rowptr, A.col, (const float *)A.val, n, slices,
+                                                   start.as<int64_t>(), off.as<int16_t>(), sval.as<float>());
+    SRTC_LAUNCH_CHECK("slice_fill");
+  }
+  // all blocks resident at once, a multiple of the eight XCDs where there are
+  // that many
+  const int64_t threads = slices > 0 ? slices * WAVE : n * G;
+  grid = (int)std::max<int64_t>(1, std::min<int64_t>((threads + JAC_BS - 1) / JAC_BS,
+                                                     (int64_t)c->num_cus * (2048 / JAC_BS)));
+  if (grid > 8) grid -= grid % 8;
+  part = Buf(c, sizeof(double) * (size_t)(2 * grid));
 }
 
-template <class T, int G>
-static void step_typed(const JacobiPlan &pl, const void *b, const void *x_in, void *x_out, JacobiState *st,
-                       double tol2, hipStream_t s) {
-  jacobi_step<T, G><<<pl.grid, 256, 0, s>>>(pl.A.rowptr, pl.A.col, (const T *)pl.A.val, pl.dbuf.as<T>(),
-                                            (const T *)b, (const T *)x_in, (T *)x_out, pl.A.m, pl.part.as<double>(),
-                                            st);
+struct StepCall {
+  const JacobiPlan &pl;
+  const void *b, *x_in;
+  void *x_out;
+  JacobiState *st;
+  double tol2;
+  int j;
+  hipStream_t s;
+};
+
+template <class T, int G> static void step_typed(const StepCall &q) {
+  const JacobiPlan &pl = q.pl;
+  double *out = pl.part.as<double>() + (int64_t)(q.j & 1) * pl.grid;
+  const double *in = pl.part.as<double>() + (int64_t)((q.j & 1) ^ 1) * pl.grid;
+  if (pl.slices > 0 && pl.wide)
+    jacobi_slices<T, int32_t><<<pl.grid, JAC_BS, 0, q.s>>>(pl.start.as<int64_t>(), pl.off.as<int32_t>(),
+                                                           pl.sval.as<T>(), pl.dbuf.as<T>(), (const T *)q.b,
+                                                           (const T *)q.x_in, (T *)q.x_out, pl.A.m, pl.slices, out,
+                                                           in, q.j, q.st, q.tol2);
+  else if (pl.slices > 0)
+    jacobi_slices<T, int16_t><<<pl.grid, JAC_BS, 0, q.s>>>(pl.start.as<int64_t>(), pl.off.as<int16_t>(),
+                                                           pl.sval.as<T>(), pl.dbuf.as<T>(), (const T *)q.b,
+                                                           (const T *)q.x_in, (T *)q.x_out, pl.A.m, pl.slices, out,
+                                                           in, q.j, q.st, q.tol2);
+  else
+    jacobi_step<T, G><<<pl.grid, JAC_BS, 0, q.s>>>(pl.A.rowptr, pl.A.col, (const T *)pl.A.val, pl.dbuf.as<T>(),
+                                                   (const T *)q.b, (const T *)q.x_in, (T *)q.x_out, pl.A.m, out, in,
+                                                   q.j, q.st, q.tol2);
   SRTC_LAUNCH_CHECK("jacobi_step");
-  jacobi_reduce<<<1, 256, 0, s>>>(pl.part.as<double>(), pl.grid, st, tol2);
-  SRTC_LAUNCH_CHECK("jacobi_reduce");
 }
 
-template <class T>
-static void step_width(const JacobiPlan &pl, const void *b, const void *x_in, void *x_out, JacobiState *st,
-                       double tol2, hipStream_t s) {
-  switch (pl.G) {
-    case 4: step_typed<T, 4>(pl, b, x_in, x_out, st, tol2, s); break;
-    case 8: step_typed<T, 8>(pl, b, x_in, x_out, st, tol2, s); break;
-    case 16: step_typed<T, 16>(pl, b, x_in, x_out, st, tol2, s); break;
-    case 32: step_typed<T, 32>(pl, b, x_in, x_out, st, tol2, s); break;
-    default: step_typed<T, 64>(pl, b, x_in, x_out, st, tol2, s); break;
+template <class T> static void step_width(const StepCall &q) {
+  switch (q.pl.G) {
+    case 4: step_typed<T, 4>(q); break;
+    case 8: step_typed<T, 8>(q); break;
+    case 16: step_typed<T, 16>(q); break;
+    case 32: step_typed<T, 32>(q); break;
+    default: step_typed<T, 64>(q); break;
   }
 }
 
 void jacobi_step_call(const JacobiPlan &pl, const void *b, const void *x_in, void *x_out, JacobiState *st,
-                      double tol2, hipStream_t s) {
+                      double tol2, int j, bool last, hipStream_t s) {
   ProfScope ps(pl.ctx, "jacobi.step",
                (4.0 + (double)dtype_size(pl.dt)) * (double)pl.A.nnz + 8.0 * (double)(pl.A.m + 1) +
                    4.0 * (double)dtype_size(pl.dt) * (double)pl.A.m,
                s);
-  if (pl.dt == SRTC_F64) step_width<double>(pl, b, x_in, x_out, st, tol2, s);
-  else step_width<float>(pl, b, x_in, x_out, st, tol2, s);
+  const StepCall q{pl, b, x_in, x_out, st, tol2, j, s};
+  if (pl.dt == SRTC_F64) step_width<double>(q);
+  else step_width<float>(q);
+  if (last) {
+    jacobi_reduce<<<1, 256, 0, s>>>(pl.part.as<double>() + (int64_t)(j & 1) * pl.grid, pl.grid, j + 1, st, tol2);
+    SRTC_LAUNCH_CHECK("jacobi_reduce");
+  }
 }
 
 }  // namespace srtc
