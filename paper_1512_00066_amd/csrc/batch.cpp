@@ -482,6 +482,7 @@ srtc_status srtc_batch_fixpoint(srtc_ctx *ctx, srtc_semiring sr, const void *add
     };
     move(0);
     SpmmPlan pl;
+    pl.batched = true;
     pl.build(c, av, sw, s);
     int k = std::max(2, (int)steps_per_check);
     if (k % 2) k++;

@@ -1124,7 +1124,7 @@ srtc_status srtc_fixpoint_ex(srtc_ctx *ctx, srtc_semiring sr, const void *add_id
       fill_i32(reinterpret_cast<int32_t *>(rbuf[0]), nw, 0x01010101, s);  // first step: every row
     }
     auto step = [&](int t, int parity, hipStream_t st) {
-      fill_i32(chg.as<int32_t>() + t, 1, 0, st);
+      if (t == 0) fill_i32(chg.as<int32_t>(), k, 0, st);  // the flags of this run of steps
       if (delta) fill_i32(reinterpret_cast<int32_t *>(rbuf[parity ^ 1]), nw, 0, st);
       spmm_with_plan(pl, sr, dt, id, av, bufs[parity], sw, bufs[parity ^ 1], 1, 0, chg.as<int32_t>() + t,
                      nullptr, nullptr, nullptr, st, delta ? rbuf[parity] : nullptr, delta ? rbuf[parity ^ 1] : nullptr);

@@ -49,18 +49,221 @@ __global__ void items_count(const int64_t *rp, int64_t m, int64_t T, int64_t *cn
 }
 
 __global__ void items_fill(const int64_t *rp, int64_t m, int64_t T, const int64_t *ioff, const int64_t *poff,
-                           int32_t *irow, int64_t *ibeg, int64_t *iend, int64_t *ipidx) {
+                           int32_t *irow, int64_t *ibeg, int64_t *ipidx) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m;
        i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t a = rp[i], b = rp[i + 1];
+    const int64_t a = rp[i];
     const int64_t c = ioff[i + 1] - ioff[i];
+    if (i == m - 1) ibeg[ioff[m]] = rp[m];  // items are consecutive: item it ends where it + 1 begins
     for (int64_t t = 0; t < c; t++) {
       const int64_t it = ioff[i] + t;
       irow[it] = (int32_t)i;
       ibeg[it] = a + t * T;
-      iend[it] = std::min(b, a + (t + 1) * T);
       ipidx[it] = c > 1 ? poff[i] + t : -1;
     }
+  }
+}
+
+// First item of every unit: items are cut into units of about `cost` work,
+// an item counting its nonzeros plus UNIT_ITEM.  Unit w starts at the first
+// item whose preceding work reaches w cost; ufirst[nunits] = nitems.  With
+// cost = T + UNIT_ITEM and T <= 256 a unit has at most 53 items, one per lane.
+constexpr int64_t UNIT_ITEM = 5;
+constexpr int T_MAX = 256;  // most nonzeros of an item (a grain as long is never reached)
+__global__ void units_fill(const int64_t *__restrict__ ibeg, const int64_t *__restrict__ nitems_p, int64_t cost,
+                           int64_t max_units, int64_t *__restrict__ ufirst) {
+  const int64_t nitems = *nitems_p;
+  const int64_t z0 = nitems > 0 ? ibeg[0] : 0;
+  for (int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; w <= max_units;
+       w += (int64_t)gridDim.x * blockDim.x) {
+    int64_t lo = 0, hi = nitems;
+    while (lo < hi) {
+      const int64_t mid = (lo + hi) >> 1;
+      if (ibeg[mid] - z0 + mid * UNIT_ITEM < w * cost) lo = mid + 1; else hi = mid;
+    }
+    ufirst[w] = lo;
+  }
+}
+
+// A lane's value as a scalar (the same on every lane of the wave).
+template <class T> __device__ __forceinline__ T lane_value(T v, int lane) {
+  if constexpr (sizeof(T) == 8) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint64_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+    const uint64_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+    return __builtin_bit_cast(T, (hi << 32) | lo);
+  } else if constexpr (sizeof(T) == 4) {
+    return __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+  } else {
+    return (T)__builtin_amdgcn_readlane((int)v, lane);
+  }
+}
+
+// The products wider than 32 columns: one wave per (unit, chunk of 64
+// columns), one lane per column.  A unit's nonzeros are consecutive whatever
+// rows they belong to, so the wave reads 64 of A's entries at a time (one
+// load, the next 64 in flight) and takes each as a scalar, U rows of X in
+// flight; an item's sum is written when its last nonzero has been added.
+// (One wave per item kept at most four rows in flight and waited for the
+// item's bounds, its entries and X one after the other: R-MAT 18, 64 int32
+// sources, 311 us per step; 140 now.)
+// Sums run over `grain` nonzeros of an item in order, and those sums are added
+// in order.  (Reading the next U rows during the additions of these gained
+// nothing: eight waves per SIMD cover the wait.)
+// With at least eight chunks, XCD x (block id mod 8) takes chunks x, x + 8,
+// ...: its L2 then holds one 64-column slice of X at a time, not all of X
+// (16,384 x 16,384 at 1% times 1,024 fp64 columns: 2.96 -> 2.17 ms).
+// DELTA (rin given): only nonzeros of rows that changed in the previous step
+// count: an unchanged row's term is already part of the row's value.
+// Eight waves per SIMD (64 registers): the grid's blocks are then all resident.
+template <class SR, int MODE, bool ACC, bool DELTA>
+__global__ void __launch_bounds__(256, 8) spmm_units(const int64_t *__restrict__ ufirst, int32_t nunits,
+                                                  const int32_t *__restrict__ irow, const int64_t *__restrict__ ibeg,
+                                                  const int64_t *__restrict__ ipidx, const int32_t *__restrict__ cA,
+                                                  const typename SR::val_t *__restrict__ vA,
+                                                  const typename SR::val_t *__restrict__ X, int64_t s, int grain,
+                                                  void *__restrict__ Yv, typename SR::acc_t *__restrict__ P,
+                                                  typename SR::acc_t id, int32_t *changed,
+                                                  const uint8_t *__restrict__ rin, uint8_t *__restrict__ rout) {
+  using V = typename SR::val_t;
+  using A = typename SR::acc_t;
+  constexpr int U = 8, WPB = 256 / WAVE;
+  static_assert(MODE == 0 || !ACC, "one old value per entry");
+  constexpr bool OLD = MODE == 1 || ACC;
+  V *Y = reinterpret_cast<V *>(Yv);
+  const int lane = lane_id();
+  const int32_t nch = (int32_t)((s + WAVE - 1) / WAVE);
+  const int32_t wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
+  // turn t of this wave: the first own turns go to its XCD's chunks, the
+  // others to the chunks shared by all (every chunk when there are few)
+  const bool by_xcd = nch >= 8 && gridDim.x % 8 == 0;
+  const int32_t mine = by_xcd ? nunits * (nch / 8) : 0;
+  const int32_t w_own = (int32_t)(blockIdx.x / 8) * WPB + wv, st_own = (int32_t)(gridDim.x / 8) * WPB;
+  const int32_t c_all = by_xcd ? nch / 8 * 8 : 0;
+  const int32_t all = nunits * (nch - c_all);
+  const int32_t w_all = (int32_t)blockIdx.x * WPB + wv, st_all = (int32_t)gridDim.x * WPB;
+  int32_t t = w_own;
+  bool own = by_xcd;
+  if (!own) t = w_all;
+  for (;;) {
+    if (own && t >= mine) {
+      own = false;
+      t = w_all;
+    }
+    if (!own && t >= all) break;
+    const int32_t ch = t / nunits, un = t - ch * nunits;
+    const int32_t c = own ? (int32_t)(blockIdx.x % 8) + 8 * ch : c_all + ch;
+    t += own ? st_own : st_all;
+    const int64_t i0 = ufirst[un];
+    const int n = (int)(ufirst[un + 1] - i0);
+    if (n == 0) continue;
+    const int64_t col = (int64_t)c * WAVE + lane;
+    const bool on = col < s;
+    const uint32_t lo = (uint32_t)((on ? lane : 0) * sizeof(V));  // a lane's bytes into the chunk
+    const char *Xc = reinterpret_cast<const char *>(X + (int64_t)c * WAVE);
+    const uint32_t rb = (uint32_t)(s * sizeof(V));  // bytes per row (the host checks that they fit)
+    auto row_of = [&](const char *base, int32_t r) { return base + (uint64_t)(uint32_t)r * rb; };
+    // lane j: item j's row, partial slot and end
+    int32_t mrow = 0;
+    int64_t mpi = -1, mend = 0;
+    const int64_t b = ibeg[i0], e = ibeg[i0 + n];
+    if (lane < n) {
+      mrow = irow[i0 + lane];
+      mpi = ipidx[i0 + lane];
+      mend = ibeg[i0 + lane + 1] - b;
+    }
+    const int32_t len = (int32_t)(e - b);
+    const int32_t mend32 = (int32_t)mend;
+    // item `it` ends at iend; its running sum `acc` stops at ie, there or at
+    // the next multiple of grain
+    int it = 0;
+    int32_t iend = lane_value(mend32, 0), ie = min(iend, grain);
+    const char *Oc = MODE == 1 ? Xc : reinterpret_cast<const char *>(Y + (int64_t)c * WAVE);
+    V old{};
+    if (OLD) old = *(const V *)(row_of(Oc, lane_value(mrow, 0)) + lo);
+    A acc = id, tot = id;
+    // the running sum is complete; if item `it` is too, its total goes out and
+    // the next one's old value comes in
+    auto put = [&]() {
+      if (ie < iend) {
+        tot = SR::add(tot, acc);
+        acc = id;
+        ie = min(iend, ie + grain);
+        return;
+      }
+      if (grain < T_MAX) acc = SR::add(tot, acc);
+      const int32_t row = lane_value(mrow, it);
+      const int64_t pi = lane_value(mpi, it);
+      bool diff = false;
+      if (pi >= 0) {
+        if (on) P[pi * s + col] = acc;
+      } else {
+        if (OLD && !SR::absent(old, id)) acc = SR::add(acc, (A)old);
+        const V o = out_clamped<SR>(acc, id);
+        if (on) Y[(int64_t)row * s + col] = o;
+        if (MODE == 1) diff = on && o != old;
+      }
+      if (MODE == 1 && __any(diff) && lane == 0) {
+        *changed = 1;
+        if (rout) rout[row] = 1;
+      }
+      acc = id;
+      tot = id;
+      it++;
+      if (it < n) {
+        const int32_t ib = iend;
+        iend = lane_value(mend32, it);
+        ie = min(iend, ib + grain);
+        if (OLD) old = *(const V *)(row_of(Oc, lane_value(mrow, it)) + lo);
+      }
+    };
+    const int32_t *cb = cA + b;
+    const V *vb = vA + b;
+    int32_t kk = 0, kn = 0;
+    V vv{}, vn{};
+    if (lane < len) {
+      kn = cb[lane];
+      vn = vb[lane];
+    }
+    for (int32_t p = 0; p < len; p += WAVE) {
+      kk = kn;
+      vv = vn;
+      const int cnt = min(WAVE, len - p);
+      if (p + WAVE + lane < len) {
+        kn = cb[p + WAVE + lane];
+        vn = vb[p + WAVE + lane];
+      }
+      bool good = lane < cnt && !SR::absent(vv, id);
+      if (DELTA && good) good = rin[kk] != 0;
+      const uint64_t use = __ballot(good);
+      for (int q = 0; q < cnt; q += U) {
+        const uint32_t m = (uint32_t)(use >> q) & ((1u << U) - 1u);
+        // every load is issued (past the last nonzero, of a row read before):
+        // a branch around each would wait for all of them
+        V x[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+          x[u] = V{};
+          if (!DELTA || ((m >> u) & 1u)) x[u] = *(const V *)(row_of(Xc, lane_value(kk, q + u)) + lo);
+        }
+        if (m == (1u << U) - 1u && ie >= p + q + U) {
+#pragma unroll
+          for (int u = 0; u < U; u++) {
+            const A y = SR::mul(lane_value(vv, q + u), x[u]);
+            if (!SR::absent(x[u], id)) acc = SR::add(acc, y);
+          }
+        } else {
+#pragma unroll
+          for (int u = 0; u < U; u++) {
+            if (q + u < cnt)
+              while (ie <= p + q + u) put();
+            const A y = SR::mul(lane_value(vv, q + u), x[u]);
+            if (((m >> u) & 1u) && !SR::absent(x[u], id)) acc = SR::add(acc, y);
+          }
+        }
+      }
+    }
+    while (it < n) put();
   }
 }
 
@@ -68,7 +271,7 @@ __global__ void items_fill(const int64_t *rp, int64_t m, int64_t T, const int64_
 // step (self term, change flag, optional per-instance bookkeeping).
 template <class SR, int G, int MODE, bool ACC>
 __global__ void __launch_bounds__(256) spmm_items(const int32_t *__restrict__ irow, const int64_t *__restrict__ ibeg,
-                                                  const int64_t *__restrict__ iend, const int64_t *__restrict__ ipidx,
+                                                  const int64_t *__restrict__ ipidx,
                                                   const int64_t *__restrict__ nitems_p, const int32_t *__restrict__ cA,
                                                   const typename SR::val_t *__restrict__ vA,
                                                   const typename SR::val_t *__restrict__ X, int64_t s,
@@ -94,7 +297,7 @@ __global__ void __launch_bounds__(256) spmm_items(const int32_t *__restrict__ ir
     const int64_t it = nch == 1 ? u : u / nch;
     const int64_t row = irow[it];
     if (MODE == 1 && row_inst && !inst_active[row_inst[row]]) continue;
-    const int64_t b = ibeg[it], e = iend[it];
+    const int64_t b = ibeg[it], e = ibeg[it + 1];
     const int64_t pi = ipidx[it];
     {
       const int64_t c0 = (u - it * nch) * G;
@@ -175,8 +378,12 @@ __global__ void __launch_bounds__(256) spmm_items(const int32_t *__restrict__ ir
   }
 }
 
-// Rows split into several items: combine partials in item order.
-template <class SR, int G, int MODE, bool ACC>
+// Rows split into several items: combine partials in item order.  A wave
+// looks at 64 items at a time for first items of split rows (few rows are
+// split; with one item per look the search took 31 us of an R-MAT 18 step)
+// and then takes each such row, one lane per column, eight partials in
+// flight.
+template <class SR, int MODE, bool ACC>
 __global__ void __launch_bounds__(256) spmm_combine(const int32_t *__restrict__ irow, const int64_t *__restrict__ ibeg,
                                                     const int64_t *__restrict__ ipidx, const int64_t *__restrict__ nitems_p,
                                                     const int64_t *__restrict__ rp, int64_t T,
@@ -188,25 +395,40 @@ __global__ void __launch_bounds__(256) spmm_combine(const int32_t *__restrict__ 
                                                     uint8_t *__restrict__ rout) {
   using V = typename SR::val_t;
   using A = typename SR::acc_t;
+  constexpr int U = 8;
   V *Y = reinterpret_cast<V *>(Yv);
-  constexpr int PER_WAVE = WAVE / G;
   const int64_t nitems = *nitems_p;
   const int lane = lane_id();
-  const int grp = lane / G, c = lane % G;
   const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
   const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) / WAVE;
-  for (int64_t it = wave * PER_WAVE + grp; it < nitems; it += nwaves * PER_WAVE) {
-    const int64_t pi = ipidx[it];
-    const int64_t row = irow[it];
-    if (pi < 0 || ibeg[it] != rp[row]) continue;  // only the first item of a split row
-    if (MODE == 1 && row_inst && !inst_active[row_inst[row]]) continue;
-    const int64_t nz = rp[row + 1] - rp[row];
-    const int64_t cnt = (nz + T - 1) / T;
-    for (int64_t c0 = 0; c0 < s; c0 += G) {
-      const int64_t col = c0 + c;
+  // (64 items, chunk of 64 columns) per turn
+  const int64_t nch = (s + WAVE - 1) / WAVE, groups = (nitems + WAVE - 1) / WAVE;
+  for (int64_t g = wave; g < groups * nch; g += nwaves) {
+    const int64_t it = g / nch * WAVE + lane;
+    int64_t pi0 = -1;
+    int32_t row0 = 0;
+    if (it < nitems) {
+      pi0 = ipidx[it];
+      row0 = irow[it];
+      if (pi0 >= 0 && ibeg[it] != rp[row0]) pi0 = -1;  // only the first item of a split row
+    }
+    const int64_t col = g % nch * WAVE + lane;
+    for (uint64_t mk = __ballot(pi0 >= 0); mk; mk &= mk - 1) {
+      const int src = __ffsll((unsigned long long)mk) - 1;
+      const int64_t pi = lane_value(pi0, src);
+      const int64_t row = lane_value(row0, src);
+      if (MODE == 1 && row_inst && !inst_active[row_inst[row]]) continue;
       if (col >= s) continue;
+      const int64_t cnt = (rp[row + 1] - rp[row] + T - 1) / T;
       A acc = id;
-      for (int64_t t = 0; t < cnt; t++) acc = SR::add(acc, P[(pi + t) * s + col]);
+      for (int64_t t = 0; t < cnt; t += U) {
+        A x[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) x[u] = t + u < cnt ? P[(pi + t + u) * s + col] : id;
+#pragma unroll
+        for (int u = 0; u < U; u++)
+          if (t + u < cnt) acc = SR::add(acc, x[u]);
+      }
       if (MODE == 1) {
         const V old = X[row * s + col];
         if (!SR::absent(old, id)) acc = SR::add(acc, (A)old);
@@ -236,14 +458,38 @@ void run_items(const SpmmPlan &pl, const CsrView &A, const void *X, int64_t s, v
   const int64_t nch = (s + G - 1) / G;
   const unsigned grid =
       (unsigned)std::max<int64_t>(1, std::min<int64_t>(pl.max_items * nch * G / 256 + 1, pl.grid_cap));
-  spmm_items<SR, G, MODE, ACC><<<grid, 256, 0, st>>>(pl.irow, pl.ibeg, pl.iend, pl.ipidx, pl.nitems, A.col,
-                                                      (const V *)A.val, (const V *)X, s, Y, (Acc *)pl.partial, id,
-                                                      changed, row_inst, inst_active, inst_changed, rin, rout);
-  SRTC_LAUNCH_CHECK("spmm_items");
+  bool done = false;
+  if constexpr (G == WAVE) {
+    const int64_t waves = pl.nunits * nch;
+    if (pl.nunits > 0 && !row_inst && waves < (1ll << 31) && s < (1ll << 29)) {
+      unsigned gu = (unsigned)std::max<int64_t>(1, std::min<int64_t>((waves + 3) / 4, pl.grid_cap / 2));
+      if (gu > 8) gu -= gu % 8;
+      auto launch = [&](auto kern) {
+        kern<<<gu, 256, 0, st>>>(pl.ufirst, (int32_t)pl.nunits, pl.irow, pl.ibeg, pl.ipidx, A.col, (const V *)A.val,
+                                 (const V *)X, s, pl.grain, Y, (Acc *)pl.partial, id, changed, rin, rout);
+      };
+      if constexpr (MODE == 1) {
+        if (rin) launch(spmm_units<SR, MODE, ACC, true>);
+        else launch(spmm_units<SR, MODE, ACC, false>);
+      } else {
+        launch(spmm_units<SR, MODE, ACC, false>);
+      }
+      SRTC_LAUNCH_CHECK("spmm_units");
+      done = true;
+    }
+  }
+  if (!done) {
+    spmm_items<SR, G, MODE, ACC><<<grid, 256, 0, st>>>(pl.irow, pl.ibeg, pl.ipidx, pl.nitems, A.col,
+                                                        (const V *)A.val, (const V *)X, s, Y, (Acc *)pl.partial, id,
+                                                        changed, row_inst, inst_active, inst_changed, rin, rout);
+    SRTC_LAUNCH_CHECK("spmm_items");
+  }
   if (pl.may_split) {
-    spmm_combine<SR, G, MODE, ACC><<<grid, 256, 0, st>>>(pl.irow, pl.ibeg, pl.ipidx, pl.nitems, A.rowptr, pl.T,
-                                                          (const V *)X, s, Y, (const Acc *)pl.partial, id, changed,
-                                                          row_inst, inst_active, inst_changed, rout);
+    const int64_t cw = (pl.max_items + WAVE - 1) / WAVE * ((s + WAVE - 1) / WAVE);
+    const unsigned gc = (unsigned)std::max<int64_t>(1, std::min<int64_t>((cw + 3) / 4, pl.grid_cap));
+    spmm_combine<SR, MODE, ACC><<<gc, 256, 0, st>>>(pl.irow, pl.ibeg, pl.ipidx, pl.nitems, A.rowptr, pl.T,
+                                                    (const V *)X, s, Y, (const Acc *)pl.partial, id, changed, row_inst,
+                                                    inst_active, inst_changed, rout);
     SRTC_LAUNCH_CHECK("spmm_combine");
   }
 }
@@ -294,33 +540,89 @@ template <class SR> void spmm_dispatch(const SpmmCall &q) {
 }
 
 // --------------------------------------------------------------------- BFS --
+// One level: a row gathers its neighbours' frontier words and keeps the
+// sources that had not reached it.  Sixteen lanes per row, four entries each
+// in flight; the rows of a block with more than BFS_LONG entries are then
+// taken by the whole block.  Either stops once every missing source is found
+// (the hubs of a skewed graph find theirs in a few entries; with one wave per
+// row, 64 entries at a time to the end, they bound the level: R-MAT 18, 64
+// sources, 76 us per level, now 36).
+constexpr int BFS_G = 16, BFS_U = 4, BFS_LONG = 512;
 __global__ void __launch_bounds__(256) bfs_step_kernel(const int64_t *__restrict__ rp, const int32_t *__restrict__ cA,
                                                        int64_t n, const uint64_t *__restrict__ front,
                                                        uint64_t *__restrict__ visited, uint64_t *__restrict__ next,
                                                        int32_t *__restrict__ levels, int nsrc, int level,
                                                        uint64_t full, int32_t *changed) {
-  const int64_t wid = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
-  const int64_t nw = ((int64_t)gridDim.x * blockDim.x) / WAVE;
-  const int lane = lane_id();
-  for (int64_t i = wid; i < n; i += nw) {
-    const uint64_t vis = visited[i];
-    if (vis == full) {
-      if (lane == 0) next[i] = 0;
-      continue;
-    }
+  constexpr int ROWS = 256 / BFS_G;
+  __shared__ uint64_t found[ROWS], miss[ROWS];
+  __shared__ int32_t has_long;
+  const int t = threadIdx.x, g = t / BFS_G, l = t % BFS_G;
+  auto take = [&](int64_t p, int64_t e, int64_t stride) {
+    int32_t k[BFS_U];
     uint64_t acc = 0;
-    for (int64_t p = rp[i] + lane; p < rp[i + 1]; p += WAVE) acc |= front[cA[p]];
 #pragma unroll
-    for (int d = WAVE / 2; d >= 1; d >>= 1) acc |= __shfl_xor(acc, d, WAVE);
-    const uint64_t nw_bits = acc & ~vis & full;
-    if (lane == 0) {
-      next[i] = nw_bits;
-      if (nw_bits) {
-        visited[i] = vis | nw_bits;
-        *changed = 1;
+    for (int u = 0; u < BFS_U; u++) k[u] = p + u * stride < e ? cA[p + u * stride] : -1;
+#pragma unroll
+    for (int u = 0; u < BFS_U; u++)
+      if (k[u] >= 0) acc |= front[k[u]];
+    return acc;
+  };
+  for (int64_t i0 = (int64_t)blockIdx.x * ROWS; i0 < n; i0 += (int64_t)gridDim.x * ROWS) {
+    const int64_t i = i0 + g;
+    if (t == 0) has_long = 0;
+    __syncthreads();
+    int64_t a = 0, e = 0;
+    uint64_t want = 0, acc = 0;
+    if (i < n) {
+      want = full & ~visited[i];
+      if (want) {
+        a = rp[i];
+        e = rp[i + 1];
       }
     }
-    if (lane < nsrc && ((nw_bits >> lane) & 1ull)) levels[i * nsrc + lane] = level;
+    // (the lanes of a row take the same trips: its bits are combined each time)
+    for (int64_t p = a; p < min(e, a + BFS_LONG) && (acc & want) != want; p += BFS_G * BFS_U) {
+      acc |= take(p + l, e, BFS_G);
+#pragma unroll
+      for (int d = BFS_G / 2; d >= 1; d >>= 1) acc |= __shfl_xor((unsigned long long)acc, d, WAVE);
+    }
+    if (l == 0) {
+      found[g] = acc & want;
+      miss[g] = want;
+      if (e - a > BFS_LONG && (acc & want) != want) has_long = 1;
+    }
+    __syncthreads();
+    if (has_long) {  // the same on every thread
+      for (int q = 0; q < ROWS; q++) {
+        const uint64_t w = miss[q];
+        uint64_t f = found[q];
+        const int64_t ri = i0 + q;
+        if (f == w) continue;
+        const int64_t re = rp[ri + 1];
+        for (int64_t p = rp[ri] + BFS_LONG; p < re && f != w; p += 256 * BFS_U) {
+          uint64_t x = take(p + t, re, 256) & w;
+#pragma unroll
+          for (int d = WAVE / 2; d >= 1; d >>= 1) x |= __shfl_xor((unsigned long long)x, d, WAVE);
+          if (lane_id() == 0 && x) atomicOr((unsigned long long *)&found[q], (unsigned long long)x);
+          __syncthreads();
+          f = found[q];
+          __syncthreads();
+        }
+      }
+    }
+    const uint64_t fresh = found[g];
+    if (i < n) {
+      if (l == 0) {
+        next[i] = fresh;
+        if (fresh) {
+          visited[i] = (full & ~miss[g]) | fresh;
+          *changed = 1;
+        }
+      }
+      for (int q = l; q < nsrc; q += BFS_G)
+        if ((fresh >> q) & 1ull) levels[i * nsrc + q] = level;
+    }
+    __syncthreads();  // found and miss are rewritten by the next rows
   }
 }
 
@@ -332,18 +634,26 @@ void SpmmPlan::shape(Ctx *c, const CsrView &A, int64_t s_width) {
   int g = 1;
   while (g < s_width && g < WAVE) g <<= 1;
   G = g;
-  // a work unit is one item times one chunk of G columns: wider operands
-  // have more chunks per item, so shorter items keep the units short
-  T = s_width > 128 ? 64 : (G >= 64 ? 256 : (G >= 8 ? 64 : 32));
+  // an item times one chunk of G columns is the least that a wave (G = 64) or
+  // a lane group takes at a time.  Shorter items for wide operands in a batch,
+  // whose items are taken one by one; elsewhere 64 nonzeros an item would
+  // split every row of the MP3 tensor (164 nonzeros) and write and read
+  // partial sums three times the size of its result.
+  T = s_width > 128 && batched ? 64 : (G >= 64 ? T_MAX : (G >= 8 ? 64 : 32));
+  // wide operands still add up 64 nonzeros at a time
+  grain = s_width > 128 ? 64 : T_MAX;
   max_items = A.m + A.nnz / T + 1;
   // a split row of z > T nonzeros has ceil(z / T) < 2 z / T items
   max_partial = 2 * (A.nnz / T) + 1;
   may_split = true;
   grid_cap = (int64_t)c->num_cus * 16;
+  // units of one full item's work; their table fits where max_items entries do
+  nunits = G == WAVE ? (A.nnz + UNIT_ITEM * max_items) / (T + UNIT_ITEM) + 1 : 0;
+  if (nunits + 1 > max_items) nunits = 0;
 }
 
 void SpmmPlan::fill(const CsrView &A, int64_t *cnt_p, int64_t *pcnt_p, int64_t *ioff_p, int64_t *poff_p,
-                    int64_t *sums, int32_t *irow_p, int64_t *ibeg_p, int64_t *iend_p, int64_t *ipidx_p,
+                    int64_t *sums, int32_t *irow_p, int64_t *ibeg_p, int64_t *ufirst_p, int64_t *ipidx_p,
                     void *partial_p, hipStream_t st) {
   const int64_t m = A.m;
   if (m > 0) {
@@ -354,12 +664,16 @@ void SpmmPlan::fill(const CsrView &A, int64_t *cnt_p, int64_t *pcnt_p, int64_t *
   excl_scan_i64_ws(cnt_p, ioff_p, m, sums, st);
   excl_scan_i64_ws(pcnt_p, poff_p, m, sums, st);
   if (m > 0) {
-    items_fill<<<gridn(m), 256, 0, st>>>(A.rowptr, m, T, ioff_p, poff_p, irow_p, ibeg_p, iend_p, ipidx_p);
+    items_fill<<<gridn(m), 256, 0, st>>>(A.rowptr, m, T, ioff_p, poff_p, irow_p, ibeg_p, ipidx_p);
     SRTC_LAUNCH_CHECK("items_fill");
+    if (nunits > 0) {
+      units_fill<<<gridn(nunits + 1), 256, 0, st>>>(ibeg_p, ioff_p + m, T + UNIT_ITEM, nunits, ufirst_p);
+      SRTC_LAUNCH_CHECK("units_fill");
+    }
   }
   irow = irow_p;
   ibeg = ibeg_p;
-  iend = iend_p;
+  ufirst = ufirst_p;
   ipidx = ipidx_p;
   nitems = ioff_p + m;
   partial = partial_p;
@@ -376,11 +690,11 @@ void SpmmPlan::build(Ctx *c, const CsrView &A, int64_t s_width, hipStream_t st) 
   Buf sums(c, sizeof(int64_t) * (size_t)std::max<int64_t>(excl_scan_workspace(m), 1));
   irow_b = Buf(c, sizeof(int32_t) * (size_t)max_items);
   ibeg_b = Buf(c, sizeof(int64_t) * (size_t)max_items);
-  iend_b = Buf(c, sizeof(int64_t) * (size_t)max_items);
+  ufirst_b = Buf(c, sizeof(int64_t) * (size_t)max_items);
   ipidx_b = Buf(c, sizeof(int64_t) * (size_t)max_items);
   partial_b = Buf(c, (size_t)max_partial * (size_t)s_width * 8);
   fill(A, cnt.as<int64_t>(), pcnt.as<int64_t>(), ioff.as<int64_t>(), poff.as<int64_t>(), sums.as<int64_t>(),
-       irow_b.as<int32_t>(), ibeg_b.as<int64_t>(), iend_b.as<int64_t>(), ipidx_b.as<int64_t>(), partial_b.p, st);
+       irow_b.as<int32_t>(), ibeg_b.as<int64_t>(), ufirst_b.as<int64_t>(), ipidx_b.as<int64_t>(), partial_b.p, st);
 }
 
 namespace {
@@ -399,7 +713,7 @@ struct Carve {
 struct PlanParts {
   int64_t *cnt, *pcnt, *ioff, *poff, *sums;
   int32_t *irow;
-  int64_t *ibeg, *iend, *ipidx;
+  int64_t *ibeg, *ufirst, *ipidx;
   double *partial;
 };
 
@@ -413,7 +727,7 @@ int64_t carve_plan(const SpmmPlan &pl, int64_t m, int64_t s_width, char *base, P
   q.sums = cv.take<int64_t>(excl_scan_workspace(m));
   q.irow = cv.take<int32_t>(pl.max_items);
   q.ibeg = cv.take<int64_t>(pl.max_items);
-  q.iend = cv.take<int64_t>(pl.max_items);
+  q.ufirst = cv.take<int64_t>(pl.max_items);
   q.ipidx = cv.take<int64_t>(pl.max_items);
   q.partial = cv.take<double>(pl.max_partial * s_width);
   if (out) *out = q;
@@ -432,7 +746,7 @@ int64_t SpmmPlan::workspace_bytes(int64_t s_width) const {
 void SpmmPlan::build_in(const CsrView &A, int64_t s_width, void *ws, hipStream_t st) {
   PlanParts q;
   carve_plan(*this, A.m, s_width, static_cast<char *>(ws), &q);
-  fill(A, q.cnt, q.pcnt, q.ioff, q.poff, q.sums, q.irow, q.ibeg, q.iend, q.ipidx, q.partial, st);
+  fill(A, q.cnt, q.pcnt, q.ioff, q.poff, q.sums, q.irow, q.ibeg, q.ufirst, q.ipidx, q.partial, st);
 }
 
 void spmm_with_plan(const SpmmPlan &pl, int sr, int dt, IdVal id, const CsrView &A, const void *X,
@@ -498,7 +812,7 @@ void spmm_fixed(Ctx *c, int sr, int dt, IdVal id, const CsrView &A, const void *
 void bfs_step(const CsrView &A, const uint64_t *front, uint64_t *visited, uint64_t *next, int32_t *levels,
               int nsrc, int level, int32_t *changed, hipStream_t s) {
   const uint64_t full = nsrc >= 64 ? ~0ull : ((1ull << nsrc) - 1);
-  bfs_step_kernel<<<gridn(A.m * WAVE, 256, 16384), 256, 0, s>>>(A.rowptr, A.col, A.m, front, visited, next,
+  bfs_step_kernel<<<gridn(A.m * BFS_G, 256, 16384), 256, 0, s>>>(A.rowptr, A.col, A.m, front, visited, next,
                                                                  levels, nsrc, level, full, changed);
   SRTC_LAUNCH_CHECK("bfs_step");
 }

@@ -13,11 +13,14 @@ struct SpmmPlan {
   int64_t max_items = 0;
   int64_t grid_cap = 4096;
   bool may_split = true;
-  Buf cnt, pcnt, ioff, poff, irow_b, ibeg_b, iend_b, ipidx_b, partial_b;
+  int grain = 256;         // nonzeros of an item summed before they join its total
+  bool batched = false;    // rows of several instances (set before build)
+  Buf cnt, pcnt, ioff, poff, irow_b, ibeg_b, ufirst_b, ipidx_b, partial_b;
   const int32_t *irow = nullptr;
-  const int64_t *ibeg = nullptr, *iend = nullptr, *ipidx = nullptr, *nitems = nullptr;
+  const int64_t *ibeg = nullptr, *ufirst = nullptr, *ipidx = nullptr, *nitems = nullptr;
   void *partial = nullptr;
   int64_t rows = 0;         // rows of A
+  int64_t nunits = 0;       // units of items taken by one wave each (0: none)
   int64_t max_partial = 0;  // rows of s_width accumulators for split rows
   // item length, lanes per item and buffer sizes for A and s_width
   void shape(Ctx *c, const CsrView &A, int64_t s_width);
@@ -31,7 +34,7 @@ struct SpmmPlan {
 
  private:
   void fill(const CsrView &A, int64_t *cnt_p, int64_t *pcnt_p, int64_t *ioff_p, int64_t *poff_p, int64_t *sums,
-            int32_t *irow_p, int64_t *ibeg_p, int64_t *iend_p, int64_t *ipidx_p, void *partial_p, hipStream_t st);
+            int32_t *irow_p, int64_t *ibeg_p, int64_t *ufirst_p, int64_t *ipidx_p, void *partial_p, hipStream_t st);
 };
 
 // mode 0: Y = A (x) X (accumulate: Y (+)= A (x) X); mode 1: fixpoint step
