@@ -73,12 +73,43 @@ __global__ void __launch_bounds__(SCAN_BS) scan_tile_down(const In *in, int64_t 
   }
 }
 
+// The whole scan in one block and one launch, for short inputs.
+constexpr int SCAN1_BS = 1024;
+constexpr int SCAN1_IT = 16;
+constexpr int64_t SCAN1_MAX = SCAN1_BS * SCAN1_IT;
+template <class In>
+__global__ void __launch_bounds__(SCAN1_BS) scan_one_block(const In *in, int64_t n, int64_t *out) {
+  __shared__ int64_t tmp[SCAN1_BS / WAVE + 1];
+  const int per = (int)((n + SCAN1_BS - 1) / SCAN1_BS);  // at most SCAN1_IT consecutive entries per thread
+  const int64_t base = (int64_t)threadIdx.x * per;
+  int64_t v[SCAN1_IT];
+  int64_t acc = 0;
+#pragma unroll
+  for (int t = 0; t < SCAN1_IT; t++) {
+    v[t] = t < per && base + t < n ? (int64_t)in[base + t] : 0;
+    acc += v[t];
+  }
+  int64_t total;
+  int64_t pre = block_excl_scan<SCAN1_BS>(acc, tmp, &total);
+#pragma unroll
+  for (int t = 0; t < SCAN1_IT; t++) {
+    if (t < per && base + t < n) out[base + t] = pre;
+    pre += v[t];
+  }
+  if (threadIdx.x == 0) out[n] = total;
+}
+
 // The tile-sum kernel must sum the same elements the down-sweep assigns to
 // a tile; both cover [base, base + SCAN_TILE), in different orders.
 template <class In>
 void excl_scan_into(const In *in, int64_t *out, int64_t n, int64_t *sums, hipStream_t s) {
   if (n <= 0) {
     fill_i64(out, 1, 0, s);
+    return;
+  }
+  if (n <= SCAN1_MAX) {
+    scan_one_block<In><<<1, SCAN1_BS, 0, s>>>(in, n, out);
+    SRTC_LAUNCH_CHECK("scan_one_block");
     return;
   }
   const int64_t nt = (n + SCAN_TILE - 1) / SCAN_TILE;

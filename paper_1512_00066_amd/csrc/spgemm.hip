@@ -134,32 +134,44 @@ __device__ __forceinline__ int bin_of(int64_t v, const Thresholds &th) {
 constexpr int BIN_BS = 256;
 constexpr int BIN_MAXB = 1024;
 constexpr int BIN_SMALL = 4096;
-constexpr int BIN_Q = 3 * (NBIN - 1);  // per block: counts, value sums, A length sums of bins 1..
+constexpr int64_t SMALL_COLS = 16384;  // most columns of B of a small product's row bitmap
+// per block: counts of bins 1.., the sum of all values, and, for the profile's
+// byte counts, the value sums and A length sums of bins 1..
+constexpr int BIN_C = NBIN - 1;
+constexpr int BIN_Q = BIN_C + 1;
+constexpr int BIN_QS = 3 * BIN_C + 1;
+template <bool SUMS> constexpr int bin_quantities() { return SUMS ? BIN_QS : BIN_Q; }
 
-// Counts, value sums and A length sums of rows i0, i0 + stride, ... below i1,
-// reduced over each wave into acc[.][wave].
-template <int BS>
+// Those quantities over rows i0, i0 + stride, ... below i1, reduced over each
+// wave into acc[.][wave].
+template <int BS, bool SUMS>
 __device__ __forceinline__ void bin_tally(const int64_t *__restrict__ v, int64_t i0, int64_t i1, int64_t stride,
                                           const Thresholds &th, const int64_t *__restrict__ rpA,
                                           const int32_t *__restrict__ row_map, int64_t (*acc)[BS / WAVE]) {
-  int64_t q[BIN_Q];
-#pragma unroll
-  for (int b = 0; b < BIN_Q; b++) q[b] = 0;
+  constexpr int NQ = bin_quantities<SUMS>();
+  int32_t cnt[BIN_C] = {};
+  int64_t q[NQ] = {};
   for (int64_t i = i0; i < i1; i += stride) {
     const int64_t x = v[i];
     const int b = bin_of(x, th);
-    const int64_t r = row_map ? row_map[i] : i;
-    const int64_t len = rpA[r + 1] - rpA[r];
+    int64_t len = 0;
+    if (SUMS) {
+      const int64_t r = row_map ? row_map[i] : i;
+      len = rpA[r + 1] - rpA[r];
+    }
+    if (b > 0) q[BIN_C] += x;
 #pragma unroll
     for (int bb = 1; bb < NBIN; bb++) {
-      q[bb - 1] += b == bb ? 1 : 0;
-      q[NBIN - 2 + bb] += b == bb ? x : 0;
-      q[2 * (NBIN - 1) + bb - 1] += b == bb ? len : 0;
+      cnt[bb - 1] += b == bb ? 1 : 0;
+      if constexpr (SUMS) {
+        q[BIN_C + bb] += b == bb ? x : 0;
+        q[2 * BIN_C + bb] += b == bb ? len : 0;
+      }
     }
   }
 #pragma unroll
-  for (int b = 0; b < BIN_Q; b++) {
-    const int64_t x = wave_sum(q[b]);
+  for (int b = 0; b < NQ; b++) {
+    const int64_t x = b < BIN_C ? (int64_t)wave_sum(cnt[b]) : wave_sum(q[b]);
     if (lane_id() == 0) acc[b][threadIdx.x / WAVE] = x;
   }
 }
@@ -199,54 +211,57 @@ __device__ __forceinline__ void bin_place(const int64_t *__restrict__ v, int64_t
   }
 }
 
+template <bool SUMS>
 __global__ void __launch_bounds__(BIN_BS) bin_count(const int64_t *__restrict__ v, int64_t m, int64_t chunk,
                                                     Thresholds th, int64_t *__restrict__ part,
                                                     const int64_t *__restrict__ rpA,
                                                     const int32_t *__restrict__ row_map) {
-  __shared__ int64_t acc[BIN_Q][BIN_BS / WAVE];
+  constexpr int NQ = bin_quantities<SUMS>();
+  __shared__ int64_t acc[NQ][BIN_BS / WAVE];
   const int64_t i0 = (int64_t)blockIdx.x * chunk;
-  bin_tally<BIN_BS>(v, i0 + threadIdx.x, min(m, i0 + chunk), BIN_BS, th, rpA, row_map, acc);
+  bin_tally<BIN_BS, SUMS>(v, i0 + threadIdx.x, min(m, i0 + chunk), BIN_BS, th, rpA, row_map, acc);
   __syncthreads();
-  if (threadIdx.x < BIN_Q) {
+  if (threadIdx.x < NQ) {
     int64_t x = 0;
     for (int q = 0; q < BIN_BS / WAVE; q++) x += acc[threadIdx.x][q];
     part[(int64_t)threadIdx.x * BIN_MAXB + blockIdx.x] = x;
   }
 }
 
-// info's counts, starts and sums from the totals of the BIN_Q quantities.
-__device__ __forceinline__ void bin_info(const int64_t *tot, int64_t *info) {
-  int64_t run = 0, sum = 0;
+// info's counts, starts and sums from the totals of the quantities.
+template <bool SUMS> __device__ __forceinline__ void bin_info(const int64_t *tot, int64_t *info) {
+  int64_t run = 0;
   info[0] = info[NBIN] = info[SUMV] = info[SUMA] = 0;
   for (int b = 1; b < NBIN; b++) {
     info[b] = tot[b - 1];
     info[NBIN + b] = run;
     run += tot[b - 1];
-    sum += tot[NBIN - 2 + b];
-    info[SUMV + b] = tot[NBIN - 2 + b];
-    info[SUMA + b] = tot[2 * (NBIN - 1) + b - 1];
+    info[SUMV + b] = SUMS ? tot[BIN_C + b] : 0;
+    info[SUMA + b] = SUMS ? tot[2 * BIN_C + b] : 0;
   }
-  info[SUM] = sum;
+  info[SUM] = tot[BIN_C];
 }
 
 // One wave per quantity: the counts become exclusive prefixes over the
 // blocks, the sums are added up.
+template <bool SUMS>
 __global__ void __launch_bounds__(1024) bin_offsets(int64_t *__restrict__ part, int nblk, int64_t *__restrict__ info) {
-  __shared__ int64_t tot[BIN_Q];
+  constexpr int NQ = bin_quantities<SUMS>();
+  __shared__ int64_t tot[NQ];
   const int l = lane_id();
-  for (int q = threadIdx.x / WAVE; q < BIN_Q; q += 1024 / WAVE) {
+  for (int q = threadIdx.x / WAVE; q < NQ; q += 1024 / WAVE) {
     int64_t run = 0;
     for (int b0 = 0; b0 < nblk; b0 += WAVE) {
       const int b = b0 + l;
       const int64_t x = b < nblk ? part[(int64_t)q * BIN_MAXB + b] : 0;
       const int64_t inc = wave_incl_scan(x);
-      if (q < NBIN - 1 && b < nblk) part[(int64_t)q * BIN_MAXB + b] = run + inc - x;
+      if (q < BIN_C && b < nblk) part[(int64_t)q * BIN_MAXB + b] = run + inc - x;
       run += lane63(inc);
     }
     if (l == 0) tot[q] = run;
   }
   __syncthreads();
-  if (threadIdx.x == 0) bin_info(tot, info);
+  if (threadIdx.x == 0) bin_info<SUMS>(tot, info);
 }
 
 __global__ void __launch_bounds__(BIN_BS) bin_scatter(const int64_t *__restrict__ v, int64_t m, int64_t chunk,
@@ -262,23 +277,26 @@ __global__ void __launch_bounds__(BIN_BS) bin_scatter(const int64_t *__restrict_
   bin_place<BIN_BS>(v, i0, min(m, i0 + chunk), th, row_map, base, cnt, lists);
 }
 
-__global__ void __launch_bounds__(1024) bin_small(const int64_t *__restrict__ v, int64_t m, Thresholds th,
-                                                  const int64_t *__restrict__ rpA, const int32_t *__restrict__ row_map,
-                                                  int64_t *__restrict__ info, int32_t *__restrict__ lists) {
-  __shared__ int64_t acc[BIN_Q][1024 / WAVE];
-  __shared__ int64_t tot[BIN_Q];
+// All of it by one block of 1,024 threads.
+template <bool SUMS>
+__device__ __forceinline__ void bin_all(const int64_t *__restrict__ v, int64_t m, const Thresholds &th,
+                                        const int64_t *__restrict__ rpA, const int32_t *__restrict__ row_map,
+                                        int64_t *__restrict__ info, int32_t *__restrict__ lists) {
+  constexpr int NQ = bin_quantities<SUMS>();
+  __shared__ int64_t acc[NQ][1024 / WAVE];
+  __shared__ int64_t tot[NQ];
   __shared__ int64_t base[NBIN];
   __shared__ int32_t cnt[1024 / WAVE][NBIN];
-  bin_tally<1024>(v, threadIdx.x, m, 1024, th, rpA, row_map, acc);
+  bin_tally<1024, SUMS>(v, threadIdx.x, m, 1024, th, rpA, row_map, acc);
   __syncthreads();
-  if (threadIdx.x < BIN_Q) {
+  if (threadIdx.x < NQ) {
     int64_t x = 0;
     for (int q = 0; q < 1024 / WAVE; q++) x += acc[threadIdx.x][q];
     tot[threadIdx.x] = x;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    bin_info(tot, info);
+    bin_info<SUMS>(tot, info);
     int64_t run = 0;
     for (int b = 1; b < NBIN; b++) {
       base[b] = run;
@@ -287,6 +305,44 @@ __global__ void __launch_bounds__(1024) bin_small(const int64_t *__restrict__ v,
   }
   __syncthreads();
   bin_place<1024>(v, 0, m, th, row_map, base, cnt, lists);
+}
+template <bool SUMS>
+__global__ void __launch_bounds__(1024) bin_small(const int64_t *__restrict__ v, int64_t m, Thresholds th,
+                                                  const int64_t *__restrict__ rpA, const int32_t *__restrict__ row_map,
+                                                  int64_t *__restrict__ info, int32_t *__restrict__ lists) {
+  bin_all<SUMS>(v, m, th, rpA, row_map, info, lists);
+}
+
+// The numeric layout of up to BIN_SMALL rows in one launch: C's row pointers
+// (the exclusive scan of the rows' output counts), the bins and their lists,
+// and a copy of the output size and the bin table for the host, written to
+// its pinned memory (read after the stream has been waited for).
+template <bool SUMS>
+__global__ void __launch_bounds__(1024) small_layout(const int64_t *__restrict__ v, int64_t m, Thresholds th,
+                                                     const int64_t *__restrict__ rpA, int64_t *__restrict__ rowptr,
+                                                     int64_t *__restrict__ info, int32_t *__restrict__ lists,
+                                                     int64_t *__restrict__ host) {
+  constexpr int PER = BIN_SMALL / 1024;
+  __shared__ int64_t tmp[1024 / WAVE + 1];
+  const int64_t i0 = (int64_t)threadIdx.x * PER;
+  int64_t x[PER], sum = 0;
+#pragma unroll
+  for (int u = 0; u < PER; u++) {
+    x[u] = i0 + u < m ? v[i0 + u] : 0;
+    sum += x[u];
+  }
+  int64_t total;
+  int64_t pre = block_excl_scan<1024>(sum, tmp, &total);
+#pragma unroll
+  for (int u = 0; u < PER; u++) {
+    if (i0 + u < m) rowptr[i0 + u] = pre;
+    pre += x[u];
+  }
+  if (threadIdx.x == 0) rowptr[m] = total;
+  bin_all<SUMS>(v, m, th, rpA, nullptr, info, lists);
+  __syncthreads();
+  if (threadIdx.x == 0) host[0] = total;
+  if (threadIdx.x < INFO) host[1 + threadIdx.x] = info[threadIdx.x];
 }
 
 // Sort key putting heavy rows first: descending in a 16-bit code of the
@@ -749,6 +805,31 @@ __global__ void __launch_bounds__(BS) sym_bitmap(const int32_t *__restrict__ lis
     const int64_t tot = block_sum<BS>(mine, red);
     if (threadIdx.x == 0) nnz_row[i] = tot;
    }
+  }
+}
+
+// Output counts of every row of a small product, one block per row, in one
+// launch: a bitmap over all of B's columns (dynamic LDS, `wwords` words).  No
+// row products, no binning and no host read come before it.
+template <int BS>
+__global__ void __launch_bounds__(BS) sym_small(const int64_t *__restrict__ rpA, const int32_t *__restrict__ cA,
+                                                const int64_t *__restrict__ rpB, const int32_t *__restrict__ cB,
+                                                int64_t m, int32_t wwords, int64_t *__restrict__ nnz_row) {
+  extern __shared__ uint32_t bits[];
+  __shared__ Chunk<BS, uint8_t> L;
+  __shared__ int32_t red[BS / WAVE + 1];
+  for (int64_t i = blockIdx.x; i < m; i += gridDim.x) {
+    for (int s = threadIdx.x; s < wwords; s += BS) bits[s] = 0;
+    __syncthreads();
+    for_products<BS, false, uint8_t>(rpA, cA, (const uint8_t *)nullptr, rpB, cB, (const uint8_t *)nullptr, i, nullptr,
+                                     0, 0, 1, L, [&](int32_t j, uint8_t, uint8_t) {
+      if ((uint32_t)j < (uint32_t)wwords * 32) atomicOr(&bits[j >> 5], 1u << (j & 31));
+    });
+    __syncthreads();
+    int32_t mine = 0;
+    for (int s = threadIdx.x; s < wwords; s += BS) mine += __popc(bits[s]);
+    const int32_t tot = block_sum<BS>(mine, red);
+    if (threadIdx.x == 0) nnz_row[i] = tot;
   }
 }
 
@@ -1731,22 +1812,28 @@ inline unsigned gridn(int64_t n, int bs = 256, int64_t cap = 65536) {
 // entries) and the rows listed by bin.
 void bin_rows(Ctx *c, const int64_t *v, int64_t nsel, const Thresholds &th, const int64_t *rpA,
               const int32_t *row_map, int64_t *info, int32_t *list, hipStream_t s) {
-  if (nsel <= BIN_SMALL) {
-    bin_small<<<1, 1024, 0, s>>>(v, nsel, th, rpA, row_map, info, list);
-    SRTC_LAUNCH_CHECK("bin_small");
-    return;
-  }
-  // whole tiles per block, at most BIN_MAXB blocks
-  const int64_t tiles = (nsel + BIN_BS - 1) / BIN_BS;
-  const int64_t chunk = (tiles + BIN_MAXB - 1) / BIN_MAXB * BIN_BS;
-  const int nblk = (int)((nsel + chunk - 1) / chunk);
-  Buf part(c, sizeof(int64_t) * (size_t)(BIN_Q * BIN_MAXB));
-  bin_count<<<nblk, BIN_BS, 0, s>>>(v, nsel, chunk, th, part.as<int64_t>(), rpA, row_map);
-  SRTC_LAUNCH_CHECK("bin_count");
-  bin_offsets<<<1, 1024, 0, s>>>(part.as<int64_t>(), nblk, info);
-  SRTC_LAUNCH_CHECK("bin_offsets");
-  bin_scatter<<<nblk, BIN_BS, 0, s>>>(v, nsel, chunk, th, part.as<int64_t>(), info, list, row_map);
-  SRTC_LAUNCH_CHECK("bin_scatter");
+  auto run = [&](auto sums) {
+    constexpr bool SUMS = decltype(sums)::value;
+    if (nsel <= BIN_SMALL) {
+      bin_small<SUMS><<<1, 1024, 0, s>>>(v, nsel, th, rpA, row_map, info, list);
+      SRTC_LAUNCH_CHECK("bin_small");
+      return;
+    }
+    // whole tiles per block, at most BIN_MAXB blocks
+    const int64_t tiles = (nsel + BIN_BS - 1) / BIN_BS;
+    const int64_t chunk = (tiles + BIN_MAXB - 1) / BIN_MAXB * BIN_BS;
+    const int nblk = (int)((nsel + chunk - 1) / chunk);
+    Buf part(c, sizeof(int64_t) * (size_t)(BIN_QS * BIN_MAXB));
+    bin_count<SUMS><<<nblk, BIN_BS, 0, s>>>(v, nsel, chunk, th, part.as<int64_t>(), rpA, row_map);
+    SRTC_LAUNCH_CHECK("bin_count");
+    bin_offsets<SUMS><<<1, 1024, 0, s>>>(part.as<int64_t>(), nblk, info);
+    SRTC_LAUNCH_CHECK("bin_offsets");
+    bin_scatter<<<nblk, BIN_BS, 0, s>>>(v, nsel, chunk, th, part.as<int64_t>(), info, list, row_map);
+    SRTC_LAUNCH_CHECK("bin_scatter");
+  };
+  // the per-bin sums are for the profile's byte counts alone
+  if (c->profiling) run(std::true_type{});
+  else run(std::false_type{});
 }
 
 // Order the rows of one bin heaviest first (by their product counts), so the
@@ -2009,6 +2096,20 @@ template <class SR> Schedule budgeted(const Ctx *c, int id) {
   return S;
 }
 
+// Numeric bins: 1: <= t_tiny outputs (64-slot hash), 2: <= t_small (512), 3:
+// <= 512 (1024), 4: <= 1024 (2048), 5: <= t_mid (4096), 6: <= t_big (8192),
+// 7: dense windows.
+Thresholds numeric_edges(const Schedule &S) {
+  Thresholds th2{};
+  th2.t[0] = S.t_tiny;
+  th2.t[1] = std::max(S.t_small, th2.t[0]);
+  th2.t[2] = std::max(std::min<int64_t>(512, S.t_mid), th2.t[1]);
+  th2.t[3] = std::max(std::min<int64_t>(1024, S.t_mid), th2.t[2]);
+  th2.t[4] = std::max(S.t_mid, th2.t[3]);
+  th2.t[5] = std::max(S.t_big, th2.t[4]);
+  return th2;
+}
+
 // Numeric binning of one group of rows (row ids in g.row_map, or every row
 // when it is null) under schedule g.sched: rows go to bins by their exact
 // output counts (info2: INFO entries; list: the group's rows by bin).  Nothing is read back here.
@@ -2026,13 +2127,7 @@ void numeric_bin(Ctx *c, const CsrView &Am, const int64_t *nnz_row, const RowGro
     SRTC_LAUNCH_CHECK("gather_i64");
     vsel = vbuf->as<int64_t>();
   }
-  Thresholds th2{};
-  th2.t[0] = S.t_tiny;
-  th2.t[1] = std::max(S.t_small, th2.t[0]);
-  th2.t[2] = std::max(std::min<int64_t>(512, S.t_mid), th2.t[1]);
-  th2.t[3] = std::max(std::min<int64_t>(1024, S.t_mid), th2.t[2]);
-  th2.t[4] = std::max(S.t_mid, th2.t[3]);
-  th2.t[5] = std::max(S.t_big, th2.t[4]);
+  const Thresholds th2 = numeric_edges(S);
   bin_rows(c, vsel, nsel, th2, Am.rowptr, g.row_map, info2, list, s);
 }
 
@@ -2051,7 +2146,7 @@ void numeric_launch(Ctx *c, typename SR::acc_t id, const CsrView &Am, const CsrV
   const Schedule S = budgeted<SR>(c, g.sched);
   const int64_t n = Bm.n;
   Launch L{c, s};
-  heavy_first(c, lst + hinfo2[NBIN + HEAVY], hinfo2[HEAVY], w, s);
+  if (w) heavy_first(c, lst + hinfo2[NBIN + HEAVY], hinfo2[HEAVY], w, s);  // (a small product has no order)
   c->tracef("spgemm: schedule %d, nnz %lld; numeric bins %lld %lld %lld %lld %lld %lld %lld", g.sched,
             (long long)hinfo2[SUM], (long long)hinfo2[1], (long long)hinfo2[2], (long long)hinfo2[3],
             (long long)hinfo2[4], (long long)hinfo2[5], (long long)hinfo2[6], (long long)hinfo2[7]);
@@ -2170,70 +2265,97 @@ void spgemm_groups(Ctx *c, IdVal idv, const CsrView &Am, const CsrView &Bm, cons
     return;
   }
   const int G = (int)groups.size();
-  // flags: [0] a row came out short, [1] numeric hash invariant broken,
-  // int64 at byte 8: symbolic hash invariant broken
-  Buf flag(c, 64);
-  fill_i32(flag.as<int32_t>(), 4, 0, s);
-  int32_t *fl = flag.as<int32_t>();
-  int64_t *sym_err = reinterpret_cast<int64_t *>(flag.as<char>() + 8);
-  // 1-3. products per row, symbolic bins, symbolic pass (per group)
-  Buf w(c, sizeof(int64_t) * (size_t)m);
-  {
-    ProfScope ps(c, "spgemm.row_products", 16.0 * (m + 1) + 4.0 * Am.nnz + 8.0 * (Bm.m + 1), s);
-    row_products(Am, Bm, w.as<int64_t>(), s);
-  }
-  Buf nnz_row(c, sizeof(int64_t) * (size_t)m);
-  fill_i64(nnz_row.as<int64_t>(), m, 0, s);
   c->tracef("spgemm: %lld x %lld (nnz %lld) times %lld x %lld (nnz %lld), %d group(s), schedule %d", (long long)m,
             (long long)Am.n, (long long)Am.nnz, (long long)Bm.m, (long long)Bm.n, (long long)Bm.nnz, G,
             G ? groups[0].sched : -1);
-  // per group: a bin table (symbolic, then reused for the numeric pass) and
-  // a row list; slot 0 of `tables` receives the output size
-  // the row counters of both passes follow the tables
-  Buf tables(c, sizeof(int64_t) * (size_t)(1 + G * (INFO + 2 * NBIN * BIN_CTRS)));
-  int64_t *tab = tables.as<int64_t>();
-  int64_t *ctrs = tab + 1 + (int64_t)G * INFO;
-  fill_i64(tab, 1 + (int64_t)G * (INFO + 2 * NBIN * BIN_CTRS), 0, s);
+  // One scratch block, its first part cleared by one fill:
+  //   flags: [0] a row came out short, [1] numeric hash invariant broken,
+  //     int64 at byte 8: symbolic hash invariant broken
+  //   tab: the output size, then per group a bin table (symbolic, reused for
+  //     the numeric pass)
+  //   ctrs: the row counters of both passes
+  //   kept, nnz_row: per row (rows in no bin, without outputs, keep 0)
+  //   w: products per row; then each group's row list
+  const int64_t ntab = 1 + (int64_t)G * INFO, nctr = (int64_t)2 * G * NBIN * BIN_CTRS;
+  std::vector<int64_t> loff(G + 1, 0);  // row lists, in int32 from the start of the first
+  for (int q = 0; q < G; q++) loff[q + 1] = loff[q] + (groups[q].row_map ? groups[q].nsel : m);
+  const int64_t nclear = 8 + ntab + nctr + 2 * m;
+  Buf ws(c, sizeof(int64_t) * (size_t)(nclear + m) + sizeof(int32_t) * (size_t)(loff[G] + 1));
+  int64_t *const w0 = ws.as<int64_t>();
+  int32_t *fl = ws.as<int32_t>();
+  int64_t *sym_err = w0 + 1;
+  int64_t *tab = w0 + 8;
+  int64_t *ctrs = tab + ntab;
+  int64_t *kp = ctrs + nctr;
+  int64_t *nnz_row = kp + m;
+  int64_t *w = nnz_row + m;
+  auto list_of = [&](int q) { return reinterpret_cast<int32_t *>(w + m) + loff[q]; };
   auto pass_ctrs = [&](int q, int pass) { return ctrs + (int64_t)(2 * q + pass) * NBIN * BIN_CTRS; };
-  std::vector<Buf> lists(G);
-  int64_t products = 0;
-  for (int q = 0; q < G; q++) {
-    const RowGroup &g = groups[q];
-    const int64_t nsel = g.row_map ? g.nsel : m;
-    lists[q] = Buf(c, sizeof(int32_t) * (size_t)std::max<int64_t>(nsel, 1));
-    if (nsel == 0) continue;
-    int64_t *info1 = tab + 1 + (int64_t)q * INFO;
-    products += run_symbolic(L, budgeted<SR>(c, g.sched), Am, Bm, w.as<int64_t>(), g.row_map, nsel, info1,
-                             lists[q].as<int32_t>(), nnz_row.as<int64_t>(), sym_err, pass_ctrs(q, 0));
+  fill_i64(w0, nclear, 0, s);
+  std::vector<int64_t> htab((size_t)ntab);
+  // A small product (its rows fit one block's binning, B's columns a bitmap
+  // of 2 KB) is launches and host reads, not work: output counts of all rows
+  // in one launch, then row pointers and bins in one, and one read.  Median
+  // call with the passes below and so, R-MAT in fp64, ER in int32: ER n = 100
+  // d = 4 98 and 68 us; n = 1,000 d = 8 113 and 81 us; n = 4,000 d = 64 446
+  // and 311 us; R-MAT 10 d = 16 239 and 144 us, R-MAT 12 391 and 298 us.
+  const bool small = G == 1 && !groups[0].row_map && m <= BIN_SMALL && Bm.n <= SMALL_COLS && c->lds_budget >= LDS_BYTES;
+  if (small) {
+    const int32_t ww = (int32_t)((Bm.n + 31) / 32);
+    {
+      ProfScope ps(c, "spgemm.symbolic.small", 24.0 * m + 4.0 * Am.nnz + 4.0 * Bm.nnz + 8.0 * (Bm.m + 1), s);
+      sym_small<256><<<(unsigned)m, 256, (size_t)ww * 4, s>>>(Am.rowptr, Am.col, Bm.rowptr, Bm.col, m, ww, nnz_row);
+      SRTC_LAUNCH_CHECK("sym_small");
+    }
+    int64_t *host = (int64_t *)c->host_scratch(sizeof(int64_t) * (size_t)ntab);
+    const Thresholds th = numeric_edges(budgeted<SR>(c, groups[0].sched));
+    if (c->profiling)
+      small_layout<true><<<1, 1024, 0, s>>>(nnz_row, m, th, Am.rowptr, out->rowptr.as<int64_t>(), tab + 1, list_of(0),
+                                            host);
+    else
+      small_layout<false><<<1, 1024, 0, s>>>(nnz_row, m, th, Am.rowptr, out->rowptr.as<int64_t>(), tab + 1, list_of(0),
+                                             host);
+    SRTC_LAUNCH_CHECK("small_layout");
+    SRTC_HIP(hipStreamSynchronize(s));
+    memcpy(htab.data(), host, sizeof(int64_t) * htab.size());
+  } else {
+    // 1-3. products per row, symbolic bins, symbolic pass (per group)
+    {
+      ProfScope ps(c, "spgemm.row_products", 16.0 * (m + 1) + 4.0 * Am.nnz + 8.0 * (Bm.m + 1), s);
+      row_products(Am, Bm, w, s);
+    }
+    int64_t products = 0;
+    for (int q = 0; q < G; q++) {
+      const RowGroup &g = groups[q];
+      const int64_t nsel = g.row_map ? g.nsel : m;
+      if (nsel == 0) continue;
+      products += run_symbolic(L, budgeted<SR>(c, g.sched), Am, Bm, w, g.row_map, nsel, tab + 1 + (int64_t)q * INFO,
+                               list_of(q), nnz_row, sym_err, pass_ctrs(q, 0));
+    }
+    c->tracef("spgemm: symbolic launched, %lld products", (long long)products);
+    if (st) st->products = products;
+    // 4. rowptr of C, numeric bins; one host read sizes C and every bin
+    excl_scan_i64(c, nnz_row, out->rowptr.as<int64_t>(), m, s);
+    std::vector<Buf> vbufs(G);
+    for (int q = 0; q < G; q++)
+      numeric_bin<SR>(c, Am, nnz_row, groups[q], tab + 1 + (int64_t)q * INFO, list_of(q), &vbufs[q], s);
+    copy_i64<<<1, 64, 0, s>>>(out->rowptr.as<int64_t>() + m, tab);
+    read_to_host(c, htab.data(), tab, sizeof(int64_t) * htab.size(), s);
   }
-  c->tracef("spgemm: symbolic launched, %lld products", (long long)products);
-  if (st) st->products = products;
-  // 4. rowptr of C, numeric bins; one host read sizes C and every bin
-  excl_scan_i64(c, nnz_row.as<int64_t>(), out->rowptr.as<int64_t>(), m, s);
-  std::vector<Buf> vbufs(G);
-  for (int q = 0; q < G; q++)
-    numeric_bin<SR>(c, Am, nnz_row.as<int64_t>(), groups[q], tab + 1 + (int64_t)q * INFO, lists[q].as<int32_t>(),
-                    &vbufs[q], s);
-  copy_i64<<<1, 64, 0, s>>>(out->rowptr.as<int64_t>() + m, tab);
-  std::vector<int64_t> htab(1 + (size_t)G * INFO);
-  read_to_host(c, htab.data(), tab, sizeof(int64_t) * htab.size(), s);
   const int64_t total = htab[0];
   c->tracef("spgemm: nnz(C) = %lld", (long long)total);
   if (st) st->nnz = total;
   // 5. numeric, group by group into the one output
   Buf col(c, sizeof(int32_t) * (size_t)std::max<int64_t>(total, 1), out->kind);
   Buf val(c, es * (size_t)std::max<int64_t>(total, 1), out->kind);
-  Buf kept(c, sizeof(int64_t) * (size_t)m);
-  fill_i64(kept.as<int64_t>(), m, 0, s);  // rows in no bin (no outputs) keep 0
   const int64_t *rpC = out->rowptr.as<int64_t>();
   int32_t *cC = col.as<int32_t>();
   V *vC = val.as<V>();
-  int64_t *kp = kept.as<int64_t>();
   if (total > 0)
     for (int q = 0; q < G; q++)
-      numeric_launch<SR>(c, id, Am, Bm, w.as<int64_t>(), groups[q], htab.data() + 1 + (size_t)q * INFO,
-                         tab + 1 + (int64_t)q * INFO, lists[q].as<int32_t>(), sorted,
-                         OutRows{rpC, nnz_row.as<int64_t>(), 0}, cC, vC, kp, fl, pass_ctrs(q, 1), st, s);
+      numeric_launch<SR>(c, id, Am, Bm, small ? nullptr : w, groups[q], htab.data() + 1 + (size_t)q * INFO,
+                         tab + 1 + (int64_t)q * INFO, list_of(q), sorted, OutRows{rpC, nnz_row, 0}, cC, vC, kp, fl,
+                         pass_ctrs(q, 1), st, s);
   // 6. compaction when identity results were dropped
   int32_t flags_h[4] = {0, 0, 0, 0};
   read_to_host(c, flags_h, fl, sizeof(flags_h), s);
