@@ -2061,6 +2061,12 @@ template <class SR, int BS, int W> constexpr int num_dense_lds() {
          (int)sizeof(Chunk<BS, typename SR::val_t>) + (RankWin<SR, BS, W>::OK ? NWPW * 8 : 8) + 64;
 }
 
+// Threads of the 8192-slot hash kernel: 512 where two such blocks fit a CU,
+// 1,024 where only one does (ER n = 20,000, d = 64, whole call: int32, 75 KB
+// of LDS a block of 512, 1,024 threads 1,788, 512 threads 1,515 us; fp64, 110
+// KB, 1,844 and 2,207 us).
+template <class SR> constexpr int hash8k_threads() { return 2 * num_hash_lds<SR, 512>(8192) <= LDS_BYTES ? 512 : 1024; }
+
 // A schedule as run under the context's LDS budget (SRTC_LDS_BUDGET): a
 // hash bin whose kernel would need more LDS per block is merged into the
 // next larger one, up to the dense windows (a row's result does not depend
@@ -2077,8 +2083,8 @@ template <class SR> Schedule budgeted(const Ctx *c, int id) {
   if (sym_hash_lds<64>(64) > B) S.sym_hash_max = 0;
   // numeric bins, largest first: a dropped bin's rows fall through to the
   // dense windows (thresholds are applied as running maxima)
-  if (num_hash_lds<SR, 1024>(8192) > B) S.t_big = S.t_mid;
-  if (num_hash_lds<SR, 256>(4096) > B) S.t_mid = S.t_big = S.t_small;
+  if (num_hash_lds<SR, hash8k_threads<SR>()>(8192) > B) S.t_big = S.t_mid;
+  if (num_hash_lds<SR, 512>(4096) > B) S.t_mid = S.t_big = S.t_small;
   if (num_hash_lds<SR, 128>(512) > B) S.t_small = S.t_mid = S.t_big = S.t_tiny;
   if (num_hash_lds<SR, 64>(64) > B) S.t_tiny = S.t_small = S.t_mid = S.t_big = 0;
   constexpr int W0 = (int)dense_width<SR>(0), W1 = (int)dense_width<SR>(1), W2 = (int)dense_width<SR>(2);
@@ -2153,6 +2159,7 @@ void numeric_launch(Ctx *c, typename SR::acc_t id, const CsrView &Am, const CsrV
   if (st) st->dense_rows += hinfo2[HEAVY];
   auto ctr2 = [&](int b) { return ctrs + b * BIN_CTRS; };
   using NL = NumLaunch<SR>;
+  constexpr int BS8 = hash8k_threads<SR>();
   // algorithmic bytes of a numeric bin: its C entries written, its A rows
   // read, B read once
   const double vb = (double)sizeof(V);
@@ -2182,8 +2189,9 @@ void numeric_launch(Ctx *c, typename SR::acc_t id, const CsrView &Am, const CsrV
     // kernels wait on dependent LDS and memory accesses, and three to four
     // times as many of their rows fit a CU as of the 4096-slot table's (20
     // ER instances batched: 3,866 -> 1,762 us; R-MAT 18 fp64: 2,406 -> 728
-    // us in all); the 8192-slot table fills the LDS with one block, so it
-    // takes 1024 threads (R-MAT 18 fp64: 512 threads 2,010, 1,024 1,535 us)
+    // us in all); two blocks of the 4096-slot table fit a CU in fp64,
+    // so it takes 512 threads (ER n = 20,000, d = 40 fp64: 256 threads 1,235
+    // us, 512 964; int32, three to a CU, 847 and 816)
     } else if (b == 3) {
       if (sorted) NL::template hash<128, 1024, 0>(L, hinfo2[3], lst, info2, 3, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(3));
       else NL::template hash<128, 1024, 2>(L, hinfo2[3], lst, info2, 3, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(3));
@@ -2191,11 +2199,11 @@ void numeric_launch(Ctx *c, typename SR::acc_t id, const CsrView &Am, const CsrV
       if (sorted) NL::template hash<256, 2048, 0>(L, hinfo2[4], lst, info2, 4, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(4));
       else NL::template hash<256, 2048, 2>(L, hinfo2[4], lst, info2, 4, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(4));
     } else if (b == 5) {
-      if (sorted) NL::template hash<256, 4096, 0>(L, hinfo2[5], lst, info2, 5, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(5));
-      else NL::template hash<256, 4096, 2>(L, hinfo2[5], lst, info2, 5, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(5));
+      if (sorted) NL::template hash<512, 4096, 0>(L, hinfo2[5], lst, info2, 5, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(5));
+      else NL::template hash<512, 4096, 2>(L, hinfo2[5], lst, info2, 5, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(5));
     } else if (b == 6) {
-      if (sorted) NL::template hash<1024, 8192, 0>(L, hinfo2[6], lst, info2, 6, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(6));
-      else NL::template hash<1024, 8192, 2>(L, hinfo2[6], lst, info2, 6, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(6));
+      if (sorted) NL::template hash<BS8, 8192, 0>(L, hinfo2[6], lst, info2, 6, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(6));
+      else NL::template hash<BS8, 8192, 2>(L, hinfo2[6], lst, info2, 6, Am, Bm, rpC, cC, vC, id, kp, fl, ctr2(6));
     }
   }
   if (hinfo2[HEAVY] > 0) {
