@@ -273,7 +273,6 @@ void prepare_batch(Ctx *c, srtc_semiring sr, const void *add_id, int32_t ninst, 
     if (t.format == SRTC_CSR && idx == rows + cols) return view_of(t);
     std::vector<int> rm{(int)idx.find(rows[0])}, cm{(int)idx.find(cols[0])};
     const int64_t nr = t.dims[rm[0]], nc = t.dims[cm[0]];
-    Buf keys(c, sizeof(int64_t) * (size_t)std::max<int64_t>(t.nnz, 1));
     const int64_t *src = t.coo_keys;
     Buf tmp;
     if (t.format == SRTC_CSR) {
@@ -281,10 +280,10 @@ void prepare_batch(Ctx *c, srtc_semiring sr, const void *add_id, int32_t ninst, 
       csr_to_keys(view_of(t), tmp.as<int64_t>(), s);
       src = tmp.as<int64_t>();
     }
-    remap_keys(c, src, t.nnz, 2, t.dims, 1, rm.data(), 1, cm.data(), keys.as<int64_t>(), s);
+    const KeyMap km = key_map(2, t.dims, 1, rm.data(), 1, cm.data());
     owned.emplace_back();
     owned.back().kind = SCRATCH;
-    fold_keys_to_csr(c, sr, dt, id, keys.as<int64_t>(), t.vals, t.nnz, nr, nc, &owned.back(), s);
+    fold_keys_to_csr(c, sr, dt, id, &km, src, t.vals, t.nnz, nr, nc, &owned.back(), s);
     const CsrOut &f = owned.back();
     return CsrView{f.m, f.n, f.nnz, f.rowptr.as<int64_t>(), f.col.as<int32_t>(), f.val.p};
   };

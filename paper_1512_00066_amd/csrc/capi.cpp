@@ -298,7 +298,6 @@ void fold_sparse(Ctx *c, int sr, IdVal id, const srtc_tensor *t, const std::stri
   for (int q : rm) nr *= t->dims[q];
   for (int q : cm) nc *= t->dims[q];
   const int64_t nnz = t->nnz;
-  Buf keys(c, sizeof(int64_t) * (size_t)std::max<int64_t>(nnz, 1));
   const int64_t *src_keys = t->coo_keys;
   Buf tmp;
   if (t->format == SRTC_CSR) {
@@ -307,10 +306,9 @@ void fold_sparse(Ctx *c, int sr, IdVal id, const srtc_tensor *t, const std::stri
     csr_to_keys(v, tmp.as<int64_t>(), s);
     src_keys = tmp.as<int64_t>();
   }
-  remap_keys(c, src_keys, nnz, t->order, t->dims, (int)rm.size(), rm.data(), (int)cm.size(), cm.data(),
-             keys.as<int64_t>(), s);
+  const KeyMap km = key_map(t->order, t->dims, (int)rm.size(), rm.data(), (int)cm.size(), cm.data());
   if (!force) f->own.kind = SCRATCH;
-  fold_keys_to_csr(c, sr, t->dtype, id, keys.as<int64_t>(), t->vals, nnz, nr, nc, &f->own, s);
+  fold_keys_to_csr(c, sr, t->dtype, id, &km, src_keys, t->vals, nnz, nr, nc, &f->own, s);
   f->owned = true;
   f->view.m = f->own.m;
   f->view.n = f->own.n;
@@ -804,15 +802,14 @@ srtc_status srtc_contract(srtc_ctx *ctx, srtc_semiring sr, const void *add_id, i
         for (size_t q = 0; q < cidx.size(); q++)
           (q < crow.size() ? rm : cm).push_back((int)from.find(cidx[q]));
         CsrView tv{t.m, t.n, t.nnz, t.rowptr.as<int64_t>(), t.col.as<int32_t>(), t.val.p};
-        Buf k0(c, sizeof(int64_t) * (size_t)t.nnz), k1(c, sizeof(int64_t) * (size_t)t.nnz);
+        Buf k0(c, sizeof(int64_t) * (size_t)t.nnz);
         csr_to_keys(tv, k0.as<int64_t>(), s);
-        remap_keys(c, k0.as<int64_t>(), t.nnz, (int)from.size(), fd.data(), (int)rm.size(), rm.data(), (int)cm.size(),
-                   cm.data(), k1.as<int64_t>(), s);
+        const KeyMap km = key_map((int)from.size(), fd.data(), (int)rm.size(), rm.data(), (int)cm.size(), cm.data());
         int64_t nr = 1, nc = 1;
         for (int q : rm) nr *= fd[q];
         for (int q : cm) nc *= fd[q];
         CsrOut u;
-        fold_keys_to_csr(c, sr, dt, id, k1.as<int64_t>(), t.val.p, t.nnz, nr, nc, &u, s);
+        fold_keys_to_csr(c, sr, dt, id, &km, k0.as<int64_t>(), t.val.p, t.nnz, nr, nc, &u, s);
         t = std::move(u);
       }
       if (accumulate && C->format == SRTC_CSR && C->nnz > 0) {

@@ -17,7 +17,7 @@ void ewise_add(Ctx *c, int sr, int dt, IdVal id, const CsrView &X, const CsrView
   if (X.nnz) SRTC_HIP(hipMemcpyAsync(vals.p, X.val, es * (size_t)X.nnz, hipMemcpyDeviceToDevice, s));
   if (Y.nnz)
     SRTC_HIP(hipMemcpyAsync((char *)vals.p + es * (size_t)X.nnz, Y.val, es * (size_t)Y.nnz, hipMemcpyDeviceToDevice, s));
-  fold_keys_to_csr(c, sr, dt, id, keys.as<int64_t>(), vals.p, nnz, X.m, X.n, out, s);
+  fold_keys_to_csr(c, sr, dt, id, nullptr, keys.as<int64_t>(), vals.p, nnz, X.m, X.n, out, s);
 }
 
 }  // namespace srtc

@@ -135,15 +135,20 @@ int64_t read_i64(Ctx *c, const int64_t *dev, hipStream_t s);
 void read_to_host(Ctx *c, void *host, const void *dev, size_t bytes, hipStream_t s);
 
 // ----------------------------------------------------------------- fold --
-// Keys (row*ncols + col, < 2^63) with values -> CSR, duplicates combined in
-// input order, identity entries dropped.  Synchronizes once.
-void fold_keys_to_csr(Ctx *c, int sr, int dt, IdVal id, const int64_t *keys, const void *vals,
+// Mode remap of linearized keys: a key's mode indices, each times the mode's
+// multiplier in the matrix key row*ncols + col.
+struct KeyMap {
+  int order;
+  uint64_t dim[SRTC_MAX_ORDER], magic[SRTC_MAX_ORDER], mul[SRTC_MAX_ORDER];
+};
+// The map whose row (col) key linearizes the listed source modes.
+KeyMap key_map(int order, const int64_t *dims, int nrow_modes, const int *row_modes, int ncol_modes,
+               const int *col_modes);
+// Keys (row*ncols + col, < 2^63, after the map if there is one) with values
+// -> CSR, duplicates combined in input order, identity entries dropped.
+// Synchronizes once.
+void fold_keys_to_csr(Ctx *c, int sr, int dt, IdVal id, const KeyMap *map, const int64_t *keys, const void *vals,
                       int64_t nnz, int64_t nrows, int64_t ncols, CsrOut *out, hipStream_t s);
-// Mode remap of linearized keys: out[t] = rowkey*ncols + colkey where the
-// row (col) key linearizes the listed source modes.
-void remap_keys(Ctx *c, const int64_t *keys, int64_t nnz, int order, const int64_t *dims,
-                int nrow_modes, const int *row_modes, int ncol_modes, const int *col_modes,
-                int64_t *out, hipStream_t s);
 // Expand a CSR matrix to linearized keys row*ncols+col.
 void csr_to_keys(const CsrView &a, int64_t *keys, hipStream_t s);
 // Stable LSD radix sort of 64-bit keys carrying a 32-bit payload (exposed
