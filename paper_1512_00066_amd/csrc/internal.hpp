@@ -166,7 +166,6 @@ struct Schedule {
   // above: dense LDS windows
   int64_t t_tiny, t_small, t_mid, t_big;
   int small_wave;    // 512-slot bin: one 64-thread wave per row (1) or two waves (0)
-  int dense_bs;      // dense-window block size (256 or 512; the widest windows always take 1024)
   int dense_wide;    // dense window of 8K (0), 16K (1) or 4K (2) 8-byte accumulators
 };
 const Schedule &schedule(int id);

@@ -110,10 +110,11 @@ struct Thresholds {
 
 // info layout: [0..NBIN) counts, [NBIN..2NBIN) starts, [SUM] sum of values,
 // [SUMV..SUMV+NBIN) per-bin sums of values, [SUMA..SUMA+NBIN) per-bin sums
-// of A row lengths (bin 0's sums stay 0)
+// of A row lengths (bin 0's sums stay 0), [MAXV] the largest value
 constexpr int SUM = 2 * NBIN;
 constexpr int SUMV = 2 * NBIN + 1;
 constexpr int SUMA = 3 * NBIN + 1;
+constexpr int MAXV = 4 * NBIN + 1;
 constexpr int INFO = 4 * NBIN + 2;
 
 __device__ __forceinline__ int bin_of(int64_t v, const Thresholds &th) {
@@ -135,12 +136,21 @@ constexpr int BIN_BS = 256;
 constexpr int BIN_MAXB = 1024;
 constexpr int BIN_SMALL = 4096;
 constexpr int64_t SMALL_COLS = 16384;  // most columns of B of a small product's row bitmap
-// per block: counts of bins 1.., the sum of all values, and, for the profile's
-// byte counts, the value sums and A length sums of bins 1..
+// per block: counts of bins 1.., the sum and the largest of all values, and,
+// for the profile's byte counts, the value sums and A length sums of bins 1..
 constexpr int BIN_C = NBIN - 1;
-constexpr int BIN_Q = BIN_C + 1;
-constexpr int BIN_QS = 3 * BIN_C + 1;
+constexpr int BIN_MX = BIN_C + 1;
+constexpr int BIN_Q = BIN_C + 2;
+constexpr int BIN_QS = 3 * BIN_C + 2;
 template <bool SUMS> constexpr int bin_quantities() { return SUMS ? BIN_QS : BIN_Q; }
+
+// (of values of at least 0)
+__device__ __forceinline__ int64_t wave_max(int64_t v) {
+#pragma unroll
+  for (int o = 1; o < WAVE; o <<= 1) v = max(v, (int64_t)__shfl_xor((long long)v, o));
+  return v;
+}
+__device__ __forceinline__ int64_t bin_join(int q, int64_t a, int64_t b) { return q == BIN_MX ? max(a, b) : a + b; }
 
 // Those quantities over rows i0, i0 + stride, ... below i1, reduced over each
 // wave into acc[.][wave].
@@ -160,18 +170,19 @@ __device__ __forceinline__ void bin_tally(const int64_t *__restrict__ v, int64_t
       len = rpA[r + 1] - rpA[r];
     }
     if (b > 0) q[BIN_C] += x;
+    q[BIN_MX] = max(q[BIN_MX], x);
 #pragma unroll
     for (int bb = 1; bb < NBIN; bb++) {
       cnt[bb - 1] += b == bb ? 1 : 0;
       if constexpr (SUMS) {
-        q[BIN_C + bb] += b == bb ? x : 0;
-        q[2 * BIN_C + bb] += b == bb ? len : 0;
+        q[BIN_MX + bb] += b == bb ? x : 0;
+        q[BIN_MX + BIN_C + bb] += b == bb ? len : 0;
       }
     }
   }
 #pragma unroll
   for (int b = 0; b < NQ; b++) {
-    const int64_t x = b < BIN_C ? (int64_t)wave_sum(cnt[b]) : wave_sum(q[b]);
+    const int64_t x = b < BIN_C ? (int64_t)wave_sum(cnt[b]) : b == BIN_MX ? wave_max(q[b]) : wave_sum(q[b]);
     if (lane_id() == 0) acc[b][threadIdx.x / WAVE] = x;
   }
 }
@@ -223,7 +234,7 @@ __global__ void __launch_bounds__(BIN_BS) bin_count(const int64_t *__restrict__ 
   __syncthreads();
   if (threadIdx.x < NQ) {
     int64_t x = 0;
-    for (int q = 0; q < BIN_BS / WAVE; q++) x += acc[threadIdx.x][q];
+    for (int q = 0; q < BIN_BS / WAVE; q++) x = bin_join(threadIdx.x, x, acc[threadIdx.x][q]);
     part[(int64_t)threadIdx.x * BIN_MAXB + blockIdx.x] = x;
   }
 }
@@ -236,10 +247,11 @@ template <bool SUMS> __device__ __forceinline__ void bin_info(const int64_t *tot
     info[b] = tot[b - 1];
     info[NBIN + b] = run;
     run += tot[b - 1];
-    info[SUMV + b] = SUMS ? tot[BIN_C + b] : 0;
-    info[SUMA + b] = SUMS ? tot[2 * BIN_C + b] : 0;
+    info[SUMV + b] = SUMS ? tot[BIN_MX + b] : 0;
+    info[SUMA + b] = SUMS ? tot[BIN_MX + BIN_C + b] : 0;
   }
   info[SUM] = tot[BIN_C];
+  info[MAXV] = tot[BIN_MX];
 }
 
 // One wave per quantity: the counts become exclusive prefixes over the
@@ -254,6 +266,10 @@ __global__ void __launch_bounds__(1024) bin_offsets(int64_t *__restrict__ part, 
     for (int b0 = 0; b0 < nblk; b0 += WAVE) {
       const int b = b0 + l;
       const int64_t x = b < nblk ? part[(int64_t)q * BIN_MAXB + b] : 0;
+      if (q == BIN_MX) {
+        run = max(run, wave_max(x));
+        continue;
+      }
       const int64_t inc = wave_incl_scan(x);
       if (q < BIN_C && b < nblk) part[(int64_t)q * BIN_MAXB + b] = run + inc - x;
       run += lane63(inc);
@@ -291,7 +307,7 @@ __device__ __forceinline__ void bin_all(const int64_t *__restrict__ v, int64_t m
   __syncthreads();
   if (threadIdx.x < NQ) {
     int64_t x = 0;
-    for (int q = 0; q < 1024 / WAVE; q++) x += acc[threadIdx.x][q];
+    for (int q = 0; q < 1024 / WAVE; q++) x = bin_join(threadIdx.x, x, acc[threadIdx.x][q]);
     tot[threadIdx.x] = x;
   }
   __syncthreads();
@@ -1872,15 +1888,15 @@ const void *b_table(Ctx *c, const CsrView &Bm, int64_t key, size_t bytes, Buf &l
 // Schedules: symbolic hash ceiling, numeric bin edges, extraction and dense
 // window shape.  Index = schedule id.
 const Schedule kSchedules[SRTC_NUM_SCHEDULES] = {
-    // sym_hash_max, t_tiny, t_small, t_mid, t_big, small_wave, dense_bs, dense_wide
-    {2048, 32, 256, 2048, 4096, 0, 256, 0},   // 0 balanced
-    {2048, 32, 256, 2048, 4096, 1, 256, 0},   // 1 as 0 with one wave per row in the 512-slot bin
-    {2048, 32, 256, 256, 256, 1, 256, 0},     // 2 dense windows from 257 outputs
-    {8192, 32, 256, 2048, 2048, 0, 1024, 1},  // 3 wide dense windows (1024-thread blocks) from 2049 outputs
-    {0, 0, 0, 0, 0, 0, 256, 0},               // 4 dense windows for every row
-    {2048, 32, 256, 256, 256, 0, 512, 0},     // 5 as 0, 512-thread dense windows from 257 outputs
-    {2048, 32, 256, 2048, 4096, 0, 512, 2},   // 6 as 5 with narrow dense windows (more blocks per CU)
-    {256, 32, 256, 1024, 1024, 1, 256, 0},    // 7 bitmap symbolic above 256 products
+    // sym_hash_max, t_tiny, t_small, t_mid, t_big, small_wave, dense_wide
+    {2048, 32, 256, 2048, 4096, 0, 0},  // 0 balanced
+    {2048, 32, 256, 2048, 4096, 1, 0},  // 1 as 0 with one wave per row in the 512-slot bin
+    {2048, 32, 256, 256, 256, 1, 0},    // 2 dense windows from 257 outputs
+    {8192, 32, 256, 2048, 2048, 0, 1},  // 3 wide dense windows (1024-thread blocks) from 2049 outputs
+    {0, 0, 0, 0, 0, 0, 0},              // 4 dense windows for every row
+    {2048, 32, 256, 256, 256, 0, 0},    // 5 as 0, dense windows from 257 outputs
+    {2048, 32, 256, 2048, 4096, 0, 2},  // 6 as 0 with narrow dense windows (more blocks per CU)
+    {256, 32, 256, 1024, 1024, 1, 0},   // 7 bitmap symbolic above 256 products
 };
 
 struct Launch {
@@ -1924,7 +1940,7 @@ int32_t bitmap_words(int64_t ncols, int bs, int64_t budget_bytes) {
 // counters (NBIN * BIN_CTRS, zeroed by the caller).
 int64_t run_symbolic(const Launch &L, const Schedule &S, const CsrView &Am, const CsrView &Bm, const int64_t *w,
                      const int32_t *row_map, int64_t nsel, int64_t *info1, int32_t *list, int64_t *nnz_row,
-                     int64_t *err, int64_t *ctrs) {
+                     int64_t *err, int64_t *ctrs, int64_t *most = nullptr) {
   hipStream_t s = L.s;
   Ctx *c = L.c;
   const int64_t n = Bm.n;
@@ -2002,6 +2018,7 @@ int64_t run_symbolic(const Launch &L, const Schedule &S, const CsrView &Am, cons
                                           nnz_row, heavy_feed(ctr1(HEAVY), hinfo[HEAVY], grid));
     SRTC_LAUNCH_CHECK("sym_bitmap");
   }
+  if (most) *most = hinfo[MAXV];
   return hinfo[SUM];
 }
 
@@ -2091,16 +2108,28 @@ template <class SR> Schedule budgeted(const Ctx *c, int id) {
   int need = 0;
   if (S.dense_wide == 1) need = num_dense_lds<SR, 1024, W1>();
   else if (S.dense_wide == 2) need = num_dense_lds<SR, 512, W2>();
-  else need = S.dense_bs == 512 ? num_dense_lds<SR, 512, W0>() : num_dense_lds<SR, 256, W0>();
+  else need = num_dense_lds<SR, 512, W0>();
   if (need > B) {
     S.dense_wide = 2;
-    S.dense_bs = 512;
     if (num_dense_lds<SR, 512, W2>() > B)
       fail(SRTC_ERR_UNSUPPORTED, "SRTC_LDS_BUDGET is below the narrowest dense window (" +
                                      std::to_string(num_dense_lds<SR, 512, W2>()) + " bytes)");
   }
   return S;
 }
+
+// A row of very many products runs on one block from its first window to its
+// last: where it has more than the share of one of 170 blocks of all products,
+// it, and not the chip, bounds the dense rows, and the 1,024-thread kernel
+// with half as many windows finishes it earlier (row panels of R-MAT 17 and
+// 19, 800 to 9,000 rows whose largest has 4 to 28 512th parts, fp32: 512
+// threads 1,200, 2,445 and 5,346 us, 1,024 threads 900, 1,640 and 3,300 us).
+// Below, more blocks are better (R-MAT 16, 0.8 512th parts: 2,813 and 3,157;
+// R-MAT 18, 0.4: 20,250 and 22,760; R-MAT 14, 1.6: 903 and 828, but 628 and
+// 726 under schedule 2), and so they are for few rows of moderate work (300
+// rows of 10,000 products: 145 and 159).
+constexpr double HUB_BLOCKS = 512.0 / 3;
+constexpr int64_t HUB_PRODUCTS = 1 << 17;
 
 // Numeric bins: 1: <= t_tiny outputs (64-slot hash), 2: <= t_small (512), 3:
 // <= 512 (1024), 4: <= 1024 (2048), 5: <= t_mid (4096), 6: <= t_big (8192),
@@ -2147,9 +2176,10 @@ template <class SR>
 void numeric_launch(Ctx *c, typename SR::acc_t id, const CsrView &Am, const CsrView &Bm, const int64_t *w,
                     const RowGroup &g, const int64_t *hinfo2, int64_t *info2, int32_t *lst, int sorted,
                     OutRows rpC, int32_t *cC, typename SR::val_t *vC, int64_t *kp, int32_t *fl,
-                    int64_t *ctrs, SpgemmStats *st, hipStream_t s) {
+                    int64_t *ctrs, SpgemmStats *st, hipStream_t s, bool hub = false) {
   using V = typename SR::val_t;
-  const Schedule S = budgeted<SR>(c, g.sched);
+  Schedule S = budgeted<SR>(c, g.sched);
+  if (hub && S.dense_wide == 0 && num_dense_lds<SR, 1024, (int)dense_width<SR>(1)>() <= c->lds_budget) S.dense_wide = 1;
   const int64_t n = Bm.n;
   Launch L{c, s};
   if (w) heavy_first(c, lst + hinfo2[NBIN + HEAVY], hinfo2[HEAVY], w, s);  // (a small product has no order)
@@ -2236,8 +2266,12 @@ void numeric_launch(Ctx *c, typename SR::acc_t id, const CsrView &Am, const CsrV
     } else if (S.dense_wide == 2) {
       NL::template dense<512, W2>(L, hinfo2[HEAVY], lst, info2, HEAVY, Am, Bm, wo, nwin, rb, rpC, cC, vC, id, kp, fl, ctr2(HEAVY));
     } else {
-      if (S.dense_bs == 512) NL::template dense<512, W0>(L, hinfo2[HEAVY], lst, info2, HEAVY, Am, Bm, wo, nwin, rb, rpC, cC, vC, id, kp, fl, ctr2(HEAVY));
-      else NL::template dense<256, W0>(L, hinfo2[HEAVY], lst, info2, HEAVY, Am, Bm, wo, nwin, rb, rpC, cC, vC, id, kp, fl, ctr2(HEAVY));
+      // 512 threads: two blocks fit a CU whatever their threads, and 256 of
+      // them left it 8 waves (default schedule, R-MAT 18 fp64: 256 threads
+      // 24,980, 512 threads 20,240 us; R-MAT 16 fp32 3,263 and 2,839; ER n =
+      // 200,000 d = 90 fp64 29,640 and 21,330; ER n = 20,000 d = 80 fp32
+      // 1,436 and 1,255)
+      NL::template dense<512, W0>(L, hinfo2[HEAVY], lst, info2, HEAVY, Am, Bm, wo, nwin, rb, rpC, cC, vC, id, kp, fl, ctr2(HEAVY));
     }
   }
 }
@@ -2301,6 +2335,7 @@ void spgemm_groups(Ctx *c, IdVal idv, const CsrView &Am, const CsrView &Bm, cons
   auto pass_ctrs = [&](int q, int pass) { return ctrs + (int64_t)(2 * q + pass) * NBIN * BIN_CTRS; };
   fill_i64(w0, nclear, 0, s);
   std::vector<int64_t> htab((size_t)ntab);
+  std::vector<char> hub((size_t)G, 0);  // a few of the group's rows bound it (numeric_launch)
   // A small product (its rows fit one block's binning, B's columns a bitmap
   // of 2 KB) is launches and host reads, not work: output counts of all rows
   // in one launch, then row pointers and bins in one, and one read.  Median
@@ -2337,8 +2372,12 @@ void spgemm_groups(Ctx *c, IdVal idv, const CsrView &Am, const CsrView &Bm, cons
       const RowGroup &g = groups[q];
       const int64_t nsel = g.row_map ? g.nsel : m;
       if (nsel == 0) continue;
-      products += run_symbolic(L, budgeted<SR>(c, g.sched), Am, Bm, w, g.row_map, nsel, tab + 1 + (int64_t)q * INFO,
-                               list_of(q), nnz_row, sym_err, pass_ctrs(q, 0));
+      int64_t most = 0;
+      const int64_t sum = run_symbolic(L, budgeted<SR>(c, g.sched), Am, Bm, w, g.row_map, nsel,
+                                       tab + 1 + (int64_t)q * INFO, list_of(q), nnz_row, sym_err, pass_ctrs(q, 0),
+                                       &most);
+      hub[q] = most >= HUB_PRODUCTS && (double)most * HUB_BLOCKS > (double)sum;
+      products += sum;
     }
     c->tracef("spgemm: symbolic launched, %lld products", (long long)products);
     if (st) st->products = products;
@@ -2363,7 +2402,7 @@ void spgemm_groups(Ctx *c, IdVal idv, const CsrView &Am, const CsrView &Bm, cons
     for (int q = 0; q < G; q++)
       numeric_launch<SR>(c, id, Am, Bm, small ? nullptr : w, groups[q], htab.data() + 1 + (size_t)q * INFO,
                          tab + 1 + (int64_t)q * INFO, list_of(q), sorted, OutRows{rpC, nnz_row, 0}, cC, vC, kp, fl,
-                         pass_ctrs(q, 1), st, s);
+                         pass_ctrs(q, 1), st, s, hub[q]);
   // 6. compaction when identity results were dropped
   int32_t flags_h[4] = {0, 0, 0, 0};
   read_to_host(c, flags_h, fl, sizeof(flags_h), s);
