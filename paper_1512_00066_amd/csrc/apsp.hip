@@ -192,11 +192,44 @@ struct Narrow {
   }
 };
 
-//
-// With cnt given, the epilogue also counts for the next round (l2 = 2l):
+// The tile's results to Pn, thread (ty, tx) = (tid / 16, tid % 16).
+// With cnt given, it also counts for the next round (l2 = 2l):
 // cnt[i] += entries of row i of Pn with exactly l2 hops (cnt zeroed by the
 // caller), and part[2 b], part[2 b + 1] = largest weight and hop count in
 // block b's tile, so the next round needs no separate pass over P.
+template <class E, int RM, int RN>
+__device__ __forceinline__ void write_tile(const typename E::T (&acc)[RM][RN], uint64_t *__restrict__ Pn, int64_t n,
+                                           int64_t row0, int64_t col0, uint32_t idw, const E &enc,
+                                           int64_t *__restrict__ cnt, uint32_t l2, uint32_t *__restrict__ part) {
+  const int ty = threadIdx.x / 16, tx = threadIdx.x % 16;
+  uint32_t wmax = 0, hmax = 0;
+#pragma unroll
+  for (int m = 0; m < RM; m++) {
+    const int64_t i = row0 + ty * RM + m;
+    int c = 0;
+#pragma unroll
+    for (int q = 0; q < RN; q++) {
+      const int64_t j = col0 + tx * RN + q;
+      if (i < n && j < n) {
+        const uint64_t o = enc.dec(acc[m][q]);
+        Pn[i * n + j] = o;
+        const uint32_t w = (uint32_t)(o >> 32), h = (uint32_t)o;
+        if (w < idw) {
+          c += h == l2 ? 1 : 0;
+          wmax = w > wmax ? w : wmax;
+          hmax = h > hmax ? h : hmax;
+        }
+      }
+    }
+    if (cnt) {
+      // the 16 threads of a tile row are 16 consecutive lanes
+      for (int d = 8; d >= 1; d >>= 1) c += __shfl_xor(c, d, WAVE);
+      if (tx == 0 && i < n && c > 0) atomicAdd((unsigned long long *)(cnt + i), (unsigned long long)c);
+    }
+  }
+  if (cnt) block_range(wmax, hmax, part, (int64_t)blockIdx.y * gridDim.x + blockIdx.x);
+}
+
 template <class E, int TM, int TN, int TK, int MINB>
 __global__ void __launch_bounds__(256, MINB) apsp_dense_round(const uint64_t *__restrict__ P, uint64_t *__restrict__ Pn,
                                                               int64_t n, uint32_t l, uint32_t idw, E enc,
@@ -280,32 +313,98 @@ __global__ void __launch_bounds__(256, MINB) apsp_dense_round(const uint64_t *__
     }
     __syncthreads();
   }
-  uint32_t wmax = 0, hmax = 0;
+  write_tile<E, RM, RN>(acc, Pn, n, row0, col0, idw, enc, cnt, l2, part);
+}
+
+// The 32-bit round on operands encoded once.  B = P and Lt = the l-hop part of
+// P transposed, as Narrow words in ld x ld matrices (ld = n rounded up to 64,
+// the identity outside n).  Staged from P itself, a tile's words cost a
+// 64-bit load, a range test, a shift and a 4-byte LDS write each, in every
+// block that uses them: 16 per thread and k-tile next to 384 sums' worth of
+// adds and mins.  Here they are 16-byte copies, and two LDS buffers leave one
+// barrier per k-tile.  Bound by the vector ALU (1.5 instructions a sum, two
+// adds and a three-way min for two).  Dense graphs, whole call of four to six
+// rounds: n = 1,000 836 -> 707 us, n = 2,000 2,258 -> 1,818, n = 3,001 6,034 ->
+// 4,999.  Larger tiles per thread (8 x 4, 4 x 8) took 2,506 and 2,455 at n =
+// 2,000 before: fewer blocks cost more than fewer LDS reads gave.
+__global__ void __launch_bounds__(256) encode_tiles(const uint64_t *__restrict__ P, int64_t n, int64_t ld, uint32_t l,
+                                                    Narrow enc, uint32_t *__restrict__ B, uint32_t *__restrict__ Lt) {
+  __shared__ uint32_t T[64][65];
+  const int64_t i0 = (int64_t)blockIdx.y * 64, j0 = (int64_t)blockIdx.x * 64;
+  const int x = threadIdx.x % 64, y = threadIdx.x / 64;
 #pragma unroll
-  for (int m = 0; m < RM; m++) {
-    const int64_t i = row0 + ty * RM + m;
-    int c = 0;
+  for (int r = 0; r < 64; r += 4) {
+    const int64_t i = i0 + r + y, j = j0 + x;
+    const uint64_t v = i < n && j < n ? P[i * n + j] : (uint64_t)enc.idw << 32;
+    const uint32_t e = enc.enc(v);
+    B[i * ld + j] = e;
+    T[r + y][x] = (uint32_t)v == l ? e : enc.id();
+  }
+  __syncthreads();
 #pragma unroll
-    for (int q = 0; q < RN; q++) {
-      const int64_t j = col0 + tx * RN + q;
-      if (i < n && j < n) {
-        const uint64_t o = enc.dec(acc[m][q]);
-        Pn[i * n + j] = o;
-        const uint32_t w = (uint32_t)(o >> 32), h = (uint32_t)o;
-        if (w < idw) {
-          c += h == l2 ? 1 : 0;
-          wmax = w > wmax ? w : wmax;
-          hmax = h > hmax ? h : hmax;
-        }
+  for (int r = 0; r < 64; r += 4) Lt[(j0 + r + y) * ld + i0 + x] = T[x][r + y];
+}
+
+__global__ void __launch_bounds__(256, 4) apsp_round32(const uint32_t *__restrict__ B, const uint32_t *__restrict__ Lt,
+                                                       int64_t ld, uint64_t *__restrict__ Pn, int64_t n, uint32_t idw,
+                                                       Narrow enc, int64_t *__restrict__ cnt, uint32_t l2,
+                                                       uint32_t *__restrict__ part) {
+  constexpr int TK = 32, TS = 64 + 4, R = 4;
+  __shared__ __align__(16) uint32_t Ls[2][TK][TS], Bs[2][TK][64];
+  const int tid = threadIdx.x, ty = tid / 16, tx = tid % 16;
+  const int64_t row0 = (int64_t)blockIdx.y * 64, col0 = (int64_t)blockIdx.x * 64;
+  uint32_t acc[R][R];
+#pragma unroll
+  for (int m = 0; m < R; m++) {
+    const uint4 v = *reinterpret_cast<const uint4 *>(B + (row0 + ty * R + m) * ld + col0 + tx * R);
+    acc[m][0] = v.x;
+    acc[m][1] = v.y;
+    acc[m][2] = v.z;
+    acc[m][3] = v.w;
+  }
+  // thread tid stages words 4 tx .. 4 tx + 3 of rows ty and ty + 16
+  uint4 ra[2], rb[2];
+  const uint32_t *pa = Lt + ty * ld + row0 + 4 * tx, *pb = B + ty * ld + col0 + 4 * tx;
+  auto fetch = [&](int64_t k0) {
+#pragma unroll
+    for (int q = 0; q < 2; q++) {
+      ra[q] = *reinterpret_cast<const uint4 *>(pa + (k0 + 16 * q) * ld);
+      rb[q] = *reinterpret_cast<const uint4 *>(pb + (k0 + 16 * q) * ld);
+    }
+  };
+  auto stage = [&](int buf) {
+    uint32_t least = enc.id();
+#pragma unroll
+    for (int q = 0; q < 2; q++) {
+      *reinterpret_cast<uint4 *>(&Ls[buf][ty + 16 * q][4 * tx]) = ra[q];
+      *reinterpret_cast<uint4 *>(&Bs[buf][ty + 16 * q][4 * tx]) = rb[q];
+      least = min(min(least, min(ra[q].x, ra[q].y)), min(ra[q].z, ra[q].w));
+    }
+    return least < enc.id() ? 1 : 0;
+  };
+  fetch(0);
+  int live = __syncthreads_or(stage(0));
+  int buf = 0;
+  for (int64_t k0 = 0; k0 < ld; k0 += TK, buf ^= 1) {
+    const bool more = k0 + TK < ld;
+    if (more) fetch(k0 + TK);
+    if (live) {
+#pragma unroll 4
+      for (int kk = 0; kk < TK; kk++) {
+        uint32_t a[R], b[R];
+#pragma unroll
+        for (int m = 0; m < R; m++) a[m] = Ls[buf][kk][ty * R + m];
+#pragma unroll
+        for (int q = 0; q < R; q++) b[q] = Bs[buf][kk][tx * R + q];
+#pragma unroll
+        for (int m = 0; m < R; m++)
+#pragma unroll
+          for (int q = 0; q < R; q++) acc[m][q] = min(acc[m][q], a[m] + b[q]);
       }
     }
-    if (cnt) {
-      // the 16 threads of a tile row are 16 consecutive lanes
-      for (int d = 8; d >= 1; d >>= 1) c += __shfl_xor(c, d, WAVE);
-      if (tx == 0 && i < n && c > 0) atomicAdd((unsigned long long *)(cnt + i), (unsigned long long)c);
-    }
+    if (more) live = __syncthreads_or(stage(buf ^ 1));
   }
-  if (cnt) block_range(wmax, hmax, part, (int64_t)blockIdx.y * gridDim.x + blockIdx.x);
+  write_tile<Narrow, R, R>(acc, Pn, n, row0, col0, idw, enc, cnt, l2, part);
 }
 
 __global__ void apsp_out(const uint64_t *__restrict__ P, int64_t total, uint32_t idw, int32_t *__restrict__ D,
@@ -328,6 +427,10 @@ __global__ void apsp_out(const uint64_t *__restrict__ P, int64_t total, uint32_t
 // sums about 18x faster per sum than the CSR product forms nnz * n, a
 // 64-bit round about 7x.
 constexpr double kDenseFracNarrow = 0.05, kDenseFracWide = 0.14;
+// Largest n whose 32-bit rounds encode their operands first (8 GB of words
+// beside the two path matrices' 16 GB); larger ones stage from P, whose own
+// size then decides what fits.
+constexpr int64_t kEncodeMax = 32768;
 
 void apsp_tiskin(Ctx *c, const CsrView &A, int32_t idw, int32_t *D, int32_t *H, int32_t *rounds, int64_t *round_nnz,
                  hipStream_t s) {
@@ -368,6 +471,7 @@ void apsp_tiskin(Ctx *c, const CsrView &A, int32_t idw, int32_t *D, int32_t *H, 
   const int64_t cnt_blocks = std::min<int64_t>(grid_of(n * WAVE), 1024);
   const int64_t tiles = ((n + DTM - 1) / DTM) * ((n + DTN - 1) / DTN);
   Buf part(c, 8 * (size_t)std::max<int64_t>({cnt_blocks, tiles, 1}));
+  Buf words;  // encoded operands of the 32-bit rounds
   bool counted = false;  // the previous dense round already counted this round's paths
   int32_t r = 0;
   if (round_nnz) std::fill(round_nnz, round_nnz + 64, (int64_t)0);
@@ -403,10 +507,19 @@ void apsp_tiskin(Ctx *c, const CsrView &A, int32_t idw, int32_t *D, int32_t *H, 
       if (nc) fill_i64(nc, n, 0, s);
       const dim3 grid((unsigned)((n + DTN - 1) / DTN), (unsigned)((n + DTM - 1) / DTM));
       if (narrow) {
-        // 64 x 64 tiles, 3 blocks per CU: measured best at n = 2048 of
-        // 128x128 (k 16/32), 128x64, 64x128 (k 32/64) and 64x64 (k 32/64)
-        apsp_dense_round<Narrow, DTM, DTN, DTK, 3><<<grid, 256, 0, s>>>(
-            P, Pn, n, (uint32_t)l, (uint32_t)idw, Narrow{(uint32_t)idw, hb}, nc, l2, part.as<uint32_t>());
+        const Narrow enc{(uint32_t)idw, hb};
+        if (n <= kEncodeMax) {
+          const int64_t ld = (n + 63) / 64 * 64;
+          if (!words.p) words = Buf(c, sizeof(uint32_t) * 2 * (size_t)(ld * ld));
+          uint32_t *B = words.as<uint32_t>(), *Lt = B + ld * ld;
+          const dim3 tg((unsigned)(ld / 64), (unsigned)(ld / 64));
+          encode_tiles<<<tg, 256, 0, s>>>(P, n, ld, (uint32_t)l, enc, B, Lt);
+          SRTC_LAUNCH_CHECK("encode_tiles");
+          apsp_round32<<<tg, 256, 0, s>>>(B, Lt, ld, Pn, n, (uint32_t)idw, enc, nc, l2, part.as<uint32_t>());
+        } else {
+          apsp_dense_round<Narrow, DTM, DTN, DTK, 3><<<grid, 256, 0, s>>>(P, Pn, n, (uint32_t)l, (uint32_t)idw, enc, nc,
+                                                                           l2, part.as<uint32_t>());
+        }
       } else {
         apsp_dense_round<Wide, DTM, DTN, 16, 2><<<grid, 256, 0, s>>>(P, Pn, n, (uint32_t)l, (uint32_t)idw,
                                                                       Wide{idv}, nc, l2, part.as<uint32_t>());
