@@ -73,29 +73,41 @@ __global__ void __launch_bounds__(SCAN_BS) scan_tile_down(const In *in, int64_t 
   }
 }
 
-// The whole scan in one block and one launch, for short inputs.
+// The whole scan in one block and one launch, for short inputs: a wave holds
+// `per` rounds of 64 consecutive entries, scans each round with the sum of
+// those before it, and the waves' totals meet in one barrier (16,384 entries
+// of 8 bytes: 11 us; 19 us with consecutive entries per thread, and the three
+// kernels below 13 us and the gaps between them).
 constexpr int SCAN1_BS = 1024;
 constexpr int SCAN1_IT = 16;
 constexpr int64_t SCAN1_MAX = SCAN1_BS * SCAN1_IT;
 template <class In>
 __global__ void __launch_bounds__(SCAN1_BS) scan_one_block(const In *in, int64_t n, int64_t *out) {
-  __shared__ int64_t tmp[SCAN1_BS / WAVE + 1];
-  const int per = (int)((n + SCAN1_BS - 1) / SCAN1_BS);  // at most SCAN1_IT consecutive entries per thread
-  const int64_t base = (int64_t)threadIdx.x * per;
+  __shared__ int64_t tmp[SCAN1_BS / WAVE];
+  const int per = (int)((n + SCAN1_BS - 1) / SCAN1_BS);  // at most SCAN1_IT
+  const int w = threadIdx.x / WAVE;
+  const int64_t base = (int64_t)w * per * WAVE + lane_id();
   int64_t v[SCAN1_IT];
-  int64_t acc = 0;
 #pragma unroll
-  for (int t = 0; t < SCAN1_IT; t++) {
-    v[t] = t < per && base + t < n ? (int64_t)in[base + t] : 0;
-    acc += v[t];
-  }
-  int64_t total;
-  int64_t pre = block_excl_scan<SCAN1_BS>(acc, tmp, &total);
+  for (int r = 0; r < SCAN1_IT; r++) v[r] = r < per && base + r * WAVE < n ? (int64_t)in[base + r * WAVE] : 0;
+  int64_t sum = 0;
 #pragma unroll
-  for (int t = 0; t < SCAN1_IT; t++) {
-    if (t < per && base + t < n) out[base + t] = pre;
-    pre += v[t];
+  for (int r = 0; r < SCAN1_IT; r++) {
+    if (r >= per) break;
+    const int64_t inc = wave_incl_scan(v[r]);
+    v[r] = sum + inc - v[r];
+    sum += lane63(inc);
   }
+  if (lane_id() == 0) tmp[w] = sum;
+  __syncthreads();
+  int64_t before = 0, total = 0;
+  for (int q = 0; q < SCAN1_BS / WAVE; q++) {
+    if (q < w) before += tmp[q];
+    total += tmp[q];
+  }
+#pragma unroll
+  for (int r = 0; r < SCAN1_IT; r++)
+    if (r < per && base + r * WAVE < n) out[base + r * WAVE] = before + v[r];
   if (threadIdx.x == 0) out[n] = total;
 }
 

@@ -59,3 +59,15 @@ def test_small_product_empty_and_cancelled(ctx):
     A, B = gpu_fold(ctx, "plus_times", "f64", ar, ac, av, m, 2), gpu_fold(ctx, "plus_times", "f64", br, bc, bv, 2, 12)
     rp, col, val = ctx.contract("plus_times", "ik", A, "kj", B, "ij").to_host()
     assert np.array_equal(rp, np.arange(m + 1)) and np.all(col == 9) and np.all(val == -4)
+
+
+@pytest.mark.parametrize("m", [4097, 5121, 16383, 16384, 16385])
+def test_rows_around_the_one_block_scan(ctx, m):
+    """Row pointers from the scan in one block (up to 16,384 rows) and from
+    the tiled one."""
+    say("one-block scan", m)
+    (ar, ac, av), (br, bc, bv) = operands("min_plus", "i32", m, 200, 900, 2, 3, m, True)
+    A, B = gpu_fold(ctx, "min_plus", "i32", ar, ac, av, m, 200), gpu_fold(ctx, "min_plus", "i32", br, bc, bv, 200, 900)
+    exp = oracle.spgemm("min_plus", "i32", oracle.fold("min_plus", "i32", ar, ac, av, m, 200),
+                        oracle.fold("min_plus", "i32", br, bc, bv, 200, 900))
+    check_csr(ctx.contract("min_plus", "ik", A, "kj", B, "ij"), exp, "min_plus", "i32")
