@@ -11,14 +11,15 @@
 //                     an LDS bitmap over the columns (heavy rows)
 //   4. scan           rowptr of C; the single host sync sizes C
 //   5. numeric        per bin: LDS hash, then the kept entries placed by
-//                     rank or bitonic-sorted in LDS, or dense LDS
-//                     accumulator windows and ranked groups over the columns
-//                     (heavy rows)
+//                     bucket rank or, in crowded rows, bitonic-sorted in LDS,
+//                     or dense LDS accumulator windows and ranked groups over
+//                     the columns (heavy rows)
 //   6. compaction     only if some result equalled the additive identity
 //                     (dropped, or written with column -1), the rows are
 //                     packed again.
 // Every per-bin kernel is persistent: a grid sized to the machine pulls rows
-// from an atomic work counter.
+// from a sharded atomic work counter.  Small products replace 1 to 4 by one
+// launch over column bitmaps and one for the layout.
 #include <algorithm>
 #include <cmath>
 #include <vector>

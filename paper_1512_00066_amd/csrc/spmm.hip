@@ -8,12 +8,12 @@
 // Bellman-Ford is P <- P (+) A (x) P on the tropical semiring (Section 4.2).
 //
 // Work is cut into items of at most T nonzeros of one row, so a row of any
-// length costs at most T sequential gathers per lane group; G lanes (G = a
-// power of two >= the dense width, up to 64) share an item, one lane per
-// dense column; a wider operand is cut into chunks of 64 columns and every
-// (item, chunk) pair is a unit of work of its own.  A row split into several items writes partial sums that a
-// second kernel combines in item order, which keeps every semiring,
-// including fp (+), deterministic.
+// length costs at most T sequential gathers per lane.  Up to 32 dense columns,
+// G lanes (G = a power of two >= the width) share an item, one lane per
+// column; above, a wave takes a unit of consecutive nonzeros, of however many
+// items, times a chunk of 64 columns.  A row split into several items writes
+// partial sums that a second kernel combines in item order, which keeps every
+// semiring, including fp (+), deterministic.
 #include <algorithm>
 #include <mutex>
 #include <string>
