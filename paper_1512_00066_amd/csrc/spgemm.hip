@@ -2341,8 +2341,8 @@ void spgemm_groups(Ctx *c, IdVal idv, const CsrView &Am, const CsrView &Bm, cons
   // of 2 KB) is launches and host reads, not work: output counts of all rows
   // in one launch, then row pointers and bins in one, and one read.  Median
   // call with the passes below and so, R-MAT in fp64, ER in int32: ER n = 100
-  // d = 4 98 and 68 us; n = 1,000 d = 8 113 and 81 us; n = 4,000 d = 64 446
-  // and 311 us; R-MAT 10 d = 16 239 and 144 us, R-MAT 12 391 and 298 us.
+  // d = 4 98 and 68 us; n = 1,000 d = 8 113 and 81 us; R-MAT 10 d = 16 239 and
+  // 144 us, R-MAT 12 391 and 298 us.
   const bool small = G == 1 && !groups[0].row_map && m <= BIN_SMALL && Bm.n <= SMALL_COLS && c->lds_budget >= LDS_BYTES;
   if (small) {
     const int32_t ww = (int32_t)((Bm.n + 31) / 32);
@@ -2352,7 +2352,11 @@ void spgemm_groups(Ctx *c, IdVal idv, const CsrView &Am, const CsrView &Bm, cons
       SRTC_LAUNCH_CHECK("sym_small");
     }
     int64_t *host = (int64_t *)c->host_scratch(sizeof(int64_t) * (size_t)ntab);
-    const Thresholds th = numeric_edges(budgeted<SR>(c, groups[0].sched));
+    Thresholds th = numeric_edges(budgeted<SR>(c, groups[0].sched));
+    // The shortest rows join the 512-slot bin: all of them run at once in
+    // either, and each kernel takes as long as a row does, 9 to 10 us (ER n =
+    // 1,000 d = 8: 82 us with a bin of their own, 74 so).
+    th.t[0] = 0;
     if (c->profiling)
       small_layout<true><<<1, 1024, 0, s>>>(nnz_row, m, th, Am.rowptr, out->rowptr.as<int64_t>(), tab + 1, list_of(0),
                                             host);
