@@ -155,15 +155,22 @@ template <int BS> __device__ __forceinline__ double sum_parts(const double *__re
 // block adds up the partial sums of step j - 1 itself (8 KB from L2, the same
 // order everywhere) and stops if that iterate, l = st->base + j - 1, meets
 // the tolerance; block 0 records it.  (A kernel of its own for that sum took
-// one block 17 us and a launch per step.)  Later steps see st->done.  The
-// decision is the same in every block, also while block 0 sets st->done.
+// one block 17 us and a launch per step.)  Later steps see st->done.
+// Block 0 may set st->done while other blocks read it, so a block reads it
+// once, in thread 0, and all its waves take that value from LDS, after a
+// barrier that none of them can leave before.  Waves reading it for themselves
+// could disagree: one that saw the flag would leave, and the others would add
+// up a sum without its part and might run the step, over the iterate that is
+// the answer.  As it is, a block that reads the flag early and one that reads
+// it late both stop, the first by its sum.
 template <int BS>
 __device__ __forceinline__ bool step_stops(const double *__restrict__ part_in, int j, JacobiState *st, double tol2) {
-  if (st->done) return true;
-  if (j == 0) return false;
-  const double u = sum_parts<BS>(part_in, gridDim.x);
+  __shared__ int32_t stopped;
+  if (threadIdx.x == 0) stopped = st->done;
+  const double u = sum_parts<BS>(part_in, j > 0 ? gridDim.x : 0);  // its barrier publishes `stopped`
+  if (stopped) return true;
   const int64_t l = st->base + j - 1;
-  if (l < 1 || u > tol2 || u != u) return false;
+  if (j == 0 || l < 1 || u > tol2 || u != u) return false;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     st->rsq = u;
     st->iter = l;
