@@ -598,6 +598,9 @@ __global__ void __launch_bounds__(256) bfs_step_kernel(const int64_t *__restrict
         uint64_t f = found[q];
         const int64_t ri = i0 + q;
         if (f == w) continue;
+        // every wave has looked at found[q] before any of them adds to it: one
+        // that came late and saw the row complete would skip its barriers
+        __syncthreads();
         const int64_t re = rp[ri + 1];
         for (int64_t p = rp[ri] + BFS_LONG; p < re && f != w; p += 256 * BFS_U) {
           uint64_t x = take(p + t, re, 256) & w;

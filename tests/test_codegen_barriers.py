@@ -107,3 +107,42 @@ def test_jacobi_blocks_decide_to_stop_as_one(folder):
     assert len(steps) >= 14  # two types: five row widths and two slice layouts each
     bad = [n for n, c in steps.items() if leaves_before_barrier(c)]
     assert not bad, bad
+
+
+def adds_after_own_look(code):
+    looks = [k for k, ins in enumerate(code) if ins.startswith("ds_read")]
+    return reaches(code, [k + 1 for k in looks], r"ds_or", r"s_barrier")
+
+
+def test_search_sees_an_unguarded_look(folder):
+    body = """
+extern "C" __global__ void __launch_bounds__(256) _Zlong(const unsigned *in, unsigned *out, int n) {
+  __shared__ unsigned found;
+  if (threadIdx.x == 0) found = in[0];
+  __syncthreads();
+  unsigned f = found;
+  if (f != 7u) {
+    %s
+    for (int p = threadIdx.x; p < n && f != 7u; p += 256) {
+      atomicOr(&found, in[p]);
+      __syncthreads();
+      f = found;
+      __syncthreads();
+    }
+  }
+  out[threadIdx.x] = f;
+}
+"""
+    for name, guard, bad in (("unguarded", "", True), ("guarded", "__syncthreads();", False)):
+        (code,) = small_asm(body % guard, folder, name).values()
+        assert any(ins.startswith("ds_or") for ins in code)
+        assert adds_after_own_look(code) == bad
+
+
+def test_bfs_waves_agree_on_a_long_row(folder):
+    """The waves of a block add what they find of a long row to one word, and
+    leave the row when the word is complete: a wave's look at the word has to
+    lie a barrier before any wave's next addition."""
+    (code,) = [c for n, c in library_asm("spmm.hip", folder).items() if "bfs_step_kernel" in n]
+    assert any(ins.startswith("ds_or") for ins in code)
+    assert not adds_after_own_look(code)
