@@ -132,28 +132,10 @@ __global__ void __launch_bounds__(256, 8) spmm_units(const int64_t *__restrict__
   constexpr bool OLD = MODE == 1 || ACC;
   V *Y = reinterpret_cast<V *>(Yv);
   const int lane = lane_id();
-  const int32_t nch = (int32_t)((s + WAVE - 1) / WAVE);
   const int32_t wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
-  // turn t of this wave: the first own turns go to its XCD's chunks, the
-  // others to the chunks shared by all (every chunk when there are few)
-  const bool by_xcd = nch >= 8 && gridDim.x % 8 == 0;
-  const int32_t mine = by_xcd ? nunits * (nch / 8) : 0;
-  const int32_t w_own = (int32_t)(blockIdx.x / 8) * WPB + wv, st_own = (int32_t)(gridDim.x / 8) * WPB;
-  const int32_t c_all = by_xcd ? nch / 8 * 8 : 0;
-  const int32_t all = nunits * (nch - c_all);
-  const int32_t w_all = (int32_t)blockIdx.x * WPB + wv, st_all = (int32_t)gridDim.x * WPB;
-  int32_t t = w_own;
-  bool own = by_xcd;
-  if (!own) t = w_all;
-  for (;;) {
-    if (own && t >= mine) {
-      own = false;
-      t = w_all;
-    }
-    if (!own && t >= all) break;
-    const int32_t ch = t / nunits, un = t - ch * nunits;
-    const int32_t c = own ? (int32_t)(blockIdx.x % 8) + 8 * ch : c_all + ch;
-    t += own ? st_own : st_all;
+  UnitTurns turns(nunits, (int32_t)((s + WAVE - 1) / WAVE), gridDim.x, WPB, blockIdx.x, wv);
+  int32_t un, c;
+  while (turns.next(&un, &c)) {
     const int64_t i0 = ufirst[un];
     const int n = (int)(ufirst[un + 1] - i0);
     if (n == 0) continue;

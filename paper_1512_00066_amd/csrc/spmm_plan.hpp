@@ -37,6 +37,40 @@ struct SpmmPlan {
             int32_t *irow_p, int64_t *ibeg_p, int64_t *ufirst_p, int64_t *ipidx_p, void *partial_p, hipStream_t st);
 };
 
+// The (unit, chunk of 64 columns) pairs that one wave of a wide product takes.
+// With at least eight chunks the first turns go to the chunks of the wave's
+// XCD (block id mod 8) and the others to the chunks shared by all; with fewer
+// every chunk is shared.  There are fewer than 2^31 pairs and a turn advances
+// by at most the grid's waves, so unsigned numbers hold the turn past the last.
+struct UnitTurns {
+  uint32_t nunits, t, mine, all, st_own, st_all, w_all, shared, xcd;
+  bool own;
+  __host__ __device__ UnitTurns(uint32_t nunits_, uint32_t nch, uint32_t grid, uint32_t wpb, uint32_t block,
+                                uint32_t wave)
+      : nunits(nunits_), xcd(block % 8) {
+    own = nch >= 8 && grid % 8 == 0;
+    mine = own ? nunits * (nch / 8) : 0;
+    shared = own ? nch / 8 * 8 : 0;
+    all = nunits * (nch - shared);
+    st_own = grid / 8 * wpb;
+    st_all = grid * wpb;
+    w_all = block * wpb + wave;
+    t = own ? block / 8 * wpb + wave : w_all;
+  }
+  __host__ __device__ bool next(int32_t *unit, int32_t *chunk) {
+    if (own && t >= mine) {
+      own = false;
+      t = w_all;
+    }
+    if (!own && t >= all) return false;
+    const uint32_t ch = t / nunits;
+    *unit = (int32_t)(t - ch * nunits);
+    *chunk = (int32_t)(own ? xcd + 8 * ch : shared + ch);
+    t += own ? st_own : st_all;
+    return true;
+  }
+};
+
 // mode 0: Y = A (x) X (accumulate: Y (+)= A (x) X); mode 1: fixpoint step
 // Y = X (+) A (x) X raising *changed (and per-instance flags) on change.
 // In mode 1, rin (one byte per row, optional) limits the gathers to rows
