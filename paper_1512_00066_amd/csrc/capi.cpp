@@ -40,6 +40,19 @@ void Ctx::release_cache() {
   for (auto &v : free_blocks) v.clear();
 }
 
+// Gives the cache's unused blocks back; those in use stay (the call that found
+// no memory goes on with them).
+void Ctx::release_idle() {
+  (void)hipDeviceSynchronize();
+  for (auto &v : free_blocks) {
+    for (void *p : v) {
+      (void)hipFree(p);
+      block_class.erase(p);
+    }
+    v.clear();
+  }
+}
+
 void *Ctx::raw_alloc(size_t bytes, int kind) {
   if (bytes == 0) bytes = 1;
   void *p = nullptr;
@@ -47,7 +60,7 @@ void *Ctx::raw_alloc(size_t bytes, int kind) {
     p = alloc(user, bytes);
   } else if (kind == OUTPUT) {
     if (hipMalloc(&p, bytes) != hipSuccess) {
-      release_cache();
+      release_idle();
       if (hipMalloc(&p, bytes) != hipSuccess) p = nullptr;
     }
   } else {
@@ -62,7 +75,7 @@ void *Ctx::raw_alloc(size_t bytes, int kind) {
       free_blocks[c].pop_back();
     } else {
       if (hipMalloc(&p, (size_t)1 << c) != hipSuccess) {
-        release_cache();
+        release_idle();
         if (hipMalloc(&p, (size_t)1 << c) != hipSuccess) p = nullptr;
       }
       if (p) block_class[p] = c;

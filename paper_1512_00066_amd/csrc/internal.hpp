@@ -67,6 +67,7 @@ struct Ctx {
   KeptB keep_b;
   std::vector<BTable> b_tables;
   void release_cache();
+  void release_idle();
   void tracef(const char *fmt, ...);
   // per-kernel profile: HIP events around each launch on its stream, with
   // the launch's algorithmic bytes; resolved when queried
