@@ -56,12 +56,21 @@ void Ctx::release_idle() {
 void *Ctx::raw_alloc(size_t bytes, int kind) {
   if (bytes == 0) bytes = 1;
   void *p = nullptr;
+  // a refused request stays the thread's last error until it is read, and the
+  // next launch check would take it for the launch's
+  auto device_malloc = [&](size_t n) {
+    if (hipMalloc(&p, n) == hipSuccess) return true;
+    p = nullptr;
+    (void)hipGetLastError();
+    return false;
+  };
   if (alloc) {
     p = alloc(user, bytes);
+    if (!p) (void)hipGetLastError();  // the callback's own
   } else if (kind == OUTPUT) {
-    if (hipMalloc(&p, bytes) != hipSuccess) {
+    if (!device_malloc(bytes)) {
       release_idle();
-      if (hipMalloc(&p, bytes) != hipSuccess) p = nullptr;
+      device_malloc(bytes);
     }
   } else {
     if (cache_stream != stream) {
@@ -74,9 +83,9 @@ void *Ctx::raw_alloc(size_t bytes, int kind) {
       p = free_blocks[c].back();
       free_blocks[c].pop_back();
     } else {
-      if (hipMalloc(&p, (size_t)1 << c) != hipSuccess) {
+      if (!device_malloc((size_t)1 << c)) {
         release_idle();
-        if (hipMalloc(&p, (size_t)1 << c) != hipSuccess) p = nullptr;
+        device_malloc((size_t)1 << c);
       }
       if (p) block_class[p] = c;
     }

@@ -328,7 +328,8 @@ void gemm_launch(Ctx *c, const T *A, const T *B, T *C, int64_t M, int64_t N, int
   if (S > 1) {
     try {
       ws = Buf(c, sizeof(double) * (size_t)(S * batch) * (size_t)(M * N));
-    } catch (const Error &) {  // no room for the partial sums: one pass over k
+    } catch (const Error &e) {  // no room for the partial sums: one pass over k
+      if (e.st != SRTC_ERR_OOM) throw;
       S = 1;
       kchunk = K;
     }

@@ -397,7 +397,8 @@ void JacobiPlan::build(Ctx *c, int dt_, const CsrView &A_, hipStream_t s) {
       off = Buf(c, (wide ? sizeof(int32_t) : sizeof(int16_t)) * (size_t)cells);
       sval = Buf(c, es * (size_t)cells);
       slices = slices_;
-    } catch (const Error &) {
+    } catch (const Error &e) {
+      if (e.st != SRTC_ERR_OOM) throw;
       off = Buf();
       sval = Buf();
     }

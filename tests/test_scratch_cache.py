@@ -70,9 +70,31 @@ static int live_blocks_stay() {
   return 0;
 }
 
+static int error_is_read() {
+  Ctx c;
+  for (int kind : {(int)SCRATCH, (int)OUTPUT}) {
+    refuse = 1;
+    void *p = c.raw_alloc(3000, kind);
+    CHECK(p && hipGetLastError() == hipSuccess);
+    refuse = 2;
+    try { c.raw_alloc(1 << 20, kind); } catch (const Error &e) { CHECK(e.st == SRTC_ERR_OOM); p = nullptr; }
+    CHECK(!p && hipGetLastError() == hipSuccess);
+  }
+  // a callback that asks the runtime itself and is refused
+  c.alloc = [](void *, size_t n) -> void * {
+    void *p = nullptr;
+    return hipMalloc(&p, n) == hipSuccess ? p : nullptr;
+  };
+  refuse = 1;
+  void *p = &c;
+  try { p = c.raw_alloc(100, SCRATCH); } catch (const Error &e) { CHECK(e.st == SRTC_ERR_OOM); p = nullptr; }
+  CHECK(!p && hipGetLastError() == hipSuccess);
+  return 0;
+}
+
 int main(int argc, char **argv) {
   (void)argc;
-  return atoi(argv[1]) == 0 ? live_blocks_stay() : 2;
+  return atoi(argv[1]) == 0 ? live_blocks_stay() : error_is_read();
 }
 """
 
@@ -97,3 +119,7 @@ def run(program, which):
 
 def test_blocks_in_use_outlive_a_failed_allocation(program):
     run(program, 0)
+
+
+def test_a_refusal_is_not_left_for_the_next_launch_check(program):
+    run(program, 1)
