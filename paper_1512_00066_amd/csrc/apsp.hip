@@ -428,8 +428,8 @@ __global__ void apsp_out(const uint64_t *__restrict__ P, int64_t total, uint32_t
 // 64-bit round about 7x.
 constexpr double kDenseFracNarrow = 0.05, kDenseFracWide = 0.14;
 // Largest n whose 32-bit rounds encode their operands first (8 GB of words
-// beside the two path matrices' 16 GB); larger ones stage from P, whose own
-// size then decides what fits.
+// beside the two path matrices' 16 GB); larger ones, and those for whose words
+// there is no room, stage from P, whose own size then decides what fits.
 constexpr int64_t kEncodeMax = 32768;
 
 void apsp_tiskin(Ctx *c, const CsrView &A, int32_t idw, int32_t *D, int32_t *H, int32_t *rounds, int64_t *round_nnz,
@@ -472,6 +472,7 @@ void apsp_tiskin(Ctx *c, const CsrView &A, int32_t idw, int32_t *D, int32_t *H, 
   const int64_t tiles = ((n + DTM - 1) / DTM) * ((n + DTN - 1) / DTN);
   Buf part(c, 8 * (size_t)std::max<int64_t>({cnt_blocks, tiles, 1}));
   Buf words;  // encoded operands of the 32-bit rounds
+  bool encode = n <= kEncodeMax;
   bool counted = false;  // the previous dense round already counted this round's paths
   int32_t r = 0;
   if (round_nnz) std::fill(round_nnz, round_nnz + 64, (int64_t)0);
@@ -508,9 +509,16 @@ void apsp_tiskin(Ctx *c, const CsrView &A, int32_t idw, int32_t *D, int32_t *H, 
       const dim3 grid((unsigned)((n + DTN - 1) / DTN), (unsigned)((n + DTM - 1) / DTM));
       if (narrow) {
         const Narrow enc{(uint32_t)idw, hb};
-        if (n <= kEncodeMax) {
-          const int64_t ld = (n + 63) / 64 * 64;
-          if (!words.p) words = Buf(c, sizeof(uint32_t) * 2 * (size_t)(ld * ld));
+        const int64_t ld = (n + 63) / 64 * 64;
+        if (encode && !words.p) {
+          try {
+            words = Buf(c, sizeof(uint32_t) * 2 * (size_t)(ld * ld));
+          } catch (const Error &e) {  // no room for them: stage from P
+            if (e.st != SRTC_ERR_OOM) throw;
+            encode = false;
+          }
+        }
+        if (encode) {
           uint32_t *B = words.as<uint32_t>(), *Lt = B + ld * ld;
           const dim3 tg((unsigned)(ld / 64), (unsigned)(ld / 64));
           encode_tiles<<<tg, 256, 0, s>>>(P, n, ld, (uint32_t)l, enc, B, Lt);

@@ -9,6 +9,7 @@ import torch
 
 import oracle
 import paper_1512_00066_amd as srtc
+from gen import synth
 from gpu_common import say
 
 pytestmark = pytest.mark.gpu
@@ -76,3 +77,23 @@ def test_jacobi_without_the_copy_of_a():
     it, res = ctx.jacobi(A, torch.as_tensor(b, device="cuda"), x, tol=1e-9)
     assert ctx.refused > 0 and it == lo and res <= 1e-9
     assert np.all(np.abs(x.cpu().numpy() - xo) <= 1e-12 * (1 + np.abs(xo)))
+
+
+@pytest.mark.parametrize("n", [65, 130, 200])
+def test_path_doubling_without_encoded_operands(n):
+    """The 32-bit dense rounds from the path matrix itself."""
+    say("apsp without words", n)
+    src, dst, w = synth.dense_graph(n, 11, hi=50)
+    w = w.astype(np.int32)
+    O = oracle.fold("min_plus", "i32", dst, src, w, n, n)
+    A = srtc.csr_from_host(O.rowptr, O.col, O.val, (n, n))
+    Do, Ho, ro, _ = oracle.apsp_tiskin(O, inf_value=oracle.INT_INF)
+    ld = (n + 63) // 64 * 64
+    ctx = Limited()
+    for limit in (None, 8 * ld * ld - 1):  # the words take 8 ld^2 bytes, P and its successor 8 n^2 each
+        ctx.limit = limit
+        D, H, rounds = ctx.apsp_tiskin(A)
+        assert np.array_equal(D.cpu().numpy().astype(np.int64), Do)
+        assert np.array_equal(H.cpu().numpy().astype(np.int64), Ho)
+        assert rounds == ro
+    assert ctx.refused == 1
