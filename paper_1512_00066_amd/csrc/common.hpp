@@ -108,6 +108,14 @@ template <class T> __device__ __forceinline__ T lane63(T v) {
 // Sum over the 64 lanes (every lane gets it); all lanes must be active.
 template <class T> __device__ __forceinline__ T wave_sum(T v) { return lane63(wave_incl_scan(v)); }
 
+// Orders a wave's LDS accesses before and after it (no other wave is waited
+// for).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Block-wide exclusive scan for BS threads (BS a multiple of 64, <= 1024).
 // `tmp` is LDS of at least BS/64 + 1 elements.  Returns the exclusive prefix
 // and writes the block total to *total (every thread sees it).  With

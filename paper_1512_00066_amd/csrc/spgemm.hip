@@ -1559,14 +1559,6 @@ __device__ __forceinline__ int64_t write_kept(const typename SR::acc_t *vals, co
   return tot;
 }
 
-// Orders a wave's LDS accesses before and after it (no other wave is waited
-// for).
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 template <class SR, int BS, int LM>
 __global__ void __launch_bounds__(BS) masked_rows(const int64_t *__restrict__ rpA, const int32_t *__restrict__ cA,
                                                   const typename SR::val_t *__restrict__ vA,

@@ -116,22 +116,49 @@ __global__ void __launch_bounds__(256) slice_widths(const int64_t *__restrict__ 
 }
 
 // Columns as offsets from the row in C; rows shorter than their slice are
-// filled up with value 0 at offset 0 (the diagonal, which steps skip).
+// filled up with value 0 at offset 0 (the diagonal, which steps skip).  A wave
+// reads 16 consecutive entries of four rows at a time and turns them over
+// through LDS, so that reads and writes are whole lines.  Bound by its bytes:
+// stencil 100^3, fp64, 0.58 GB in 131 us (4.4 TB/s); with each lane reading a row of
+// its own 897 us, as much as the steps gain by the copy in 20 updates.
 template <class T, class C>
 __global__ void __launch_bounds__(256) slice_fill(const int64_t *__restrict__ rp, const int32_t *__restrict__ col,
                                                   const T *__restrict__ val, int64_t n, int64_t slices,
                                                   const int64_t *__restrict__ start, C *__restrict__ off,
                                                   T *__restrict__ sval) {
-  const int l = lane_id();
-  const int64_t nw = (int64_t)gridDim.x * blockDim.x / WAVE;
-  for (int64_t q = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / WAVE; q < slices; q += nw) {
-    const int64_t i = q * WAVE + l;
+  constexpr int KT = 16, RPL = WAVE / KT, WPB = 256 / WAVE;
+  __shared__ T tv[WPB][WAVE][KT + 1];
+  __shared__ C to[WPB][WAVE][KT + 1];
+  const int l = lane_id(), wv = threadIdx.x / WAVE, kl = l % KT, rl = l / KT;
+  const int64_t nw = (int64_t)gridDim.x * WPB;
+  for (int64_t q = (int64_t)blockIdx.x * WPB + wv; q < slices; q += nw) {
+    const int64_t i0 = q * WAVE, i = i0 + l;
     const int64_t a = i < n ? rp[i] : 0, len = i < n ? rp[i + 1] - a : 0;
     const int64_t s0 = start[q], w = start[q + 1] - s0;
-    for (int64_t k = 0; k < w; k++) {
-      const bool in = k < len;
-      off[(s0 + k) * WAVE + l] = in ? (C)(col[a + k] - i) : (C)0;
-      sval[(s0 + k) * WAVE + l] = in ? val[a + k] : (T)0;
+    for (int64_t k0 = 0; k0 < w; k0 += KT) {
+      T v[KT];
+      int32_t c[KT];
+#pragma unroll
+      for (int u = 0; u < KT; u++) {
+        const int r = u * RPL + rl;
+        const int64_t p = __shfl((long long)a, r, WAVE) + k0 + kl;
+        const bool in = k0 + kl < __shfl((long long)len, r, WAVE);
+        v[u] = in ? val[p] : (T)0;
+        c[u] = in ? col[p] : (int32_t)(i0 + r);
+      }
+#pragma unroll
+      for (int u = 0; u < KT; u++) {
+        const int r = u * RPL + rl;
+        tv[wv][r][kl] = v[u];
+        to[wv][r][kl] = (C)(c[u] - (i0 + r));
+      }
+      wave_sync();
+      const int kn = (int)min((int64_t)KT, w - k0);
+      for (int k = 0; k < kn; k++) {
+        off[(s0 + k0 + k) * WAVE + l] = to[wv][l][k];
+        sval[(s0 + k0 + k) * WAVE + l] = tv[wv][l][k];
+      }
+      wave_sync();
     }
   }
 }
@@ -348,7 +375,9 @@ void transform_dense_call(int op, int dt, double alpha, const int64_t *cext, int
 
 // Fewest slices of 64 rows that the steps take one row per lane: fewer leave
 // CUs without a wave (stencil 25^3, 244 slices: 15.3 us per update against
-// 8.9 with eight lanes per row; 50^3, 1,954: 14.8 against 16.7).
+// 8.9 with eight lanes per row; 50^3, 1,954: 14.8 against 16.7).  The copy is
+// made before the number of updates is known: it costs one update at this size
+// and two at 100^3 (131 us), where it pays from the fourth on.
 constexpr int64_t JAC_SLICES_MIN = 1024;
 
 void JacobiPlan::build(Ctx *c, int dt_, const CsrView &A_, hipStream_t s) {
@@ -363,12 +392,11 @@ void JacobiPlan::build(Ctx *c, int dt_, const CsrView &A_, hipStream_t s) {
   while (G < 64 && 4 * G < avg) G <<= 1;
   const size_t es = dtype_size(dt);
   dbuf = Buf(c, es * (size_t)std::max<int64_t>(n, 1));
-  // flags, then the slices' widths and starts
+  // the slices' starts, their end, and the two flags: one read has the last three
   const int64_t slices_ = (n + WAVE - 1) / WAVE;
-  Buf fw(c, sizeof(int64_t) * (size_t)(2 + slices_));
-  start = Buf(c, sizeof(int64_t) * (size_t)(slices_ + 1));
-  int64_t *flags = fw.as<int64_t>();
-  fill_i64(flags, 2, 0, s);
+  start = Buf(c, sizeof(int64_t) * (size_t)(slices_ + 3));
+  int64_t *flags = start.as<int64_t>() + slices_ + 1;
+  fill_i64(flags - 1, 3, 0, s);
   // slices for systems that fill the chip with one row per lane
   const bool want = slices_ >= JAC_SLICES_MIN;
   int64_t h[3] = {0, 0, 0};
@@ -380,19 +408,20 @@ void JacobiPlan::build(Ctx *c, int dt_, const CsrView &A_, hipStream_t s) {
       jacobi_diag<float><<<g, 256, 0, s>>>(A.rowptr, A.col, (const float *)A.val, n, dbuf.as<float>(), flags);
     SRTC_LAUNCH_CHECK("jacobi_diag");
     if (want) {
-      slice_widths<<<(unsigned)std::min<int64_t>((slices_ + 3) / 4, 8192), 256, 0, s>>>(A.rowptr, n, slices_, flags + 2);
+      Buf width(c, sizeof(int64_t) * (size_t)slices_);
+      slice_widths<<<(unsigned)std::min<int64_t>((slices_ + 3) / 4, 8192), 256, 0, s>>>(A.rowptr, n, slices_,
+                                                                                       width.as<int64_t>());
       SRTC_LAUNCH_CHECK("slice_widths");
-      excl_scan_i64(c, flags + 2, start.as<int64_t>(), slices_, s);
-      SRTC_HIP(hipMemcpyAsync(flags + 2, start.as<int64_t>() + slices_, sizeof(int64_t), hipMemcpyDeviceToDevice, s));
+      excl_scan_i64(c, width.as<int64_t>(), start.as<int64_t>(), slices_, s);
     }
-    read_to_host(c, h, flags, sizeof(int64_t) * (want ? 3 : 2), s);
-    if (h[0]) fail(SRTC_ERR_ARG, "Jacobi needs a nonzero diagonal entry in every row");
+    read_to_host(c, h, flags - 1, sizeof(h), s);
+    if (h[1]) fail(SRTC_ERR_ARG, "Jacobi needs a nonzero diagonal entry in every row");
   }
   // rows of much the same length: at most a quarter of padding; and room for
   // the copy
-  const int64_t cells = h[2] * WAVE;
+  const int64_t cells = h[0] * WAVE;
   if (want && 4 * cells <= 5 * A.nnz) {
-    wide = h[1] != 0;
+    wide = h[2] != 0;
     try {
       off = Buf(c, (wide ? sizeof(int32_t) : sizeof(int16_t)) * (size_t)cells);
       sval = Buf(c, es * (size_t)cells);
@@ -404,6 +433,7 @@ void JacobiPlan::build(Ctx *c, int dt_, const CsrView &A_, hipStream_t s) {
     }
   }
   if (slices > 0) {
+    ProfScope ps(c, "jacobi.slice_copy", (4.0 + es) * (double)A.nnz + ((wide ? 4.0 : 2.0) + es) * (double)cells, s);
     const unsigned g = (unsigned)std::min<int64_t>((slices + 3) / 4, 16384);
     if (dt == SRTC_F64 && wide)
       slice_fill<double, int32_t><<<g, 256, 0, s>>>(A.rowptr, A.col, (const double *)A.val, n, slices,
