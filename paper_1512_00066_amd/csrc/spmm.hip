@@ -67,7 +67,7 @@ __global__ void items_fill(const int64_t *rp, int64_t m, int64_t T, const int64_
 // First item of every unit: items are cut into units of about `cost` work,
 // an item counting its nonzeros plus UNIT_ITEM.  Unit w starts at the first
 // item whose preceding work reaches w cost; ufirst[nunits] = nitems.  With
-// cost = T + UNIT_ITEM and T <= 256 a unit has at most 53 items, one per lane.
+// cost <= T + UNIT_ITEM and T <= 256 a unit has at most 53 items, one per lane.
 constexpr int64_t UNIT_ITEM = 5;
 constexpr int T_MAX = 256;  // most nonzeros of an item (a grain as long is never reached)
 __global__ void units_fill(const int64_t *__restrict__ ibeg, const int64_t *__restrict__ nitems_p, int64_t cost,
@@ -632,8 +632,22 @@ void SpmmPlan::shape(Ctx *c, const CsrView &A, int64_t s_width) {
   max_partial = 2 * (A.nnz / T) + 1;
   may_split = true;
   grid_cap = (int64_t)c->num_cus * 16;
-  // units of one full item's work; their table fits where max_items entries do
-  nunits = G == WAVE ? (A.nnz + UNIT_ITEM * max_items) / (T + UNIT_ITEM) + 1 : 0;
+  // Units of wide products: a full item's work each, or less where that would
+  // not give every resident wave a unit (8,192 waves; product alone, 64
+  // columns fp64: 10,000 rows of 10 nonzeros 29 us with full units, 15 so, 18
+  // with one wave per row; 1,000 rows 42, 9 and 9).  Smaller units for the
+  // larger products too, two to four turns of each wave, cost R-MAT 18 with 64
+  // sources 3 to 9% and gained at most 4% on even rows.  The units' table fits
+  // where max_items entries do.
+  nunits = 0;
+  if (G < WAVE || batched) return;
+  const int64_t work = A.nnz + UNIT_ITEM * max_items, nch = (s_width + WAVE - 1) / WAVE;
+  const int64_t full = T + UNIT_ITEM, resident = (int64_t)c->num_cus * 32;
+  const double each = (double)work * (double)nch / (double)resident;
+  ucost = (int64_t)std::min((double)full, std::max(each, 16.0));
+  // (at least the average item's work)
+  ucost = std::max(ucost, work / max_items + 2);
+  nunits = work / ucost + 1;
   if (nunits + 1 > max_items) nunits = 0;
 }
 
@@ -652,7 +666,7 @@ void SpmmPlan::fill(const CsrView &A, int64_t *cnt_p, int64_t *pcnt_p, int64_t *
     items_fill<<<gridn(m), 256, 0, st>>>(A.rowptr, m, T, ioff_p, poff_p, irow_p, ibeg_p, ipidx_p);
     SRTC_LAUNCH_CHECK("items_fill");
     if (nunits > 0) {
-      units_fill<<<gridn(nunits + 1), 256, 0, st>>>(ibeg_p, ioff_p + m, T + UNIT_ITEM, nunits, ufirst_p);
+      units_fill<<<gridn(nunits + 1), 256, 0, st>>>(ibeg_p, ioff_p + m, ucost, nunits, ufirst_p);
       SRTC_LAUNCH_CHECK("units_fill");
     }
   }

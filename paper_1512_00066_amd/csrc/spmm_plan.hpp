@@ -20,6 +20,7 @@ struct SpmmPlan {
   const int64_t *ibeg = nullptr, *ufirst = nullptr, *ipidx = nullptr, *nitems = nullptr;
   void *partial = nullptr;
   int64_t rows = 0;         // rows of A
+  int64_t ucost = 0;        // work of a unit: nonzeros and a constant per item
   int64_t nunits = 0;       // units of items taken by one wave each (0: none)
   int64_t max_partial = 0;  // rows of s_width accumulators for split rows
   // item length, lanes per item and buffer sizes for A and s_width
