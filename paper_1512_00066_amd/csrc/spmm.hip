@@ -133,7 +133,7 @@ __global__ void __launch_bounds__(256, 8) spmm_units(const int64_t *__restrict__
   V *Y = reinterpret_cast<V *>(Yv);
   const int lane = lane_id();
   const int32_t wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE));
-  UnitTurns turns(nunits, (int32_t)((s + WAVE - 1) / WAVE), gridDim.x, WPB, blockIdx.x, wv);
+  UnitTurns turns(nunits, (int32_t)((s + WAVE - 1) / WAVE), gridDim.x, WPB, blockIdx.x, wv, s * sizeof(V) % 128 != 0);
   int32_t un, c;
   while (turns.next(&un, &c)) {
     const int64_t i0 = ufirst[un];
