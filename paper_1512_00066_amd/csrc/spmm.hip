@@ -360,15 +360,20 @@ __global__ void __launch_bounds__(256) spmm_items(const int32_t *__restrict__ ir
   }
 }
 
-// Rows split into several items: combine partials in item order.  A wave
-// looks at 64 items at a time for first items of split rows (few rows are
-// split; with one item per look the search took 31 us of an R-MAT 18 step)
-// and then takes each such row, one lane per column, eight partials in
-// flight.
-template <class SR, int MODE, bool ACC>
+// Rows split into several items: combine partials in item order.  A wave looks
+// at `look` (up to 64) items at a time for first items of split rows, brings
+// those it found to its first lanes, and each group of G lanes (one per
+// column) takes one of them, eight partials in flight.  With one item per look
+// the search through many unsplit rows took 31 us of an R-MAT 18 step; with 64
+// items per look always, and one row after the other in one lane per column,
+// small products and narrow ones, where most rows are split, took up to twice
+// the time (product alone, fp64, so / now / with one item per look: 1,000 rows
+// of 100 nonzeros x 1 column 29 / 14 / 13 us; 100,000 of 40 x 1 83 / 48 / 48;
+// 20,000 of 80 x 32 112 / 88 / 90; 300 of 1,000 x 64 59 / 36 / 45).
+template <class SR, int G, int MODE, bool ACC>
 __global__ void __launch_bounds__(256) spmm_combine(const int32_t *__restrict__ irow, const int64_t *__restrict__ ibeg,
                                                     const int64_t *__restrict__ ipidx, const int64_t *__restrict__ nitems_p,
-                                                    const int64_t *__restrict__ rp, int64_t T,
+                                                    int look, const int64_t *__restrict__ rp, int64_t T,
                                                     const typename SR::val_t *__restrict__ X, int64_t s,
                                                     void *__restrict__ Yv, const typename SR::acc_t *__restrict__ P,
                                                     typename SR::acc_t id, int32_t *changed,
@@ -377,30 +382,43 @@ __global__ void __launch_bounds__(256) spmm_combine(const int32_t *__restrict__ 
                                                     uint8_t *__restrict__ rout) {
   using V = typename SR::val_t;
   using A = typename SR::acc_t;
-  constexpr int U = 8;
+  constexpr int U = 8, PER_WAVE = WAVE / G;
   V *Y = reinterpret_cast<V *>(Yv);
   const int64_t nitems = *nitems_p;
   const int lane = lane_id();
   const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
   const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) / WAVE;
-  // (64 items, chunk of 64 columns) per turn
-  const int64_t nch = (s + WAVE - 1) / WAVE, groups = (nitems + WAVE - 1) / WAVE;
-  for (int64_t g = wave; g < groups * nch; g += nwaves) {
-    const int64_t it = g / nch * WAVE + lane;
+  // (`look` items, chunk of G columns) per turn
+  const int64_t nch = (s + G - 1) / G, looks = (nitems + look - 1) / look;
+  for (int64_t g = wave; g < looks * nch; g += nwaves) {
+    const int64_t it = g / nch * look + lane;
     int64_t pi0 = -1;
     int32_t row0 = 0;
-    if (it < nitems) {
+    if (lane < look && it < nitems) {
       pi0 = ipidx[it];
       row0 = irow[it];
       if (pi0 >= 0 && ibeg[it] != rp[row0]) pi0 = -1;  // only the first item of a split row
     }
-    const int64_t col = g % nch * WAVE + lane;
-    for (uint64_t mk = __ballot(pi0 >= 0); mk; mk &= mk - 1) {
-      const int src = __ffsll((unsigned long long)mk) - 1;
-      const int64_t pi = lane_value(pi0, src);
-      const int64_t row = lane_value(row0, src);
+    const uint64_t mk = __ballot(pi0 >= 0);
+    const int found = __popcll(mk);
+    if (found == 0) continue;
+    if (G < WAVE) {
+      // found rows to lanes 0 .. found-1 (the others' values behind them)
+      const int below = __popcll(mk & lanemask_lt());
+      const int to = 4 * (pi0 >= 0 ? below : found + lane - below);
+      const uint32_t lo = __builtin_amdgcn_ds_permute(to, (int)(uint32_t)pi0);
+      const uint32_t hi = __builtin_amdgcn_ds_permute(to, (int)(uint32_t)(pi0 >> 32));
+      pi0 = (int64_t)((uint64_t)hi << 32 | lo);
+      row0 = __builtin_amdgcn_ds_permute(to, row0);
+    }
+    const int64_t col = g % nch * G + lane % G;
+    uint64_t left = mk;
+    for (int t = 0; t < found; t += PER_WAVE, left &= left - 1) {
+      const int src = G < WAVE ? t + lane / G : __ffsll((unsigned long long)left) - 1;
+      const int64_t pi = G < WAVE ? (int64_t)__shfl((long long)pi0, src, WAVE) : lane_value(pi0, src);
+      const int64_t row = G < WAVE ? __shfl(row0, src, WAVE) : lane_value(row0, src);
+      if (src >= (G < WAVE ? found : WAVE) || col >= s) continue;
       if (MODE == 1 && row_inst && !inst_active[row_inst[row]]) continue;
-      if (col >= s) continue;
       const int64_t cnt = (rp[row + 1] - rp[row] + T - 1) / T;
       A acc = id;
       for (int64_t t = 0; t < cnt; t += U) {
@@ -467,11 +485,14 @@ void run_items(const SpmmPlan &pl, const CsrView &A, const void *X, int64_t s, v
     SRTC_LAUNCH_CHECK("spmm_items");
   }
   if (pl.may_split) {
-    const int64_t cw = (pl.max_items + WAVE - 1) / WAVE * ((s + WAVE - 1) / WAVE);
+    // fewer items per look while that gives more waves than the chip holds
+    int look = WAVE;
+    while (look > WAVE / G && (pl.max_items + look - 1) / look * nch < 2 * pl.grid_cap) look /= 2;
+    const int64_t cw = (pl.max_items + look - 1) / look * nch;
     const unsigned gc = (unsigned)std::max<int64_t>(1, std::min<int64_t>((cw + 3) / 4, pl.grid_cap));
-    spmm_combine<SR, MODE, ACC><<<gc, 256, 0, st>>>(pl.irow, pl.ibeg, pl.ipidx, pl.nitems, A.rowptr, pl.T,
-                                                    (const V *)X, s, Y, (const Acc *)pl.partial, id, changed, row_inst,
-                                                    inst_active, inst_changed, rout);
+    spmm_combine<SR, G, MODE, ACC><<<gc, 256, 0, st>>>(pl.irow, pl.ibeg, pl.ipidx, pl.nitems, look, A.rowptr, pl.T,
+                                                       (const V *)X, s, Y, (const Acc *)pl.partial, id, changed, row_inst,
+                                                       inst_active, inst_changed, rout);
     SRTC_LAUNCH_CHECK("spmm_combine");
   }
 }

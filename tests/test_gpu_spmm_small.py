@@ -40,3 +40,38 @@ def test_wide_products_of_few_short_rows(ctx, m):
     A = uniform(m, 2000, 10, m)
     narrow, wide = product_time(ctx, A, 32), product_time(ctx, A, 64)
     assert wide <= 2.5 * narrow, (narrow, wide)
+
+
+@pytest.mark.parametrize("m", [1000, 3000])
+def test_narrow_products_of_split_rows(ctx, m):
+    """One column: 100 nonzeros a row are four items and a combination, 32 are
+    one item; the items run side by side and the combination is one more short
+    launch."""
+    say("narrow split rows", m)
+    whole, split = (product_time(ctx, uniform(m, 2000, d, m), 1) for d in (32, 100))
+    assert split <= 2.5 * whole, (whole, split)
+
+
+@pytest.mark.parametrize("width", [1, 2, 3, 8, 16, 31, 32, 33, 64])
+@pytest.mark.parametrize("m", [5, 700, 9000])
+def test_split_rows_of_every_share(ctx, m, width):
+    """Runs of split and whole rows of all lengths, combined by groups of 1 to
+    64 lanes: integer values, so sums are equal whatever their order."""
+    say("split rows", m, width)
+    g = torch.Generator().manual_seed(m + width)
+    k = 900
+    ln = torch.randint(0, 40, (m,), generator=g)
+    ln[torch.rand(m, generator=g) < 0.4] = 33
+    ln[m // 2: m // 2 + 3] = torch.tensor([64, 900, 257])[: len(ln[m // 2: m // 2 + 3])]
+    rp = torch.cat([torch.zeros(1, dtype=torch.int64), torch.cumsum(ln, 0)])
+    col = torch.cat([torch.randperm(k, generator=g)[:int(x)].sort().values for x in ln])
+    val = torch.randint(1, 9, (int(rp[-1]),), generator=g).double()
+    X = torch.randint(1, 9, (k, width), generator=g).double()
+    dense = torch.zeros((m, k), dtype=torch.float64)
+    dense[torch.repeat_interleave(torch.arange(m), ln), col] = val
+    A = srtc.CSR(rp.cuda(), col.int().cuda(), val.cuda(), (m, k))
+    Y = torch.empty((m, width), dtype=torch.float64, device="cuda")
+    ctx.contract("plus_times", "ik", A, "kj", X.cuda(), "ij", C=Y)
+    assert torch.equal(Y.cpu(), dense @ X)
+    ctx.contract("plus_times", "ik", A, "kj", X.cuda(), "ij", C=Y, accumulate=True)
+    assert torch.equal(Y.cpu(), 2 * (dense @ X))
