@@ -352,73 +352,170 @@ void radix_sort(Ctx *c, const uint64_t *kin, const P *pin, const KeyMap &km, int
 // which combines it in sorted (= input) order.  Two passes over the sorted
 // pairs, one to count each tile's kept segments and one to write them: the
 // second forms the results again, which reads less than storing them would.
+// A tile's last segment may run on past the tile: the count pass then brings
+// the rest through LDS, a tile's worth at a time by the whole block and the
+// next on its way while the segment's thread adds this one, and leaves the
+// result for the write pass.  What bounds a long segment is the chain of its
+// additions, 31 ns each (2^20 entries of one key, fp32: 146 ms by one thread
+// with the bounds known, 329 ms in two passes with a test of each key, 31.5 ms
+// so; 2^22 entries, 300 a key, 548, 677 and 359 us).
 constexpr int SG_BS = 256, SG_IT = 8, SG_TILE = SG_BS * SG_IT, SG_NW = SG_BS / WAVE;
+constexpr int SG_WORDS = SG_TILE / WAVE;
 
-// A tile in LDS (entry r of thread t is position r*SG_BS + t); key 0 is the
-// entry's before the tile.
-template <class SR> struct SegTile {
+// A tile's values in LDS, with KEYS its keys too (entry r of thread t is
+// position r*SG_BS + t; key 0 is the entry's before the tile).  load leaves in
+// mask[r] the first entries of segments among the wave's 64 of round r.
+template <class SR, bool KEYS> struct SegTile {
   using V = typename SR::val_t;
-  uint64_t key[SG_TILE + 1];
+  using A = typename SR::acc_t;
+  uint64_t key[KEYS ? SG_TILE + 1 : 1];
   V val[SG_TILE];
+  uint64_t heads[SG_WORDS];  // first entries of segments, by position
+  uint64_t last;             // key of a whole tile's last entry
+  int32_t runs_on;           // its segment goes on after the tile
   __device__ __forceinline__ void load(const uint64_t *__restrict__ keys, const V *__restrict__ vals, int64_t n,
-                                       int64_t base, int cnt) {
-    uint64_t k[SG_IT];
+                                       int64_t base, int cnt, uint64_t *mask) {
+    const int t = threadIdx.x;
+    uint64_t k[SG_IT], before[SG_IT], next = 0;
     V v[SG_IT];
 #pragma unroll
     for (int r = 0; r < SG_IT; r++) {
-      const int64_t i = base + min(r * SG_BS + (int)threadIdx.x, cnt - 1);
+      const int64_t i = base + min(r * SG_BS + t, cnt - 1);
       k[r] = keys[i];
       v[r] = vals[i];
+      before[r] = lane_id() == 0 && i > 0 ? keys[i - 1] : 0;
     }
+    const bool ends = t == SG_BS - 1 && base + cnt < n;
+    if (ends) next = keys[base + cnt];
 #pragma unroll
     for (int r = 0; r < SG_IT; r++) {
-      key[1 + r * SG_BS + threadIdx.x] = k[r];
-      val[r * SG_BS + threadIdx.x] = v[r];
+      const int p = r * SG_BS + t;
+      if (KEYS) key[1 + p] = k[r];
+      val[p] = v[r];
+      const uint64_t left = dpp_move<0x138, 0xf>(k[r]);  // wave_shr:1
+      mask[r] = __ballot(p < cnt && (base + p == 0 || (lane_id() == 0 ? before[r] : left) != k[r]));
+      if (lane_id() == 0) heads[r * SG_NW + t / WAVE] = mask[r];
     }
-    if (threadIdx.x == 0 && base > 0) key[0] = keys[base - 1];
+    if (KEYS && t == 0) key[0] = before[0];
+    if (t == SG_BS - 1) {
+      last = k[SG_IT - 1];
+      runs_on = ends && next == k[SG_IT - 1];
+    }
     __syncthreads();
   }
-  __device__ __forceinline__ bool head(int64_t base, int p) const {
-    return base + p == 0 || key[p] != key[p + 1];
+  // End within the tile of the segment that starts at this thread's entry p,
+  // whose word of heads is m.
+  __device__ __forceinline__ int end_of(uint64_t m, int p, int cnt) const {
+    m = m >> lane_id() >> 1;
+    if (m) return p + __ffsll((unsigned long long)m);
+    for (int w = p / WAVE + 1; w * WAVE < cnt; w++) {
+      m = heads[w];
+      if (m) return w * WAVE + __ffsll((unsigned long long)m) - 1;
+    }
+    return cnt;
   }
-  // Result of the segment that starts at p; false if it is dropped.
-  __device__ __forceinline__ bool combine(const uint64_t *__restrict__ keys, const V *__restrict__ vals, int64_t n,
-                                          int64_t base, int cnt, int p, typename SR::acc_t id, V *o) const {
-    using A = typename SR::acc_t;
-    A acc = id;
-    bool any = false;
+  // Adds entries p .. e-1 to a segment's sum.
+  __device__ __forceinline__ void add(int p, int e, A id, A *acc, bool *any) const {
     auto take = [&](V v) {
       if (SR::absent(v, id)) return;
       const A x = SR::HAS_VALS ? (A)v : (A)1;
-      acc = any ? SR::add(acc, x) : x;
-      any = true;
+      *acc = *any ? SR::add(*acc, x) : x;
+      *any = true;
     };
-    const uint64_t k = key[p + 1];
-    take(val[p]);
-    int q = p + 1;
-    for (; q < cnt && key[q + 1] == k; q++) take(val[q]);
-    if (q == cnt)
-      for (int64_t j = base + cnt; j < n && keys[j] == k; j++) take(vals[j]);
-    *o = SR::out(acc);
-    return any && !SR::absent(*o, id);
+    if (p < e) take(val[p++]);  // most segments are one entry
+    for (; p + 8 <= e; p += 8) {
+      V v[8];
+#pragma unroll
+      for (int u = 0; u < 8; u++) v[u] = val[p + u];
+#pragma unroll
+      for (int u = 0; u < 8; u++) take(v[u]);
+    }
+    for (; p < e; p += 4) {
+      V v[4];
+#pragma unroll
+      for (int u = 0; u < 4; u++) v[u] = val[min(p + u, e - 1)];
+#pragma unroll
+      for (int u = 0; u < 4; u++)
+        if (p + u < e) take(v[u]);
+    }
   }
 };
 
+// run_val, run_keep [tile]: result of the segment that runs on past the tile,
+// and whether it is kept.
 template <class SR>
 __global__ void __launch_bounds__(SG_BS) seg_count(const uint64_t *__restrict__ keys,
                                                    const typename SR::val_t *__restrict__ vals, int64_t n,
-                                                   typename SR::acc_t id, int32_t *__restrict__ tcnt) {
+                                                   typename SR::acc_t id, int32_t *__restrict__ tcnt,
+                                                   typename SR::val_t *__restrict__ run_val,
+                                                   int32_t *__restrict__ run_keep) {
+  using V = typename SR::val_t;
+  using A = typename SR::acc_t;
   __shared__ int32_t cw[SG_NW];
   const int64_t base = (int64_t)blockIdx.x * SG_TILE;
   const int cnt = (int)min((int64_t)SG_TILE, n - base);
-  __shared__ SegTile<SR> T;
-  T.load(keys, vals, n, base, cnt);
+  __shared__ SegTile<SR, false> T;
+  uint64_t mask[SG_IT];
+  T.load(keys, vals, n, base, cnt, mask);
   int32_t kept = 0;
+  bool mine = false, run_any = false;  // this thread's segment runs on: its sum so far
+  A run_acc = id;
 #pragma unroll
   for (int r = 0; r < SG_IT; r++) {
     const int p = r * SG_BS + threadIdx.x;
-    typename SR::val_t o;
-    if (p < cnt && T.head(base, p) && T.combine(keys, vals, n, base, cnt, p, id, &o)) kept++;
+    if (!((mask[r] >> lane_id()) & 1)) continue;
+    A acc = id;
+    bool any = false;
+    const int e = T.end_of(mask[r], p, cnt);
+    T.add(p, e, id, &acc, &any);
+    if (e == cnt && T.runs_on) {
+      mine = true;
+      run_any = any;
+      run_acc = acc;
+    } else if (any && !SR::absent(SR::out(acc), id)) {
+      kept++;
+    }
+  }
+  if (T.runs_on && __syncthreads_or(mine)) {  // (no thread's where the tile lies inside a segment)
+    const uint64_t k = T.last;
+    int64_t at = base + SG_TILE;
+    V v[SG_IT];
+    int same;
+    // entries at, at + 1, ... with the same key, up to a tile's worth: values
+    // in v, their number in `same` of each thread
+    auto fetch = [&]() {
+      same = 0;
+#pragma unroll
+      for (int r = 0; r < SG_IT; r++) {
+        const int64_t i = min(at + r * SG_BS + (int)threadIdx.x, n - 1);
+        v[r] = vals[i];
+        same += at + r * SG_BS + threadIdx.x < n && keys[i] == k ? 1 : 0;
+      }
+      at += SG_TILE;
+    };
+    fetch();
+    for (bool more = true; more;) {
+      // (the barrier of the count ends the reading of the values before)
+      const int w = wave_sum(same);
+      if (lane_id() == 0) cw[threadIdx.x / WAVE] = w;
+      __syncthreads();
+      int len = 0;
+      for (int q = 0; q < SG_NW; q++) len += cw[q];
+#pragma unroll
+      for (int r = 0; r < SG_IT; r++) T.val[r * SG_BS + threadIdx.x] = v[r];
+      more = len == SG_TILE;
+      __syncthreads();
+      if (more) fetch();
+      if (mine) T.add(0, len, id, &run_acc, &run_any);
+    }
+    if (mine) {
+      const V o = SR::out(run_acc);
+      const bool keep = run_any && !SR::absent(o, id);
+      run_val[blockIdx.x] = o;
+      run_keep[blockIdx.x] = keep;
+      kept += keep;
+    }
+    __syncthreads();
   }
   kept = wave_sum(kept);
   if (lane_id() == 0) cw[threadIdx.x / WAVE] = kept;
@@ -437,23 +534,38 @@ template <class SR>
 __global__ void __launch_bounds__(SG_BS) seg_write(const uint64_t *__restrict__ keys,
                                                    const typename SR::val_t *__restrict__ vals, int64_t n,
                                                    typename SR::acc_t id, const int64_t *__restrict__ toff,
-                                                   int64_t nrows, uint64_t ncols, uint64_t magic,
-                                                   int32_t *__restrict__ col, typename SR::val_t *__restrict__ val,
-                                                   int64_t *__restrict__ rowptr) {
-  __shared__ int32_t cw[SG_IT * SG_NW];
+                                                   const typename SR::val_t *__restrict__ run_val,
+                                                   const int32_t *__restrict__ run_keep, int64_t nrows, uint64_t ncols,
+                                                   uint64_t magic, int32_t *__restrict__ col,
+                                                   typename SR::val_t *__restrict__ val, int64_t *__restrict__ rowptr) {
+  using A = typename SR::acc_t;
+  __shared__ int32_t cw[SG_WORDS];
   const int w = threadIdx.x / WAVE;
   const int64_t base = (int64_t)blockIdx.x * SG_TILE;
   const int cnt = (int)min((int64_t)SG_TILE, n - base);
-  __shared__ SegTile<SR> T;
-  T.load(keys, vals, n, base, cnt);
+  __shared__ SegTile<SR, true> T;
+  uint64_t mask[SG_IT];
+  T.load(keys, vals, n, base, cnt, mask);
   typename SR::val_t o[SG_IT];
   uint32_t below[SG_IT];
   uint32_t heads = 0, kept = 0;
 #pragma unroll
   for (int r = 0; r < SG_IT; r++) {
     const int p = r * SG_BS + threadIdx.x;
-    const bool head = p < cnt && T.head(base, p);
-    const bool k = head && T.combine(keys, vals, n, base, cnt, p, id, &o[r]);
+    const bool head = (mask[r] >> lane_id()) & 1;
+    bool k = false;
+    if (head) {
+      const int e = T.end_of(mask[r], p, cnt);
+      if (e == cnt && T.runs_on) {
+        o[r] = run_val[blockIdx.x];
+        k = run_keep[blockIdx.x] != 0;
+      } else {
+        A acc = id;
+        T.add(p, e, id, &acc, &k);
+        o[r] = SR::out(acc);
+        k = k && !SR::absent(o[r], id);
+      }
+    }
     heads |= head ? 1u << r : 0;
     kept |= k ? 1u << r : 0;
     const uint64_t m = __ballot(k);
@@ -462,10 +574,10 @@ __global__ void __launch_bounds__(SG_BS) seg_write(const uint64_t *__restrict__ 
   }
   __syncthreads();
   if (w == 0) {
-    static_assert(SG_IT * SG_NW <= WAVE, "one wave scans the tile's counts");
-    const int32_t x = lane_id() < SG_IT * SG_NW ? cw[lane_id()] : 0;
+    static_assert(SG_WORDS <= WAVE, "one wave scans the tile's counts");
+    const int32_t x = lane_id() < SG_WORDS ? cw[lane_id()] : 0;
     const int32_t inc = wave_incl_scan(x);
-    if (lane_id() < SG_IT * SG_NW) cw[lane_id()] = inc - x;
+    if (lane_id() < SG_WORDS) cw[lane_id()] = inc - x;
   }
   __syncthreads();
   const int64_t t0 = toff[blockIdx.x];
@@ -512,20 +624,23 @@ inline unsigned grid_for(int64_t n, int bs = 256, int64_t cap = 65536) {
 }
 
 template <class SR>
-void seg_count_launch(const uint64_t *keys, const void *vals, int64_t n, IdVal id, int32_t *tcnt, hipStream_t s) {
-  seg_count<SR><<<(unsigned)((n + SG_TILE - 1) / SG_TILE), SG_BS, 0, s>>>(keys, (const typename SR::val_t *)vals, n,
-                                                                          id_as<SR>(id), tcnt);
+void seg_count_launch(const uint64_t *keys, const void *vals, int64_t n, IdVal id, int32_t *tcnt, void *run_val,
+                      int32_t *run_keep, hipStream_t s) {
+  seg_count<SR><<<(unsigned)((n + SG_TILE - 1) / SG_TILE), SG_BS, 0, s>>>(
+      keys, (const typename SR::val_t *)vals, n, id_as<SR>(id), tcnt, (typename SR::val_t *)run_val, run_keep);
   SRTC_LAUNCH_CHECK("seg_count");
 }
 
 uint64_t magic_of(uint64_t d) { return ~(uint64_t)0 / std::max<uint64_t>(d, 1); }
 
 template <class SR>
-void seg_write_launch(const uint64_t *keys, const void *vals, int64_t n, IdVal id, const int64_t *toff, int64_t nrows,
-                      int64_t ncols, int32_t *col, void *val, int64_t *rowptr, hipStream_t s) {
+void seg_write_launch(const uint64_t *keys, const void *vals, int64_t n, IdVal id, const int64_t *toff,
+                      const void *run_val, const int32_t *run_keep, int64_t nrows, int64_t ncols, int32_t *col, void *val,
+                      int64_t *rowptr, hipStream_t s) {
+  using V = typename SR::val_t;
   seg_write<SR><<<(unsigned)((n + SG_TILE - 1) / SG_TILE), SG_BS, 0, s>>>(
-      keys, (const typename SR::val_t *)vals, n, id_as<SR>(id), toff, nrows, (uint64_t)ncols, magic_of((uint64_t)ncols),
-      col, (typename SR::val_t *)val, rowptr);
+      keys, (const V *)vals, n, id_as<SR>(id), toff, (const V *)run_val, run_keep, nrows, (uint64_t)ncols,
+      magic_of((uint64_t)ncols), col, (V *)val, rowptr);
   SRTC_LAUNCH_CHECK("seg_write");
 }
 
@@ -607,15 +722,17 @@ void fold_keys_to_csr(Ctx *c, int sr, int dt, IdVal id, const KeyMap *map, const
   const void *sval = passes % 2 ? vbuf.p : (const void *)(vbuf.as<char>() + es * (size_t)nnz * (two - 1));
   // segments of equal keys
   const int64_t nst = (nnz + SG_TILE - 1) / SG_TILE;
-  Buf toff(c, sizeof(int64_t) * (size_t)(nst + 1)), tcnt(c, sizeof(int32_t) * (size_t)nst);
-  SRTC_DISPATCH_SR(sr, dt, seg_count_launch, keys, sval, nnz, id, tcnt.as<int32_t>(), s);
-  excl_scan_i32(c, tcnt.as<int32_t>(), toff.as<int64_t>(), nst, s);
+  // per tile: first place, count, and the segment that runs on
+  Buf toff(c, sizeof(int64_t) * (size_t)(nst + 1)), run(c, (8 + 2 * sizeof(int32_t)) * (size_t)nst);
+  int32_t *tcnt = reinterpret_cast<int32_t *>(run.as<char>() + 8 * (size_t)nst), *run_keep = tcnt + nst;
+  SRTC_DISPATCH_SR(sr, dt, seg_count_launch, keys, sval, nnz, id, tcnt, run.p, run_keep, s);
+  excl_scan_i32(c, tcnt, toff.as<int64_t>(), nst, s);
   const int64_t total = read_i64(c, toff.as<int64_t>() + nst, s);
   c->tracef("fold: %lld entries after combining duplicates", (long long)total);
   out->nnz = total;
   out->col = Buf(c, sizeof(int32_t) * (size_t)(total > 0 ? total : 1), out->kind);
   out->val = Buf(c, es * (size_t)(total > 0 ? total : 1), out->kind);
-  SRTC_DISPATCH_SR(sr, dt, seg_write_launch, keys, sval, nnz, id, toff.as<int64_t>(), nrows, ncols,
+  SRTC_DISPATCH_SR(sr, dt, seg_write_launch, keys, sval, nnz, id, toff.as<int64_t>(), run.p, run_keep, nrows, ncols,
                    out->col.as<int32_t>(), out->val.p, out->rowptr.as<int64_t>(), s);
 }
 
