@@ -332,11 +332,13 @@ __global__ void __launch_bounds__(1024) bin_small(const int64_t *__restrict__ v,
 
 // The numeric layout of up to BIN_SMALL rows in one launch: C's row pointers
 // (the exclusive scan of the rows' output counts), the bins and their lists,
-// and a copy of the output size and the bin table for the host, written to
-// its pinned memory (read after the stream has been waited for).
+// and, for the host, written to its pinned memory (read after the stream has
+// been waited for), the output size, the bin table, and, if there are rows for
+// the dense windows, the sum and the largest of the rows' product counts w.
 template <bool SUMS>
-__global__ void __launch_bounds__(1024) small_layout(const int64_t *__restrict__ v, int64_t m, Thresholds th,
-                                                     const int64_t *__restrict__ rpA, int64_t *__restrict__ rowptr,
+__global__ void __launch_bounds__(1024) small_layout(const int64_t *__restrict__ v, const int64_t *__restrict__ w,
+                                                     int64_t m, Thresholds th, const int64_t *__restrict__ rpA,
+                                                     int64_t *__restrict__ rowptr,
                                                      int64_t *__restrict__ info, int32_t *__restrict__ lists,
                                                      int64_t *__restrict__ host) {
   constexpr int PER = BIN_SMALL / 1024;
@@ -360,6 +362,22 @@ __global__ void __launch_bounds__(1024) small_layout(const int64_t *__restrict__
   __syncthreads();
   if (threadIdx.x == 0) host[0] = total;
   if (threadIdx.x < INFO) host[1 + threadIdx.x] = info[threadIdx.x];
+  if (info[HEAVY] == 0) return;  // the same on every thread
+  __shared__ int64_t wmost[1024 / WAVE];
+  int64_t most = 0;
+  sum = 0;
+  for (int64_t i = threadIdx.x; i < m; i += 1024) {
+    sum += w[i];
+    most = max(most, w[i]);
+  }
+  most = wave_max(most);
+  if (lane_id() == 0) wmost[threadIdx.x / WAVE] = most;
+  block_excl_scan<1024>(sum, tmp, &total);
+  if (threadIdx.x == 0) {
+    host[1 + INFO] = total;
+    for (int q = 0; q < 1024 / WAVE; q++) most = max(most, wmost[q]);
+    host[2 + INFO] = most;
+  }
 }
 
 // Sort key putting heavy rows first: descending in a 16-bit code of the
@@ -606,6 +624,26 @@ constexpr int WALK_U = 4;
 // bitmap, masked rows)
 constexpr int COL_U = 8;
 
+// Columns of every product of a laid-out chunk, f(column), in no order.  Where
+// B's rows are short, most batches of eight cross rows and lose their vector
+// loads (300 rows of 20,000 entries, B's rows of 3: 734 us a call with batches
+// of eight, 638 with four single loads; of 16 1,582 and 1,590, of 24 1,899 and
+// 1,935; rows of 4,096 against rows of 400: 1,814 and 1,535 the other way).
+constexpr int COL_MIN = 20;
+template <int BS, class V, class F>
+__device__ __forceinline__ void each_col(const int32_t *__restrict__ cB, int cnt, int32_t total, const Chunk<BS, V> &L,
+                                         F &&f) {
+  if (total >= COL_MIN * cnt) {
+    walk_cols<BS, COL_U, V>(cB, cnt, total, L, [&](const ColBatch<COL_U> &g, int32_t) {
+#pragma unroll
+      for (int u = 0; u < COL_U; u++)
+        if (g.j[u] >= 0) f(g.j[u]);  // -1: past the last product
+    });
+  } else {
+    walk_chunk<BS, WALK_U, false, V, true>(cB, (const V *)nullptr, cnt, total, L, [&](int32_t j, V, V) { f(j); });
+  }
+}
+
 // Lay out one chunk's segments: thread t < cnt owns a segment of `len`
 // products starting at B position `st` with A value `a`.  Returns the total;
 // L is ready to walk when this returns.
@@ -825,28 +863,46 @@ __global__ void __launch_bounds__(BS) sym_bitmap(const int32_t *__restrict__ lis
   }
 }
 
-// Output counts of every row of a small product, one block per row, in one
-// launch: a bitmap over all of B's columns (dynamic LDS, `wwords` words).  No
-// row products, no binning and no host read come before it.
+// Output and product counts of every row of a small product, one block per
+// row, in one launch: a bitmap over all of B's columns (dynamic LDS, `wwords`
+// words).  No row products, no binning and no host read come before it.
 template <int BS>
 __global__ void __launch_bounds__(BS) sym_small(const int64_t *__restrict__ rpA, const int32_t *__restrict__ cA,
                                                 const int64_t *__restrict__ rpB, const int32_t *__restrict__ cB,
-                                                int64_t m, int32_t wwords, int64_t *__restrict__ nnz_row) {
+                                                int64_t m, int32_t wwords, int64_t *__restrict__ nnz_row,
+                                                int64_t *__restrict__ w) {
   extern __shared__ uint32_t bits[];
   __shared__ Chunk<BS, uint8_t> L;
   __shared__ int32_t red[BS / WAVE + 1];
   for (int64_t i = blockIdx.x; i < m; i += gridDim.x) {
     for (int s = threadIdx.x; s < wwords; s += BS) bits[s] = 0;
     __syncthreads();
-    for_products<BS, false, uint8_t>(rpA, cA, (const uint8_t *)nullptr, rpB, cB, (const uint8_t *)nullptr, i, nullptr,
-                                     0, 0, 1, L, [&](int32_t j, uint8_t, uint8_t) {
-      if ((uint32_t)j < (uint32_t)wwords * 32) atomicOr(&bits[j >> 5], 1u << (j & 31));
-    });
+    const int64_t pa = rpA[i], pe = rpA[i + 1];
+    int64_t products = 0;
+    for (int64_t p0 = pa; p0 < pe; p0 += BS) {
+      const int cnt = (int)min((int64_t)BS, pe - p0);
+      int32_t len = 0;
+      int64_t st = 0;
+      if ((int)threadIdx.x < cnt) {
+        const int32_t k = cA[p0 + threadIdx.x];
+        st = rpB[k];
+        len = (int32_t)(rpB[k + 1] - st);
+      }
+      const int32_t total = layout_chunk<BS, false, uint8_t>(len, st, 0, L);
+      each_col<BS>(cB, cnt, total, L, [&](int32_t j) {
+        if ((uint32_t)j < (uint32_t)wwords * 32) atomicOr(&bits[j >> 5], 1u << (j & 31));
+      });
+      products += total;
+      __syncthreads();
+    }
     __syncthreads();
     int32_t mine = 0;
     for (int s = threadIdx.x; s < wwords; s += BS) mine += __popc(bits[s]);
     const int32_t tot = block_sum<BS>(mine, red);
-    if (threadIdx.x == 0) nnz_row[i] = tot;
+    if (threadIdx.x == 0) {
+      nnz_row[i] = tot;
+      w[i] = products;
+    }
   }
 }
 
@@ -2123,6 +2179,7 @@ template <class SR> Schedule budgeted(const Ctx *c, int id) {
 // rows of 10,000 products: 145 and 159).
 constexpr double HUB_BLOCKS = 512.0 / 3;
 constexpr int64_t HUB_PRODUCTS = 1 << 17;
+bool hub_bound(int64_t most, int64_t sum) { return most >= HUB_PRODUCTS && (double)most * HUB_BLOCKS > (double)sum; }
 
 // Numeric bins: 1: <= t_tiny outputs (64-slot hash), 2: <= t_small (512), 3:
 // <= 512 (1024), 4: <= 1024 (2048), 5: <= t_mid (4096), 6: <= t_big (8192),
@@ -2175,7 +2232,7 @@ void numeric_launch(Ctx *c, typename SR::acc_t id, const CsrView &Am, const CsrV
   if (hub && S.dense_wide == 0 && num_dense_lds<SR, 1024, (int)dense_width<SR>(1)>() <= c->lds_budget) S.dense_wide = 1;
   const int64_t n = Bm.n;
   Launch L{c, s};
-  if (w) heavy_first(c, lst + hinfo2[NBIN + HEAVY], hinfo2[HEAVY], w, s);  // (a small product has no order)
+  if (w) heavy_first(c, lst + hinfo2[NBIN + HEAVY], hinfo2[HEAVY], w, s);
   c->tracef("spgemm: schedule %d, nnz %lld; numeric bins %lld %lld %lld %lld %lld %lld %lld", g.sched,
             (long long)hinfo2[SUM], (long long)hinfo2[1], (long long)hinfo2[2], (long long)hinfo2[3],
             (long long)hinfo2[4], (long long)hinfo2[5], (long long)hinfo2[6], (long long)hinfo2[7]);
@@ -2336,28 +2393,45 @@ void spgemm_groups(Ctx *c, IdVal idv, const CsrView &Am, const CsrView &Bm, cons
   // d = 4 98 and 68 us; n = 1,000 d = 8 113 and 81 us; R-MAT 10 d = 16 239 and
   // 144 us, R-MAT 12 391 and 298 us.
   const bool small = G == 1 && !groups[0].row_map && m <= BIN_SMALL && Bm.n <= SMALL_COLS && c->lds_budget >= LDS_BYTES;
+  bool order_heavy = !small;  // the dense rows heaviest first
   if (small) {
     const int32_t ww = (int32_t)((Bm.n + 31) / 32);
     {
       ProfScope ps(c, "spgemm.symbolic.small", 24.0 * m + 4.0 * Am.nnz + 4.0 * Bm.nnz + 8.0 * (Bm.m + 1), s);
-      sym_small<256><<<(unsigned)m, 256, (size_t)ww * 4, s>>>(Am.rowptr, Am.col, Bm.rowptr, Bm.col, m, ww, nnz_row);
+      // Rows of many products, by the average, take twice the threads (1 row of
+      // 4,096 against rows of 400: 1,535 and 1,150 us a call; 300 rows of 20,000
+      // against rows of 10, int32, 832 and 674).
+      const double each = (double)Am.nnz * (double)Bm.nnz / ((double)m * (double)std::max<int64_t>(Bm.m, 1));
+      auto run = [&](auto kern, int bs) {
+        kern<<<(unsigned)m, bs, (size_t)ww * 4, s>>>(Am.rowptr, Am.col, Bm.rowptr, Bm.col, m, ww, nnz_row, w);
+      };
+      if (each < 16384) run(sym_small<256>, 256);
+      else run(sym_small<512>, 512);
       SRTC_LAUNCH_CHECK("sym_small");
     }
-    int64_t *host = (int64_t *)c->host_scratch(sizeof(int64_t) * (size_t)ntab);
+    int64_t *host = (int64_t *)c->host_scratch(sizeof(int64_t) * (size_t)(ntab + 2));
     Thresholds th = numeric_edges(budgeted<SR>(c, groups[0].sched));
     // The shortest rows join the 512-slot bin: all of them run at once in
     // either, and each kernel takes as long as a row does, 9 to 10 us (ER n =
     // 1,000 d = 8: 82 us with a bin of their own, 74 so).
     th.t[0] = 0;
     if (c->profiling)
-      small_layout<true><<<1, 1024, 0, s>>>(nnz_row, m, th, Am.rowptr, out->rowptr.as<int64_t>(), tab + 1, list_of(0),
+      small_layout<true><<<1, 1024, 0, s>>>(nnz_row, w, m, th, Am.rowptr, out->rowptr.as<int64_t>(), tab + 1, list_of(0),
                                             host);
     else
-      small_layout<false><<<1, 1024, 0, s>>>(nnz_row, m, th, Am.rowptr, out->rowptr.as<int64_t>(), tab + 1, list_of(0),
+      small_layout<false><<<1, 1024, 0, s>>>(nnz_row, w, m, th, Am.rowptr, out->rowptr.as<int64_t>(), tab + 1, list_of(0),
                                              host);
     SRTC_LAUNCH_CHECK("small_layout");
     SRTC_HIP(hipStreamSynchronize(s));
     memcpy(htab.data(), host, sizeof(int64_t) * htab.size());
+    if (htab[1 + HEAVY] > 0) {
+      const int64_t sum = host[ntab], most = host[ntab + 1];
+      hub[0] = hub_bound(most, sum);
+      // Heaviest first where not all dense rows start at once and they differ:
+      // 100 rows of 4,000 entries among 4,096 of 8, fp64, 554 us unordered, 472
+      // so; 2,000 like rows lose the 12 us that it takes.
+      order_heavy = htab[1 + HEAVY] > c->num_cus && most * m >= 4 * sum;
+    }
   } else {
     // 1-3. products per row, symbolic bins, symbolic pass (per group)
     {
@@ -2373,7 +2447,7 @@ void spgemm_groups(Ctx *c, IdVal idv, const CsrView &Am, const CsrView &Bm, cons
       const int64_t sum = run_symbolic(L, budgeted<SR>(c, g.sched), Am, Bm, w, g.row_map, nsel,
                                        tab + 1 + (int64_t)q * INFO, list_of(q), nnz_row, sym_err, pass_ctrs(q, 0),
                                        &most);
-      hub[q] = most >= HUB_PRODUCTS && (double)most * HUB_BLOCKS > (double)sum;
+      hub[q] = hub_bound(most, sum);
       products += sum;
     }
     c->tracef("spgemm: symbolic launched, %lld products", (long long)products);
@@ -2397,7 +2471,7 @@ void spgemm_groups(Ctx *c, IdVal idv, const CsrView &Am, const CsrView &Bm, cons
   V *vC = val.as<V>();
   if (total > 0)
     for (int q = 0; q < G; q++)
-      numeric_launch<SR>(c, id, Am, Bm, small ? nullptr : w, groups[q], htab.data() + 1 + (size_t)q * INFO,
+      numeric_launch<SR>(c, id, Am, Bm, order_heavy ? w : nullptr, groups[q], htab.data() + 1 + (size_t)q * INFO,
                          tab + 1 + (int64_t)q * INFO, list_of(q), sorted, OutRows{rpC, nnz_row, 0}, cC, vC, kp, fl,
                          pass_ctrs(q, 1), st, s, hub[q]);
   // 6. compaction when identity results were dropped
