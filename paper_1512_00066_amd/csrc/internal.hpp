@@ -172,7 +172,6 @@ struct Schedule {
 const Schedule &schedule(int id);
 
 struct SpgemmStats {
-  int64_t products = 0;
   int64_t nnz = 0;
   int64_t dense_rows = 0;
   int compacted = 0;

@@ -2451,7 +2451,6 @@ void spgemm_groups(Ctx *c, IdVal idv, const CsrView &Am, const CsrView &Bm, cons
       products += sum;
     }
     c->tracef("spgemm: symbolic launched, %lld products", (long long)products);
-    if (st) st->products = products;
     // 4. rowptr of C, numeric bins; one host read sizes C and every bin
     excl_scan_i64(c, nnz_row, out->rowptr.as<int64_t>(), m, s);
     std::vector<Buf> vbufs(G);
@@ -2722,7 +2721,7 @@ void spgemm_blocked(Ctx *c, IdVal idv, const CsrView &Am, const CsrView &Bm, int
                                pass_ctrs(q, 0));
     }
   }
-  if (st) st->products = products;
+  c->tracef("spgemm: symbolic launched, %lld products", (long long)products);
   // rowptr: heavy rows' totals over blocks, then the scan; block starts
   Buf startq(c, sizeof(int64_t) * (size_t)(Q * m));
   if (nheavy > 0) {
