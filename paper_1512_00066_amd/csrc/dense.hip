@@ -113,14 +113,23 @@ __global__ void __launch_bounds__(WAVE *WM *WN, 2) gemm_mfma(const T *__restrict
     };
     // the terms from k0 on, fewer than a tile; zero beyond
     auto fetch_rest = [&](Regs &r, int64_t k0) {
+      const int64_t ka = k0 + (t % 8) * VEC;
 #pragma unroll
-      for (int i = 0; i < LA; i++)
+      for (int i = 0; i < LA; i++) {
+        r.a[i] = VL{};
+        if (ka + VEC <= ke) {
+          r.a[i] = *(const VG *)at_a(i, k0);
+        } else {
 #pragma unroll
-        for (int e = 0; e < VEC; e++) r.a[i][e] = k0 + (t % 8) * VEC + e < ke ? at_a(i, k0)[e] : (T)0;
+          for (int e = 0; e < VEC - 1; e++)
+            if (ka + e < ke) r.a[i][e] = at_a(i, k0)[e];
+        }
+      }
 #pragma unroll
-      for (int i = 0; i < LB; i++)
-#pragma unroll
-        for (int e = 0; e < VEC; e++) r.b[i][e] = k0 + t / VB + i * RB < ke ? at_b(k0 + i * RB)[e] : (T)0;
+      for (int i = 0; i < LB; i++) {
+        r.b[i] = VL{};
+        if (k0 + t / VB + i * RB < ke) r.b[i] = *(const VG *)at_b(k0 + i * RB);
+      }
     };
     auto stage = [&](const Regs &r, int buf) {
 #pragma unroll
@@ -193,9 +202,9 @@ __global__ void __launch_bounds__(WAVE *WM *WN, 2) gemm_mfma(const T *__restrict
     Regs r0, r1;
     if (nt > 0) {
       fetch(r0, 0);
-      fetch(r1, 1);
+      if (TM > 64 || nt > 1) fetch(r1, 1);  // (the small tile's products may be short)
       stage(r0, 0);
-      fetch(r0, 2);
+      if (TM > 64 || nt > 2) fetch(r0, 2);
     }
     __syncthreads();
     int64_t i = 0;
@@ -487,7 +496,10 @@ namespace {
 // leaves more of the chip idle.  128 x 64 tiles read A's and B's entries less
 // often and gain 1 to 5% (fp64 4096^3 1.99 -> 1.92 ms, fp32 2048^3 0.149 ->
 // 0.142 ms) where their blocks fill the last round of two per CU to at
-// least nine tenths (2560^3, filled to 0.78: 0.53 -> 0.61 ms).
+// least nine tenths (2560^3, filled to 0.78: 0.53 -> 0.61 ms) and cover at most
+// 15% more than the small ones (192 x 16,384 x 2,000 fp64 243 us, 202 with the
+// small tiles; 448 x 8,192 x 2,000 fp32, 14% more, 140 and 145; 2,000 products
+// of 64 x 64 x 64 fp32 in one call 33 and 23).
 // Otherwise k may be split over S blocks.  The time of S parts follows the
 // blocks per CU: one alone takes c1 ns per k-term (it waits on memory), b
 // together c2 b; a split adds a launch (6 us) and its fp64 partial sums
@@ -514,7 +526,7 @@ void gemm_shape(Ctx *c, const T *A, const T *B, T *C, int64_t M, int64_t N, int6
   }
   const int64_t big = blocks(LM * 16 * WM, LN * 16 * WN), small = blocks(64, 64);
   const int64_t round = 2 * cus;
-  if (10 * big >= 9 * ((big + round - 1) / round * round)) {
+  if (40 * big <= 23 * small && 10 * big >= 9 * ((big + round - 1) / round * round)) {
     gemm_launch<T, LM, LN, WM, WN>(c, A, B, C, M, N, K, accumulate, batch, 1, s);
     return;
   }
