@@ -308,6 +308,24 @@ __global__ void __launch_bounds__(256) gemm_narrow(const T *__restrict__ A, cons
   }
 }
 
+// Many small products: one thread per entry of C, products summed in fp64 in
+// order (fp32: exact ones).  Bound by its loads from L1; a 64 x 64 tile per
+// product stages and stores mostly padding (10,000 of 8 x 8 x 8: fp64 85 us,
+// 12.9 so, fp32 96 and 12.0; 16 x 16 x 16 84 and 32, 97 and 16).
+template <class T>
+__global__ void __launch_bounds__(256) gemm_tiny(const T *__restrict__ A, const T *__restrict__ B, T *__restrict__ C,
+                                                 int M, int N, int K, int accumulate, int64_t total) {
+  const int64_t step = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; o < total; o += step) {
+    const int64_t r = o / N, z = r / M;
+    const T *a = A + r * K, *b = B + z * K * N + (o - r * N);
+    double v = 0.0;
+#pragma unroll 4
+    for (int k = 0; k < K; k++) v += (double)a[k] * (double)b[(int64_t)k * N];
+    C[o] = (T)(accumulate ? v + (double)C[o] : v);
+  }
+}
+
 // C (+)= the S partial products of each batch, added in order in fp64.
 template <class T>
 __global__ void gemm_combine(const double *__restrict__ W, T *__restrict__ C, int64_t mn, int S, int64_t total,
@@ -511,6 +529,19 @@ namespace {
 template <class T, int LM, int LN, int WM, int WN>
 void gemm_shape(Ctx *c, const T *A, const T *B, T *C, int64_t M, int64_t N, int64_t K, int accumulate,
                 int64_t batch, hipStream_t s) {
+  // Small products in a batch that gives every CU one and more: a thread per
+  // entry takes 0.75 (fp64) or 0.3 (fp32) ns per 1,000 terms, a 64 x 64 tile,
+  // whatever part of it is used, 3.2 + K / 10 or 4.6 + K / 22 ns.  (Long dot
+  // products stay with the tiles, which split them.)
+  const double each = sizeof(T) == 8 ? 0.75e-3 : 0.3e-3;
+  const double tile = sizeof(T) == 8 ? 3.2 + 0.105 * (double)K : 4.6 + 0.045 * (double)K;
+  if (batch > c->num_cus && K <= 256 && M <= 64 && N <= 64 && each * (double)(M * N * K) <= tile) {
+    const int64_t total = M * N * batch;
+    gemm_tiny<T><<<(unsigned)std::min<int64_t>((total + 255) / 256, 65536), 256, 0, s>>>(A, B, C, (int)M, (int)N, (int)K,
+                                                                                       accumulate, total);
+    SRTC_LAUNCH_CHECK("gemm_tiny");
+    return;
+  }
   if (N < GemmVec<T>::N) {
     gemm_narrow<T><<<(unsigned)std::min<int64_t>((M * batch + 3) / 4, 16384), 256, 0, s>>>(A, B, C, M, (int)N, K,
                                                                                          accumulate, batch);
