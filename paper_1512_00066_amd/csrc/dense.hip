@@ -25,7 +25,7 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 // One tile of C per block: WM x WN waves, each forming NTM x NTN MFMA 16x16
 // tiles, k taken 128 bytes of A's row (16 fp64 or 32 fp32 terms) at a time
 // through two LDS buffers, one barrier per k-tile.  Bound by the matrix
-// cores: fp64 8192^3 47 -> 73 TFLOP/s of 78.6, fp32 8192^3 76 -> 130 of 157
+// cores: fp64 8192^3 47 -> 72 TFLOP/s of 78.6, fp32 8192^3 76 -> 130 of 157
 // (single-entry loads and LDS accesses, one tile of 128 x 128 per block and
 // accumulators spilled before).  The 16-byte global loads run two k-tiles
 // ahead in registers: with one tile of distance the matrix cores waited for

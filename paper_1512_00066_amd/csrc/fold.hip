@@ -23,7 +23,7 @@ namespace {
 // 40 bits with fp32 values: 76 us a scatter (5.3 TB/s; 64 registers a thread
 // are two blocks a CU, and spilling a few of them costs it 176 us), 27 us a
 // histogram; whole fold 2,335 us with 2,048-key tiles, a gather of the values
-// after the sort and segment arrays in memory, 746 us so.
+// after the sort and segment arrays in memory, 723 us so.
 constexpr int RS_BS = 1024;           // threads per tile
 constexpr int RS_IT = 8;              // keys per thread
 constexpr int RS_TILE = RS_BS * RS_IT;
@@ -304,8 +304,8 @@ __global__ void __launch_bounds__(RS_BS) radix_one_tile(const uint64_t *kin, con
 }
 
 // Sorted pairs end in ka/pa when `passes` is odd, in kb/pb when it is even
-// (pass 0 reads kin/pin and writes ka/pa).  kin/pin may be kb/pb, and with
-// one tile ka/pa is written in either case.
+// (pass 0 reads kin/pin and writes ka/pa), also where one tile takes all passes
+// at once.  kin/pin may be kb/pb, and with one tile either pair.
 template <class P, bool MAP>
 void radix_sort(Ctx *c, const uint64_t *kin, const P *pin, const KeyMap &km, int64_t n, int passes, uint64_t *ka, P *pa,
                 uint64_t *kb, P *pb, hipStream_t s) {

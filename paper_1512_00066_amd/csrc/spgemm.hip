@@ -2390,8 +2390,8 @@ void spgemm_groups(Ctx *c, IdVal idv, const CsrView &Am, const CsrView &Bm, cons
   // of 2 KB) is launches and host reads, not work: output counts of all rows
   // in one launch, then row pointers and bins in one, and one read.  Median
   // call with the passes below and so, R-MAT in fp64, ER in int32: ER n = 100
-  // d = 4 98 and 68 us; n = 1,000 d = 8 113 and 81 us; R-MAT 10 d = 16 239 and
-  // 144 us, R-MAT 12 391 and 298 us.
+  // d = 4 98 and 71 us; n = 1,000 d = 8 113 and 74 us; R-MAT 10 d = 16 239 and
+  // 139 us, R-MAT 12 391 and 268 us.
   const bool small = G == 1 && !groups[0].row_map && m <= BIN_SMALL && Bm.n <= SMALL_COLS && c->lds_budget >= LDS_BYTES;
   bool order_heavy = !small;  // the dense rows heaviest first
   if (small) {

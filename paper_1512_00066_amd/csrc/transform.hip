@@ -283,8 +283,8 @@ __global__ void __launch_bounds__(JAC_BS) jacobi_step(const int64_t *__restrict_
 // ones); on the CSR, eight lanes per row, about 25 vector instructions per
 // entry bound it instead.  Blocks of one XCD take neighbouring slices, so its
 // L2 holds its part of x_in.  Stencil 100^3 (26.5 M nonzeros), per update:
-// fp64 103 us before (83 the step, 17 the separate sum), 65.6 now (100 on the
-// CSR); fp32 49.6 (69 on the CSR); stencil 50^3 fp64 14.8 (16.7).
+// fp64 103 us before (83 the step, 17 the separate sum), 61.6 now (100 on the
+// CSR); fp32 45.9 (69 on the CSR); stencil 50^3 fp64 14.9 (16.7).
 template <class T, class C>
 __global__ void __launch_bounds__(JAC_BS, 8) jacobi_slices(const int64_t *__restrict__ start, const C *__restrict__ off,
                                                         const T *__restrict__ sval, const T *__restrict__ d,
