@@ -746,11 +746,17 @@ inline RowFeed row_feed(int64_t *ctr, int64_t rows, int64_t grid) {
 }
 // The same for rows that are long and sorted heaviest first: one at a time,
 // from one counter below 4,096 of them (at most 50 us of fetches, spread
-// over a launch of long rows, and the better balance).
-inline RowFeed heavy_feed(int64_t *ctr, int64_t rows, int64_t grid) {
+// over a launch of long rows, and the better balance), and from one counter
+// whatever their number where `slow`, each row keeps its block so long that one
+// counter is never short.  Shards drift apart, so that resident blocks work on
+// less alike rows and share less of B in L2: R-MAT 21 in panels, schedule 3,
+// 1,720 ms a step with 16 shards, 1,677 with one counter (fetched per panel,
+// fp64, 201 and 186 GB).  Rows of a few thousand products need the shards (ER n
+// = 100,000 d = 50, schedule 7: 4.01 and 4.49 ms with one counter).
+inline RowFeed heavy_feed(int64_t *ctr, int64_t rows, int64_t grid, bool slow = false) {
   RowFeed f = row_feed(ctr, rows, grid);
   f.step = 1;
-  if (rows < 4096) f.nsh = 1;
+  if (rows < 4096 || slow) f.nsh = 1;
   return f;
 }
 
@@ -2064,7 +2070,7 @@ int64_t run_symbolic(const Launch &L, const Schedule &S, const CsrView &Am, cons
       SRTC_HIP(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, ww * 4));
     const unsigned grid = L.grid(hinfo[HEAVY], stat + ww * 4, BS);
     kern<<<grid, BS, (size_t)ww * 4, s>>>(list, info1, HEAVY, Am.rowptr, Am.col, Bm.rowptr, Bm.col, n, ww, wo, nwin,
-                                          nnz_row, heavy_feed(ctr1(HEAVY), hinfo[HEAVY], grid));
+                                          nnz_row, heavy_feed(ctr1(HEAVY), hinfo[HEAVY], grid, S.sym_hash_max >= 8192));
     SRTC_LAUNCH_CHECK("sym_bitmap");
   }
   if (most) *most = hinfo[MAXV];
@@ -2104,7 +2110,7 @@ template <class SR> struct NumLaunch {
     const unsigned grid = L.grid(rows, stat, BS);
     num_dense<SR, BS, W><<<grid, BS, 0, L.s>>>(
         list, info, bin, Am.rowptr, Am.col, (const V *)Am.val, Bm.rowptr, Bm.col, (const V *)Bm.val, Bm.n, woff,
-        nwin, orows, cC, vC, id, kept, any_short, heavy_feed(ctr, rows, grid), rB);
+        nwin, orows, cC, vC, id, kept, any_short, heavy_feed(ctr, rows, grid, BS >= 1024), rB);
     SRTC_LAUNCH_CHECK("num_dense");
   }
 };
